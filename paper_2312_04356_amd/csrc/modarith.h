@@ -14,6 +14,9 @@
 //   mul_lazy:   |a| <= 2^50, b in [0, t)    -> exact representative in (-t, t)
 //   corr:       integer s in (-t, 2t)       -> [0, t)
 //   reduce:     integer |x| < 2^53          -> [0, t)
+//   reduce_c:   integer |x| < 2^53          -> centred, |r| <= t/2 + 2 (half of reduce's cost)
+// Centred words are what transforms keep between their rounds and passes: 3 operations
+// instead of 6 per word and round, and headroom for one more doubling.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -89,6 +92,24 @@ NJ_HD double reduce(double x, Mod m)
 {
     double c = rint(x * m.ti);
     return corr(fma(-c, m.t, x), m);
+}
+
+// any exact integer |x| < 2^53  ->  the representative next to 0, |r| <= t/2 + 2 (the
+// quotient's error is below |x/t| 2^-52, times t at most 2)
+NJ_HD double reduce_c(double x, Mod m)
+{
+    double c = rint(x * m.ti);
+    return fma(-c, m.t, x);
+}
+
+// mul_shoup without its last correction: |b| <= 1.5 t, w in [0, t), wq = fl(w/t) -> exact
+// representative within (-t, t): |b wq - b w/t| <= 2u 1.5 2^50 = 3/8, so |r| <= 7/8 t
+NJ_HD double mul_shoup_lazy(double b, double w, double wq, Mod m)
+{
+    double h = b * w;
+    double l = fma(b, w, -h);
+    double c = rint(b * wq);
+    return fma(-c, m.t, h) + l;
 }
 
 NJ_HD double add_mod(double a, double b, Mod m) { return corr(a + b, m); }

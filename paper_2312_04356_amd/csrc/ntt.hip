@@ -22,14 +22,25 @@ namespace nj {
 constexpr int kT = 4096;
 constexpr int kNT = 256;
 
+// FP64 values between passes, stored in a word's place
+__device__ __forceinline__ double b2d(uint64_t x) { return __longlong_as_double((long long)x); }
+__device__ __forceinline__ uint64_t d2b(double x) { return (uint64_t)__double_as_longlong(x); }
+
 __device__ __forceinline__ int pad16(int x) { return x + (x >> 4); }
 
-// Forward rounds are lazy: a round takes canonical words, runs its 4 stages without
-// correction and reduces once at the end.  With t < 2^50 the lazy product of a word
-// below B t in magnitude lies within (1/2 + 3B/8) t (the quotient estimate is off by
-// at most 1/2 + 3 ulp-relative errors of a value below B 2^50), so the bound grows
-// 1 -> 1.875 -> 3.08 -> 4.73 -> 7.01 over 4 stages: every intermediate is an integer
-// below 2^53, computed exactly.
+// Rounds are lazy in both directions: 4 stages without correction, one centred reduction
+// (reduce_c) per word at the end.  With t < 2^50 the lazy product of a word below B t in
+// magnitude lies within (1/2 + 3B/8) t (the quotient estimate is off by at most 1/2 + 3
+// ulp-relative errors of a value below B 2^50).
+//   Forward: the bound grows 1 -> 1.875 -> 3.08 -> 4.73 -> 7.01 over 4 stages from
+//   canonical words (1/2 -> 5.22 from centred ones).
+//   Inverse: sums double, 1/2 -> 1 -> 2 -> 4 -> 8 from centred words (products of
+//   differences stay below 3.5); from canonical words the two words that are sums all the
+//   way reach 8 after 3 stages and are reduced before the last one (7 for the others).
+// So every intermediate is an integer below 2^53 (8 t + 32 < 2^53 for t <= 2^50 - 4),
+// computed exactly.  A butterfly costs 9.5 FP64 operations, rounds included, in either
+// direction.  Words travel between the passes of one transform as FP64 values, centred;
+// what leaves a transform is canonical.
 
 // one round of 4 forward stages on 16 registers (strides t0 .. t0/8 within the tile)
 __device__ __forceinline__ void ct_round(double v[16], int t0, int hi, int tile, int logN1, const double *W, int N,
@@ -51,15 +62,18 @@ __device__ __forceinline__ void ct_round(double v[16], int t0, int hi, int tile,
         }
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce(v[k], m);
+    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
 }
 
-// one round of 4 inverse stages (strides t0/8 .. t0)
+// one round of 4 inverse stages (strides t0/8 .. t0); CANON: canonical words on entry, else
+// centred
+template <bool CANON>
 __device__ __forceinline__ void gs_round(double v[16], int t0, int hi, int tile, int logN1, const double *W, int N,
                                          Mod m)
 {
 #pragma unroll
     for (int s = 3; s >= 0; s--) {
+        if (CANON && s == 0) v[0] = reduce_c(v[0], m), v[8] = reduce_c(v[8], m);
         const int t = t0 >> s;
         const int hh = N / (2 * t);
         const int base = hh + tile * (hh >> logN1) + (hi << s);
@@ -69,10 +83,12 @@ __device__ __forceinline__ void gs_round(double v[16], int t0, int hi, int tile,
             if (k & step) continue;
             const double w = W[base + (k >> (4 - s))];
             const double U = v[k], V = v[k + step];
-            v[k] = corr(U + V, m);
-            v[k + step] = corr(mul_lazy(U - V, w, m), m);  // U - V in (-t, t)
+            v[k] = U + V;
+            v[k + step] = mul_lazy(U - V, w, m);
         }
     }
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
 }
 
 // The 15 twiddles of one round (tile strides t0 .. t0/8) of butterfly block hi: stage
@@ -104,26 +120,31 @@ __device__ __forceinline__ void ct_round_tw(double v[16], const double tw[15], M
         }
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce(v[k], m);
+    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
 }
 
+template <bool CANON>
 __device__ __forceinline__ void gs_round_tw(double v[16], const double tw[15], Mod m)
 {
 #pragma unroll
     for (int st = 3; st >= 0; st--) {
         const int step = 8 >> st;
+        if (CANON && st == 0) v[0] = reduce_c(v[0], m), v[8] = reduce_c(v[8], m);
 #pragma unroll
         for (int k = 0; k < 16; k++) {
             if (k & step) continue;
             const double U = v[k], V = v[k + step];
-            v[k] = corr(U + V, m);
-            v[k + step] = corr(mul_lazy(U - V, tw[(1 << st) - 1 + (k >> (4 - st))], m), m);  // U - V in (-t, t)
+            v[k] = U + V;
+            v[k + step] = mul_lazy(U - V, tw[(1 << st) - 1 + (k >> (4 - st))], m);
         }
     }
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
 }
 
-// The last 12 forward stages of one 4096-word tile: v holds words tid + 256 k on
-// entry; on return the transformed tile is in s (word x at pad16(x)), after a barrier.
+// The last 12 forward stages of one 4096-word tile: v holds words tid + 256 k (canonical
+// or centred) on entry; on return the transformed tile is in s (word x at pad16(x),
+// centred), after a barrier.
 // Each round's twiddles are requested before the barrier that precedes the round (the
 // registers of v are free there), so their latency overlaps the barrier wait.
 __device__ __forceinline__ void tile_forward(double v[16], double *s, int tid, int tile, int logN1, const double *W,
@@ -156,8 +177,9 @@ __device__ __forceinline__ void tile_forward(double v[16], double *s, int tid, i
 }
 
 // The first 12 inverse stages of one 4096-word tile (inverse twiddles W): v holds
-// words tid + 256 k on entry and on return; s must be free on entry (callers that used
-// it before put a barrier first).  Twiddles requested ahead as in tile_forward.
+// words tid + 256 k on entry (canonical or centred) and on return (centred); s must be
+// free on entry (callers that used it before put a barrier first).  Twiddles requested
+// ahead as in tile_forward.
 __device__ __forceinline__ void tile_inverse(double v[16], double *s, int tid, int tile, int logN1, const double *W,
                                              int N, Mod m)
 {
@@ -168,7 +190,7 @@ __device__ __forceinline__ void tile_inverse(double v[16], double *s, int tid, i
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
-    gs_round_tw(v, tw, m);
+    gs_round_tw<true>(v, tw, m);
 #pragma unroll
     for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
     const int lo = tid & 15, hi = tid >> 4;
@@ -176,14 +198,14 @@ __device__ __forceinline__ void tile_inverse(double v[16], double *s, int tid, i
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
-    gs_round_tw(v, tw, m);
+    gs_round_tw<false>(v, tw, m);
 #pragma unroll
     for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
     round_tw(tw, 2048, 0, tile, logN1, W, N);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = s[pad16(tid + 256 * k)];
-    gs_round_tw(v, tw, m);
+    gs_round_tw<false>(v, tw, m);
 }
 
 // tile_forward and tile_inverse with each round's twiddles loaded where they are used
@@ -223,7 +245,7 @@ __device__ __forceinline__ void tile_inverse_lean(double v[16], double *s, int t
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
-    gs_round(v, 8, tid, tile, logN1, W, N, m);
+    gs_round<true>(v, 8, tid, tile, logN1, W, N, m);
 #pragma unroll
     for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
     __syncthreads();
@@ -231,14 +253,14 @@ __device__ __forceinline__ void tile_inverse_lean(double v[16], double *s, int t
         const int lo = tid & 15, hi = tid >> 4;
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
-        gs_round(v, 128, hi, tile, logN1, W, N, m);
+        gs_round<false>(v, 128, hi, tile, logN1, W, N, m);
 #pragma unroll
         for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = s[pad16(tid + 256 * k)];
-    gs_round(v, 2048, 0, tile, logN1, W, N, m);
+    gs_round<false>(v, 2048, 0, tile, logN1, W, N, m);
 }
 
 // The twiddles of one tile's forward pass (last 12 stages), for blocks that transform
@@ -303,7 +325,7 @@ __device__ __forceinline__ void ct_round_lds(double v[16], const double *tws, in
         }
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce(v[k], m);
+    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
 }
 
 // tile_forward with the twiddles staged by stage_tile_twiddles
@@ -330,7 +352,8 @@ __device__ __forceinline__ void tile_forward_lds(double v[16], double *s, const 
     __syncthreads();
 }
 
-// rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs)
+// rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs).  With a column pass
+// beside it (N > 4096) the forward's input and the inverse's output are its FP64 words.
 template <bool INV>
 __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t *src, LimbTab lt, const double *tw,
                                                   const PrimeInfo *info, int logN)
@@ -346,21 +369,27 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t
     const double *W = tw + (size_t)pidx * N;
     double v[16];
     if (!INV) {
+        if (logN1 == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+            for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
+        }
         tile_forward(v, s, tid, tile, logN1, W, N, m);
 #pragma unroll
-        for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(s[pad16(tid + 256 * k)]);
+        for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(corr(s[pad16(tid + 256 * k)], m));
     } else {
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
         tile_inverse(v, s, tid, tile, logN1, W, N, m);
         if (logN1 == 0) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) v[k] = mul_canon(v[k], pi.ninv, m);
-        }
+            for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(corr(mul_lazy(v[k], pi.ninv, m), m));
+        } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(v[k]);
+            for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2b(v[k]);
+        }
     }
 }
 
@@ -374,11 +403,11 @@ __device__ __forceinline__ void store_p_rows(double a0[16], double a1[16], doubl
     __syncthreads();
     tile_inverse(a0, s, tid, tile, logN1, W, N, m);
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[w0 + 256 * k] = d2u(a0[k]);
+    for (int k = 0; k < 16; k++) out[w0 + 256 * k] = d2b(a0[k]);
     __syncthreads();
     tile_inverse(a1, s, tid, tile, logN1, W, N, m);
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[half_off + w0 + 256 * k] = d2u(a1[k]);
+    for (int k = 0; k < 16; k++) out[half_off + w0 + 256 * k] = d2b(a1[k]);
 }
 
 // x words of step q = z ND + j of a key inner product (job z, digit j) at words
@@ -459,8 +488,13 @@ __global__ __launch_bounds__(kNT, 2) void k_ntt_ip(KeyJobs kj, int n_jobs, uint6
         const int z = q / ND, j = q - z * ND;
         const bool own = j == r.own;
         double x[16];
+        if (own) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = u2d(xn[k]);
+            for (int k = 0; k < 16; k++) x[k] = u2d(xn[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = b2d(xn[k]);
+        }
         if (q + 1 < q1) ip_load_x<ND>(kj, r, q + 1, (uint32_t)w0, logN, (uint32_t)N, xn);
         if (!own) {
             __syncthreads();  // the previous step's words have been read out of s
@@ -483,7 +517,7 @@ __global__ __launch_bounds__(kNT, 2) void k_ntt_ip(KeyJobs kj, int n_jobs, uint6
         }
         if (j == ND - 1) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) a0[k] = reduce(a0[k], m), a1[k] = reduce(a1[k], m);
+            for (int k = 0; k < 16; k++) a0[k] = reduce_c(a0[k], m), a1[k] = reduce_c(a1[k], m);
         }
     }
     if (pout && t > level) {  // special-prime rows: on to ModDown's inverse transform
@@ -493,8 +527,8 @@ __global__ __launch_bounds__(kNT, 2) void k_ntt_ip(KeyJobs kj, int n_jobs, uint6
     }
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        u[o0 + 256 * k] = d2u(a0[k]);
-        u[o1 + 256 * k] = d2u(a1[k]);
+        u[o0 + 256 * k] = d2u(corr(a0[k], m));
+        u[o1 + 256 * k] = d2u(corr(a1[k], m));
     }
 }
 
@@ -535,11 +569,11 @@ __global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, 
             acc[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 2048u * k)), m);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) acc[k] = reduce(acc[k], m);
+    for (int k = 0; k < 16; k++) acc[k] = reduce_c(acc[k], m);
     tile_inverse(acc, s, tid, tile, logN1, itw + (size_t)pidx * N, N, m);
     uint64_t *out = pout + ((size_t)(2 * z + p) * alpha + a) * N + w0;
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[256 * k] = d2u(acc[k]);
+    for (int k = 0; k < 16; k++) out[256 * k] = d2b(acc[k]);
 }
 
 // Inverse tile pass whose input limbs are read through X -> X^g (the automorphism of a
@@ -565,11 +599,11 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_gal(uint64_t *data, const uint
     tile_inverse(v, s, tid, tile, logN1, tw + (size_t)pidx * N, N, m);
     uint64_t *out = data + (size_t)lt.off[limb] * N + w0;
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[256 * k] = d2u(v[k]);
+    for (int k = 0; k < 16; k++) out[256 * k] = d2b(v[k]);
 }
 
-// The first log2(N1) forward stages on one column of N1 canonical words (lazy, one
-// reduction at the end: at most 4 stages).
+// The first log2(N1) forward stages on one column of N1 words, canonical or centred (lazy,
+// one centred reduction at the end: at most 4 stages).
 template <int N1>
 __device__ __forceinline__ void col_forward(double v[N1], const double *W, Mod m)
 {
@@ -586,14 +620,33 @@ __device__ __forceinline__ void col_forward(double v[N1], const double *W, Mod m
         }
     }
 #pragma unroll
-    for (int r = 0; r < N1; r++) v[r] = reduce(v[r], m);
+    for (int r = 0; r < N1; r++) v[r] = reduce_c(v[r], m);
+}
+
+// The last log2(N1) inverse stages on one column of N1 centred words, uncorrected: at
+// most 4 stages, 8 t in magnitude.
+template <int N1>
+__device__ __forceinline__ void col_inverse(double v[N1], const double *W, Mod m)
+{
+#pragma unroll
+    for (int h = N1 / 2; h >= 1; h >>= 1) {
+        const int tr = N1 / (2 * h);
+#pragma unroll
+        for (int r = 0; r < N1; r++) {
+            if (r & tr) continue;
+            const double w = W[h + r / (2 * tr)];
+            const double U = v[r], V = v[r + tr];
+            v[r] = U + V;
+            v[r + tr] = mul_lazy(U - V, w, m);
+        }
+    }
 }
 
 // columns pass: first log2(N1) stages, one column of N1 words per thread.  grid (4096/256, limbs).
 // The inverse ends with the factor N^-1, or scale[pidx] when a scale table is given
 // (N^-1 times a basis conversion's input factor, so the conversion need not apply it).
-// DBL: the results are stored as FP64 values (bit patterns of exact integers in [0, t))
-// for the fused basis conversion, which then skips the integer -> FP64 step.
+// The forward's results go to the tile pass as centred FP64 values; the inverse's are
+// canonical, stored as FP64 values too when DBL (for the fused basis conversion).
 template <int N1, bool INV, bool DBL = false>
 __global__ __launch_bounds__(kNT) void k_ntt_col(uint64_t *data, const uint64_t *src, LimbTab lt, const double *tw,
                                                  const PrimeInfo *info, int logN, const double *scale)
@@ -609,29 +662,20 @@ __global__ __launch_bounds__(kNT) void k_ntt_col(uint64_t *data, const uint64_t 
     const double *W = tw + (size_t)pidx * N;
     double v[N1];
 #pragma unroll
-    for (int r = 0; r < N1; r++) v[r] = u2d(buf_ld(in, cb, 8u * r * kT));
+    for (int r = 0; r < N1; r++) {
+        const uint64_t x = buf_ld(in, cb, 8u * r * kT);
+        v[r] = INV ? b2d(x) : u2d(x);
+    }
     if (!INV) {
         col_forward<N1>(v, W, m);
     } else {
-#pragma unroll
-        for (int h = N1 / 2; h >= 1; h >>= 1) {
-            const int tr = N1 / (2 * h);
-#pragma unroll
-            for (int r = 0; r < N1; r++) {
-                if (r & tr) continue;
-                const double w = W[h + r / (2 * tr)];
-                const double U = v[r], V = v[r + tr];
-                v[r] = corr(U + V, m);
-                v[r + tr] = corr(mul_lazy(U - V, w, m), m);
-            }
-        }
+        col_inverse<N1>(v, W, m);
         const double sc = scale ? scale[pidx] : pi.ninv;
 #pragma unroll
-        for (int r = 0; r < N1; r++) v[r] = mul_canon(v[r], sc, m);
+        for (int r = 0; r < N1; r++) v[r] = reduce(mul_lazy(v[r], sc, m), m);
     }
 #pragma unroll
-    for (int r = 0; r < N1; r++)
-        buf_st(out, cb, 8u * r * kT, DBL ? (uint64_t)__double_as_longlong(v[r]) : d2u(v[r]));
+    for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, !INV || DBL ? d2b(v[r]) : d2u(v[r]));
 }
 
 // Basis conversion fused with the first log2(N1) forward stages of its outputs (the
@@ -688,19 +732,19 @@ __global__ __launch_bounds__(kNT) void k_bconv_col(BconvShared sh, BconvPtrs jp,
 #pragma unroll
             for (int q = 0; q < kBcOut; q++)
 #pragma unroll
-                for (int r = 0; r < N1; r++) acc[q][r] = reduce(acc[q][r], mo[q]);
+                for (int r = 0; r < N1; r++) acc[q][r] = reduce_c(acc[q][r], mo[q]);
         }
     }
 #pragma unroll
     for (int q = 0; q < kBcOut; q++) {
 #pragma unroll
-        for (int r = 0; r < N1; r++) acc[q][r] = reduce(acc[q][r], mo[q]);
+        for (int r = 0; r < N1; r++) acc[q][r] = reduce_c(acc[q][r], mo[q]);
         const int pq = sh.out_pidx[j][o[q]];
         col_forward<N1>(acc[q], tw + (size_t)pq * N, mo[q]);
         if (o0 + q < n_out) {
             const auto out = buf_rsrc(jp.out[job] + (size_t)sh.out_off[j][o[q]] * N, 8u * N);
 #pragma unroll
-            for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, d2u(acc[q][r]));
+            for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, d2b(acc[q][r]));
         }
     }
 }
@@ -716,8 +760,8 @@ __global__ __launch_bounds__(kNT) void k_bconv_col(BconvShared sh, BconvPtrs jp,
 // grid (N/4096, 2 K (l+1)): limb w = (2 z + p)(l+1) + i.
 template <bool CONJ>
 __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, const uint64_t *u_base, MdJobs mj, int acc,
-                                                     int level, int ne, const double *pinv, const double *tw,
-                                                     const PrimeInfo *info, int logN, const uint64_t *acc0,
+                                                     int level, int ne, const double *pinv, const double *pinvq,
+                                                     const double *tw, const PrimeInfo *info, int logN, const uint64_t *acc0,
                                                      uint64_t *last_out, const double *itw, MdConj cj, int skip)
 {
     __shared__ double s[kT + kT / 16];
@@ -729,23 +773,29 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
     const size_t t0 = (size_t)tile * kT;
     const uint64_t *in = conv + ((size_t)h * L1 + i) * N + t0;
     double v[16];
+    if (logN1 == 0) {
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+        for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
+    }
     tile_forward_lean(v, s, tid, tile, logN1, W, N, m);
     const uint64_t *u = u_base + ((size_t)z * 2 * ne + (size_t)p * ne + i) * N + t0;
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     const uint32_t g = mj.g_add[z];
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
     const uint64_t *prev = acc0 && z == 0 ? acc0 + ((size_t)p * L1 + i) * N + t0 : out;
-    const double pv = pinv[i];
+    const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const int x = tid + 256 * k;
-        double t = mul_canon(sub_mod(u2d(u[x]), s[pad16(x)], m), pv, m);
+        double t = mul_shoup_lazy(u2d(u[x]) - s[pad16(x)], pv, pvq, m);  // u in [0, t), s centred
         if (add) {
             const int kk = (int)t0 + x;
-            t = add_mod(t, u2d(add[(size_t)i * N + (g <= 1u ? kk : galois_src2(kk, g, logN))]), m);
+            t += u2d(add[(size_t)i * N + (g <= 1u ? kk : galois_src2(kk, g, logN))]);
         }
+        t = corr(t, m);
         if (acc) t = add_mod(t, u2d(prev[x]), m);
         if (CONJ) {  // the real/imaginary split, as in k_conj_split
             const size_t o = ((size_t)p * L1 + i) * N + t0 + x;
@@ -764,7 +814,7 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
         __syncthreads();
         tile_inverse_lean(v, s, tid, tile, logN1, itw + (size_t)i * N, N, m);
 #pragma unroll
-        for (int k = 0; k < 16; k++) last_out[(size_t)p * N + t0 + tid + 256 * k] = d2u(v[k]);
+        for (int k = 0; k < 16; k++) last_out[(size_t)p * N + t0 + tid + 256 * k] = d2b(v[k]);
     }
 }
 
@@ -777,8 +827,8 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
 // (N/4096, 2 K (l+1)).
 template <int ND>
 __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_md(const uint64_t *conv, KeyJobs kj, MdJobs mj, int level, int L,
-                                                      int alpha, const double *pinv, const double *tw,
-                                                      const PrimeInfo *info, int logN)
+                                                      int alpha, const double *pinv, const double *pinvq,
+                                                      const double *tw, const PrimeInfo *info, int logN)
 {
     __shared__ double s[kT + kT / 16];
     const int N = 1 << logN, logN1 = logN - 12, L1 = level + 1;
@@ -814,26 +864,26 @@ __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_m
             }
         }
 #pragma unroll
-        for (int k = 0; k < 16; k++) a[k] = reduce(a[k], m);
+        for (int k = 0; k < 16; k++) a[k] = reduce_c(a[k], m);
     }
     const uint64_t *in = conv + ((size_t)h * L1 + i) * N + t0;
     double v[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+    for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
     tile_forward_lean(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     const uint32_t ga = mj.g_add[z];
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
-    const double pv = pinv[i];
+    const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const int x = tid + 256 * k;
-        double t = mul_canon(sub_mod(a[k], s[pad16(x)], m), pv, m);
+        double t = mul_shoup_lazy(a[k] - s[pad16(x)], pv, pvq, m);  // both centred
         if (add) {
             const int kk = (int)t0 + x;
-            t = add_mod(t, u2d(add[(size_t)i * N + (ga <= 1u ? kk : galois_src2(kk, ga, logN))]), m);
+            t += u2d(add[(size_t)i * N + (ga <= 1u ? kk : galois_src2(kk, ga, logN))]);
         }
-        out[x] = d2u(t);
+        out[x] = d2u(corr(t, m));
     }
 }
 
@@ -853,12 +903,12 @@ __global__ __launch_bounds__(kNT) void k_lift_col(const uint64_t *last, int src_
 #pragma unroll
     for (int r = 0; r < N1; r++) {
         const double x = u2d(buf_ld(src, cb, 8u * r * kT));
-        v[r] = reduce(x > half ? x - ms.t : x, mt);  // centred, |x| < t_l / 2 < 2^49
+        v[r] = reduce_c(x > half ? x - ms.t : x, mt);  // centred, |x| < t_l / 2 < 2^49
     }
     col_forward<N1>(v, tw + (size_t)i * N, mt);
     const auto dst = buf_rsrc(lifted + ((size_t)z * n_out + i) * N, 8u * N);
 #pragma unroll
-    for (int r = 0; r < N1; r++) buf_st(dst, cb, 8u * r * kT, d2u(v[r]));
+    for (int r = 0; r < N1; r++) buf_st(dst, cb, 8u * r * kT, d2b(v[r]));
 }
 
 // k_ntt_tile_rs: the lifted limbs' tile pass with the rescale combine as its epilogue,
@@ -876,7 +926,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
     const uint64_t *src = lifted + (size_t)w * N + t0;
     double v[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = u2d(src[tid + 256 * k]);
+    for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
     tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
     const uint64_t *a = in + ((size_t)z * (level + 1) + i) * N + t0;
     uint64_t *o = out + ((size_t)z * n_out + i) * N + t0;
@@ -884,7 +934,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const int x = tid + 256 * k;
-        o[x] = d2u(mul_shoup(sub_mod(u2d(a[x]), s[pad16(x)], m), wl, wlq, m));
+        o[x] = d2u(corr(mul_shoup_lazy(u2d(a[x]) - s[pad16(x)], wl, wlq, m), m));
     }
 }
 
@@ -1038,9 +1088,9 @@ hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv,
     const double bytes = 8.0 * N * (n * 3.0 + K * (L1 - skip) + (acc ? n : 0));
     if (conj)
         return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<true>, dim3(N1, n), dim3(kNT), s, conv, u_base, mj, acc,
-                      level, L1 + c->alpha, c->d_pinv, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip);
+                      level, L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip);
     return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<false>, dim3(N1, n), dim3(kNT), s, conv, u_base, mj, acc, level,
-                  L1 + c->alpha, c->d_pinv, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip);
+                  L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip);
 }
 
 // The plain ModDown combine of K key switches (converted limbs column-passed) with their
@@ -1055,7 +1105,7 @@ hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64
 #define NJ_IPMD(ND)                                                                                                \
     case ND:                                                                                                       \
         return launch(c, PROF_KEYIP, bytes, k_key_ip_md<ND>, dim3(N1, n), dim3(kNT), s, conv, kj, mj, level, c->L, \
-                      c->alpha, c->d_pinv, c->d_tw, c->d_info, c->log_n);
+                      c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n);
     switch (nd) {
         NJ_IPMD(1) NJ_IPMD(2) NJ_IPMD(3) NJ_IPMD(4)
     }
