@@ -117,12 +117,12 @@ nj_status modup_multi(nj_ctx *c, int l, int K, const uint64_t *d, MultiBufs &M, 
 {
     const auto &tabs = drop ? c->modup_drop[l] : c->modup[l];
     const int N = c->N, ne = l + 1 + c->alpha, nd = n_digits(c, l);
-    // N >= 8192: the conversion's input factors ride on the inverse transform, and the
-    // conversion runs fused with its outputs' column pass
+    // N >= 8192: the conversion finishes its inputs' inverse transform (their factors ride on
+    // it) and starts its outputs' forward one
     const bool fused = N >= 8192 && c->alpha <= 8;
     if (gt && !fused) return fail(NJ_EUNSUPPORTED, "ModUp through an automorphism needs N >= 8192");
     auto intt = [&](const LimbTab &t) {
-        return fused ? launch_intt_scaled(c, M.coef, d, t, c->d_upscale[l], s, gt, l + 1)
+        return fused ? launch_intt_tiles(c, M.coef, d, t, s, gt, l + 1)
                      : launch_ntt(c, M.coef, t, true, s, d);
     };
     if (dstride < 0) dstride = l + 1;
@@ -150,7 +150,7 @@ nj_status modup_multi(nj_ctx *c, int l, int K, const uint64_t *d, MultiBufs &M, 
         }
         BconvPtrs jp;
         for (int z = 0; z < K; z++) jp.in[z] = M.coef + (size_t)z * (l + 1) * N, jp.out[z] = M.ext + (size_t)z * nd * ne * N;
-        NJ_HIP(fused ? launch_bconv_col(c, sh, jp, K, s) : launch_bconv_multi(c, sh, jp, K, s));
+        NJ_HIP(fused ? launch_bconv_col(c, sh, jp, K, c->d_upscale[l], s) : launch_bconv_multi(c, sh, jp, K, s));
     }
     if (fused && !tiles) return NJ_OK;  // the key inner product runs the tile pass
     auto ntt = [&](const LimbTab &t) { return fused ? launch_ntt_tiles(c, M.ext, t, s) : launch_ntt(c, M.ext, t, false, s); };
@@ -211,12 +211,11 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
     if (acc && !sum && K == 1 && acc != mj.out[0] && !one)
         NJ_HIP(hipMemcpyAsync(mj.out[0], acc, 2 * (size_t)(l + 1) * N * 8, hipMemcpyDeviceToDevice, s));
     auto intt = [&](const LimbTab &t) {
-        if (p_tiled) return launch_intt_cols_scaled(c, M.pc, t, c->d_downscale, s);
-        return fused ? launch_intt_scaled(c, M.pc, M.u, t, c->d_downscale, s) : launch_ntt(c, M.pc, t, true, s, M.u);
+        return fused ? launch_intt_tiles(c, M.pc, M.u, t, s) : launch_ntt(c, M.pc, t, true, s, M.u);
     };
     LimbTab lp;
     lp.n = 0;
-    for (int z = 0; z < K; z++)
+    for (int z = 0; !p_tiled && z < K; z++)
         for (int p = 0; p < 2; p++)
             for (int a = 0; a < al; a++) {
                 lp.pidx[lp.n] = c->n_q + a, lp.off[lp.n] = (2 * z + p) * al + a;
@@ -226,7 +225,7 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
                     lp.n = 0;
                 }
             }
-    NJ_HIP(intt(lp));
+    if (lp.n) NJ_HIP(intt(lp));
     const BconvTab &bt = drop ? c->moddown_drop[l] : c->moddown[l];
     BconvShared sh;
     sh.nd = 1;
@@ -235,7 +234,7 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
     for (int o = 0; o < bt.n_out; o++) sh.out_pidx[0][o] = bt.out_pidx[o], sh.out_off[0][o] = bt.out_limb[o];
     BconvPtrs jp;
     for (int h = 0; h < 2 * K; h++) jp.in[h] = M.pc + (size_t)h * al * N, jp.out[h] = M.conv + (size_t)h * (l + 1) * N;
-    NJ_HIP(fused ? launch_bconv_col(c, sh, jp, 2 * K, s) : launch_bconv_multi(c, sh, jp, 2 * K, s));
+    NJ_HIP(fused ? launch_bconv_col(c, sh, jp, 2 * K, c->d_downscale, s) : launch_bconv_multi(c, sh, jp, 2 * K, s));
     if (ipq) {
         NJ_HIP(launch_key_ip_moddown(c, l, K, M.conv, *ipq, mj, s));
         return NJ_OK;

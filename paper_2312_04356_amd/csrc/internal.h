@@ -107,6 +107,16 @@ __device__ __forceinline__ IpRow ip_row(int t, int level, int L, int alpha)
     return r;
 }
 
+// Tables read at wave-uniform places through the constant address space: scalar loads, also
+// in loops that store (where the compiler cannot tell that a table is not being written).
+template <typename T>
+using ConstTab = const T __attribute__((address_space(4))) *;
+template <typename T>
+__device__ __forceinline__ ConstTab<T> const_tab(const T *p)
+{
+    return (ConstTab<T>)(uintptr_t)p;
+}
+
 // Raw buffer access (gfx9 buffer resource: base, size in bytes): a per-thread 32-bit
 // byte offset plus a wave-uniform offset held in a scalar register, so strided loads
 // of a column need no per-load 64-bit address arithmetic.  Accesses past `bytes` read
@@ -310,13 +320,15 @@ namespace nj {
 // ---------------------------------------------------------------- kernels.hip
 hipError_t launch_ntt(const nj_ctx *c, uint64_t *data, const LimbTab &lt, bool inverse, hipStream_t s,
                       const uint64_t *src = nullptr);
-// (gt: limb b of job off[b] / L1 is read from src through X -> X^g[job])
-hipError_t launch_intt_scaled(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt,
-                              const double *scale, hipStream_t s, const GalTab *gt = nullptr, int L1 = 0);
+// inverse tile pass alone, for launch_bconv_col (gt: limb b of job off[b] / L1 is read from
+// src through X -> X^g[job])
+hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt, hipStream_t s,
+                             const GalTab *gt = nullptr, int L1 = 0);
 hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, uint64_t *out, int n_out,
                                 uint64_t *last, uint64_t *lifted, hipStream_t s, int n_polys = 2, bool last_tiled = false);
 hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, hipStream_t s);
-hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs, hipStream_t s);
+hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs,
+                            const double *scale, hipStream_t s);
 // key inner products fused with the extended digits' forward tile pass (N >= 8192,
 // 1..4 digits, every g = 1): per job u_base + z 2 ne N, or (sum) one output summed over
 // the jobs; accumulate adds to the output's previous value
@@ -335,8 +347,6 @@ hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, in
 // primes 0..n_out-1 with the column pass applied, out [n_polys][n_out][N] (N >= 8192)
 hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, int n_polys, int n_out, uint64_t *out,
                            hipStream_t s);
-hipError_t launch_intt_cols_scaled(const nj_ctx *c, uint64_t *data, const LimbTab &lt, const double *scale,
-                                   hipStream_t s);
 // (acc0: job 0's previous value read from there instead of its output; last_out, one
 // job: the last limb also leaves through the first 12 stages of its inverse transform
 // into last_out [2][N], for launch_rescale_fused(last_tiled))

@@ -604,8 +604,8 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_gal(uint64_t *data, const uint
 
 // The first log2(N1) forward stages on one column of N1 words, canonical or centred (lazy,
 // one centred reduction at the end: at most 4 stages).
-template <int N1>
-__device__ __forceinline__ void col_forward(double v[N1], const double *W, Mod m)
+template <int N1, typename P>
+__device__ __forceinline__ void col_forward(double v[N1], P W, Mod m)
 {
 #pragma unroll
     for (int mm = 1; mm < N1; mm <<= 1) {
@@ -643,13 +643,11 @@ __device__ __forceinline__ void col_inverse(double v[N1], const double *W, Mod m
 }
 
 // columns pass: first log2(N1) stages, one column of N1 words per thread.  grid (4096/256, limbs).
-// The inverse ends with the factor N^-1, or scale[pidx] when a scale table is given
-// (N^-1 times a basis conversion's input factor, so the conversion need not apply it).
-// The forward's results go to the tile pass as centred FP64 values; the inverse's are
-// canonical, stored as FP64 values too when DBL (for the fused basis conversion).
-template <int N1, bool INV, bool DBL = false>
+// The forward's results go to the tile pass as centred FP64 values; the inverse ends with
+// the factor N^-1 and is canonical.
+template <int N1, bool INV>
 __global__ __launch_bounds__(kNT) void k_ntt_col(uint64_t *data, const uint64_t *src, LimbTab lt, const double *tw,
-                                                 const PrimeInfo *info, int logN, const double *scale)
+                                                 const PrimeInfo *info, int logN)
 {
     const int N = 1 << logN;
     const int limb = blockIdx.y, pidx = lt.pidx[limb];
@@ -670,82 +668,114 @@ __global__ __launch_bounds__(kNT) void k_ntt_col(uint64_t *data, const uint64_t 
         col_forward<N1>(v, W, m);
     } else {
         col_inverse<N1>(v, W, m);
-        const double sc = scale ? scale[pidx] : pi.ninv;
 #pragma unroll
-        for (int r = 0; r < N1; r++) v[r] = reduce(mul_lazy(v[r], sc, m), m);
+        for (int r = 0; r < N1; r++) v[r] = reduce(mul_lazy(v[r], pi.ninv, m), m);
     }
 #pragma unroll
-    for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, !INV || DBL ? d2b(v[r]) : d2u(v[r]));
+    for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, INV ? d2u(v[r]) : d2b(v[r]));
 }
 
-// Basis conversion fused with the first log2(N1) forward stages of its outputs (the
-// column pass).  Inputs are coefficient-form limbs already multiplied by
-// (D/q_a)^-1 (folded into their inverse transform's N^-1) and stored by that transform
-// as FP64 values (launch_intt_scaled, launch_intt_cols_scaled), so each output word is
-// y_t = sum_a x_a (D/q_a) mod t; the converted limbs are never stored before their
-// column pass.  Thread = one column (N1 words at stride 4096) of OUT consecutive
-// targets of (job, digit) blockIdx.z = job * nd + digit; grid (4096/256,
-// ceil(n_out/OUT), jobs nd).  Input slots past the digit size re-read its last limb
-// with a zero factor; targets past n_out repeat the last one and are not stored.
-constexpr int kBcOut = 2;  // targets per thread
+// Basis conversion with the column passes on both sides of it.  Inputs are limbs after
+// their inverse tile pass (FP64 words, centred); a block takes 64 columns (N1 words each at
+// stride 4096) of (job, digit) blockIdx.z = job * nd + digit:
+//   1. wave a < m finishes input limb a's inverse transform on its columns (the last
+//      log2(N1) stages and the factor scale[prime] = N^-1 (D/q_a)^-1) and leaves the
+//      canonical words in LDS;
+//   2. each wave converts to one target after another, y_t = sum_a x_a (D/q_a) mod t, and
+//      runs the target's first log2(N1) forward stages before anything is stored.
+// So neither the inputs after their column pass nor the converted limbs before theirs go
+// to memory.  One wave works on one prime at a time: its constants and twiddles are
+// scalar loads.
+//
+// The sum is kept as an exact pair (S, L): S starts at 2^103 and takes each product
+// rounded to a multiple of 2^51 (S stays below 2^104: 8 products below 2^100), L the
+// rounding errors, d = S_old - S_new being exact and x h + d an integer below 2^50 in
+// magnitude that one fma computes exactly; |L| <= 2^53.  4 operations per product instead
+// of the 7 of a modular one, and one reduction at the end: S - 2^103 less its quotient
+// times t leaves at most t/2 + 2^51 (the quotient's error times t is below 2^-52 times
+// 2^103), plus L centred, an integer below 2^52.
+// FP64 issue bounds it (7 giant steps at level 23, N = 2^16: 33 M converted words, about 63
+// operations each, 94-98 us at 70% of the FP64 rate; the inverse column pass and a 7
+// operation product as launches of their own took 27 + 104 us), latency a single key
+// switch (25 us for its 3 digits; 6 + 24 us).  The block's LDS (64 KB at N1 = 16) allows
+// two per CU, 4 waves per SIMD; 12 or 16 waves per block with 64 registers were slower.
+// Grid (4096/64, target chunks of 8 tpw, jobs nd), wave w of chunk y taking targets
+// (y tpw + i) 8 + w.
+constexpr int kBcCols = 64, kBcWaves = 8;  // columns per block; waves, and input limbs at most
 
-template <int MMAX, int N1>
-__global__ __launch_bounds__(kNT) void k_bconv_col(BconvShared sh, BconvPtrs jp, const double *tw,
-                                                   const PrimeInfo *info, int logN)
+// step 2's sums for one column of one target: v[r] = sum_a x_a[r] hat[a n_out], centred; x_a's
+// rows at x + (a N1 + r) kBcCols, zero for m <= a < MM.  No branch on m inside, so the LDS
+// reads of one input are under way while another is being multiplied; all factors are
+// loaded first (a scalar load in between would hold up every LDS read issued before it).
+template <int MM, int N1>
+__device__ __forceinline__ void bconv_sum(double v[N1], const double *x, ConstTab<double> hat, int m, int n_out, Mod mo)
 {
+    constexpr double kGrid = 10141204801825835211973625643008.0;  // 2^103
+    constexpr int kR = N1 < 8 ? N1 : 8;  // rows at a time: 16 pairs at once would spill
+    double h[MM];
+#pragma unroll
+    for (int a = 0; a < MM; a++) h[a] = hat[(a < m ? a : m - 1) * n_out];
+#pragma unroll
+    for (int r0 = 0; r0 < N1; r0 += kR) {
+        double S[kR], L[kR];
+#pragma unroll
+        for (int r = 0; r < kR; r++) S[r] = kGrid, L[r] = 0.0;
+#pragma unroll
+        for (int a = 0; a < MM; a++)
+#pragma unroll
+            for (int r = 0; r < kR; r++) {
+                const double xv = x[(a * N1 + r0 + r) * kBcCols], Sn = fma(xv, h[a], S[r]);
+                L[r] += fma(xv, h[a], S[r] - Sn);
+                S[r] = Sn;
+            }
+#pragma unroll
+        for (int r = 0; r < kR; r++)
+            v[r0 + r] = reduce_c(reduce_c(S[r] - kGrid, mo) + reduce_c(L[r], mo), mo);
+    }
+}
+
+template <int N1>
+__global__ __launch_bounds__(kBcCols * kBcWaves, 4) void k_bconv_col(BconvShared sh, BconvPtrs jp, const double *scale,
+                                                                     const double *tw, const double *itw,
+                                                                     const PrimeInfo *info, int logN, int tpw)
+{
+    __shared__ double xs[kBcWaves * N1 * kBcCols];
     const int N = 1 << logN;
     const int job = blockIdx.z / sh.nd, j = blockIdx.z % sh.nd;
-    const int c = blockIdx.x * kNT + threadIdx.x;
-    const int n_out = sh.n_out[j], m = sh.m[j], o0 = blockIdx.y * kBcOut;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kBcCols), lane = threadIdx.x % kBcCols;
+    const int n_out = sh.n_out[j], m = sh.m[j], o0 = blockIdx.y * tpw * kBcWaves;
     if (o0 >= n_out) return;
-    const auto in = buf_rsrc(jp.in[job] + (size_t)sh.in_off0[j] * N, (uint32_t)m * N * 8u);
-    const uint32_t cb = 8u * c;
-    const double *hat = sh.hat[j];
-    int o[kBcOut];
-    Mod mo[kBcOut];
+    const uint32_t cb = 8u * (blockIdx.x * kBcCols + lane);
+    double v[N1];
+    if (w >= m) {  // bconv_sum reads 2, 4 or 8 inputs
 #pragma unroll
-    for (int q = 0; q < kBcOut; q++) {
-        o[q] = o0 + q < n_out ? o0 + q : n_out - 1;
-        mo[q] = info[sh.out_pidx[j][o[q]]].m;
+        for (int r = 0; r < N1; r++) xs[(w * N1 + r) * kBcCols + lane] = 0.0;
+    } else {
+        const int pidx = sh.in_pidx[j][w];
+        const Mod mi = info[pidx].m;
+        const auto in = buf_rsrc(jp.in[job] + (size_t)(sh.in_off0[j] + w) * N, 8u * N);
+#pragma unroll
+        for (int r = 0; r < N1; r++) v[r] = b2d(buf_ld(in, cb, 8u * r * kT));
+        col_inverse<N1>(v, itw + (size_t)pidx * N, mi);
+        const double sc = scale[pidx];
+#pragma unroll
+        for (int r = 0; r < N1; r++) xs[(w * N1 + r) * kBcCols + lane] = reduce(mul_lazy(v[r], sc, mi), mi);
     }
-    double acc[kBcOut][N1];
+    __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < tpw; i++) {
+        const int o = o0 + i * kBcWaves + w;
+        if (o >= n_out) return;
+        const int pq = sh.out_pidx[j][o];
+        const Mod mo{const_tab(info)[pq].m.t, const_tab(info)[pq].m.ti};
+        const ConstTab<double> hat = const_tab(sh.hat[j]) + o;
+        if (m > 4) bconv_sum<8, N1>(v, xs + lane, hat, m, n_out, mo);
+        else if (m > 2) bconv_sum<4, N1>(v, xs + lane, hat, m, n_out, mo);
+        else bconv_sum<2, N1>(v, xs + lane, hat, m, n_out, mo);
+        col_forward<N1>(v, const_tab(tw) + (size_t)pq * N, mo);
+        const auto out = buf_rsrc(jp.out[job] + (size_t)sh.out_off[j][o] * N, 8u * N);
 #pragma unroll
-    for (int q = 0; q < kBcOut; q++)
-#pragma unroll
-        for (int r = 0; r < N1; r++) acc[q][r] = 0.0;
-#pragma unroll 2
-    for (int a = 0; a < MMAX; a++) {  // two input limbs' loads in flight at a time
-        const int aa = a < m ? a : m - 1;
-        double h[kBcOut];
-#pragma unroll
-        for (int q = 0; q < kBcOut; q++) h[q] = a < m ? hat[aa * n_out + o[q]] : 0.0;
-        uint64_t x[N1];
-#pragma unroll
-        for (int r = 0; r < N1; r++) x[r] = buf_ld(in, cb, 8u * ((uint32_t)aa * N + r * kT));
-#pragma unroll
-        for (int r = 0; r < N1; r++) {
-            const double xv = __longlong_as_double((long long)x[r]);  // stored as FP64 by the inverse transform
-#pragma unroll
-            for (int q = 0; q < kBcOut; q++) acc[q][r] += mul_lazy(xv, h[q], mo[q]);
-        }
-        if (a % 7 == 6 && a + 1 < MMAX) {  // at most 7 lazy terms on a reduced sum
-#pragma unroll
-            for (int q = 0; q < kBcOut; q++)
-#pragma unroll
-                for (int r = 0; r < N1; r++) acc[q][r] = reduce_c(acc[q][r], mo[q]);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kBcOut; q++) {
-#pragma unroll
-        for (int r = 0; r < N1; r++) acc[q][r] = reduce_c(acc[q][r], mo[q]);
-        const int pq = sh.out_pidx[j][o[q]];
-        col_forward<N1>(acc[q], tw + (size_t)pq * N, mo[q]);
-        if (o0 + q < n_out) {
-            const auto out = buf_rsrc(jp.out[job] + (size_t)sh.out_off[j][o[q]] * N, 8u * N);
-#pragma unroll
-            for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, d2b(acc[q][r]));
-        }
+        for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, d2b(v[r]));
     }
 }
 
@@ -938,17 +968,16 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
     }
 }
 
-template <bool INV, bool DBL = false>
+template <bool INV>
 static hipError_t launch_cols(const nj_ctx *c, int kind, double bytes, int N1, dim3 grid, hipStream_t s,
                               uint64_t *data, const uint64_t *src, const LimbTab &lt, const double *tw,
-                              const PrimeInfo *info, int logN, const double *scale = nullptr)
+                              const PrimeInfo *info, int logN)
 {
     switch (N1) {
-    case 2: return launch(c, kind, bytes, k_ntt_col<2, INV, DBL>, grid, dim3(kNT), s, data, src, lt, tw, info, logN, scale);
-    case 4: return launch(c, kind, bytes, k_ntt_col<4, INV, DBL>, grid, dim3(kNT), s, data, src, lt, tw, info, logN, scale);
-    case 8: return launch(c, kind, bytes, k_ntt_col<8, INV, DBL>, grid, dim3(kNT), s, data, src, lt, tw, info, logN, scale);
-    default:
-        return launch(c, kind, bytes, k_ntt_col<16, INV, DBL>, grid, dim3(kNT), s, data, src, lt, tw, info, logN, scale);
+    case 2: return launch(c, kind, bytes, k_ntt_col<2, INV>, grid, dim3(kNT), s, data, src, lt, tw, info, logN);
+    case 4: return launch(c, kind, bytes, k_ntt_col<4, INV>, grid, dim3(kNT), s, data, src, lt, tw, info, logN);
+    case 8: return launch(c, kind, bytes, k_ntt_col<8, INV>, grid, dim3(kNT), s, data, src, lt, tw, info, logN);
+    default: return launch(c, kind, bytes, k_ntt_col<16, INV>, grid, dim3(kNT), s, data, src, lt, tw, info, logN);
     }
 }
 
@@ -976,23 +1005,19 @@ hipError_t launch_ntt_fast(const nj_ctx *c, uint64_t *data, const uint64_t *src,
     return launch_cols<true>(c, PROF_NTT_COL_INV, bytes, N1, gc, s, data, nullptr, lt, tw, c->d_info, c->log_n);
 }
 
-// Inverse transform whose final factor is scale[pidx] instead of N^-1 (N >= 8192),
-// for the fused basis conversion: the results are stored as FP64 values.  With gt,
-// the input limbs are read through X -> X^g of their job (off / L1).
-hipError_t launch_intt_scaled(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt,
-                              const double *scale, hipStream_t s, const GalTab *gt, int L1)
+// Inverse tile pass alone, into data from src (N >= 8192): the basis conversion runs the
+// column pass.  With gt, the input limbs are read through X -> X^g of their job (off / L1).
+hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt, hipStream_t s,
+                             const GalTab *gt, int L1)
 {
     const int N = c->N, N1 = N / kT;
     if (N1 < 2 || (gt && (!src || L1 < 1))) return hipErrorInvalidValue;
     if (lt.n == 0) return hipSuccess;
     const double bytes = 16.0 * N * lt.n;
-    hipError_t e = gt ? launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile_gal, dim3(N1, lt.n), dim3(kNT), s, data, src,
-                               lt, *gt, L1, c->d_itw, c->d_info, c->log_n)
-                      : launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, dim3(N1, lt.n), dim3(kNT), s, data, src,
-                               lt, c->d_itw, c->d_info, c->log_n);
-    if (e != hipSuccess) return e;
-    return launch_cols<true, true>(c, PROF_NTT_COL_INV, bytes, N1, dim3(kT / kNT, lt.n), s, data, nullptr, lt,
-                                   c->d_itw, c->d_info, c->log_n, scale);
+    return gt ? launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile_gal, dim3(N1, lt.n), dim3(kNT), s, data, src, lt, *gt,
+                       L1, c->d_itw, c->d_info, c->log_n)
+              : launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, dim3(N1, lt.n), dim3(kNT), s, data, src, lt,
+                       c->d_itw, c->d_info, c->log_n);
 }
 
 // Rescale of P packed level-l polynomials (P = 2 per ciphertext; limbs 0..n_out-1 of
@@ -1036,9 +1061,11 @@ hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, 
                   lt, c->d_tw, c->d_info, c->log_n);
 }
 
-// Basis conversion of n_jobs (job, digit) pairs fused with the outputs' column pass
-// (inputs pre-multiplied by (D/q_a)^-1), N >= 8192.
-hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs, hipStream_t s)
+// Basis conversion of n_jobs (job, digit) pairs with the column passes on both sides
+// (inputs after their inverse tile pass; scale: [n_primes] factor of each input's inverse
+// transform), N >= 8192, at most 8 input limbs per digit.
+hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs,
+                            const double *scale, hipStream_t s)
 {
     const int N = c->N, N1 = N / kT;
     if (N1 < 2 || n_jobs == 0) return N1 < 2 ? hipErrorInvalidValue : hipSuccess;
@@ -1049,15 +1076,21 @@ hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvP
         mmax = std::max(mmax, sh.m[j]);
         bytes += 8.0 * N * (sh.m[j] + sh.n_out[j]) * n_jobs;
     }
-    if (mmax > 8) return hipErrorInvalidValue;
-    const dim3 grid(kT / kNT, (max_out + kBcOut - 1) / kBcOut, n_jobs * sh.nd);
-#define NJ_BC(MM, NN)                                                                                               \
-    if (mmax <= MM && N1 == NN)                                                                                    \
-        return launch(c, PROF_BCONV, bytes, k_bconv_col<MM, NN>, grid, dim3(kNT), s, sh, jp, c->d_tw, c->d_info,   \
-                      c->log_n);
-    NJ_BC(2, 2) NJ_BC(2, 4) NJ_BC(2, 8) NJ_BC(2, 16)
-    NJ_BC(4, 2) NJ_BC(4, 4) NJ_BC(4, 8) NJ_BC(4, 16)
-    NJ_BC(8, 2) NJ_BC(8, 4) NJ_BC(8, 8) NJ_BC(8, 16)
+    if (mmax > kBcWaves) return hipErrorInvalidValue;
+    // targets per wave: step 1 is half a target's work, so a block takes all targets once
+    // there are blocks enough to fill the chip (256 CUs, two blocks each by their LDS: 8
+    // digits of one size), and one per wave below that.  N = 2^16, 24 targets: 21 digits
+    // 98 us against 107 with one per wave, one key switch's 3 digits 25 us against 31 with 3
+    const int chunks = (max_out + kBcWaves - 1) / kBcWaves, wide = kT / kBcCols * n_jobs * sh.nd;
+    const int tpw = wide >= 512 ? chunks : 1;
+    const dim3 grid(kT / kBcCols, (chunks + tpw - 1) / tpw, n_jobs * sh.nd), blk(kBcCols * kBcWaves);
+#define NJ_BC(NN)                                                                                                 \
+    case NN:                                                                                                      \
+        return launch(c, PROF_BCONV, bytes, k_bconv_col<NN>, grid, blk, s, sh, jp, scale, c->d_tw, c->d_itw,      \
+                      c->d_info, c->log_n, tpw);
+    switch (N1) {
+        NJ_BC(2) NJ_BC(4) NJ_BC(8) NJ_BC(16)
+    }
 #undef NJ_BC
     return hipErrorInvalidValue;
 }
@@ -1157,18 +1190,6 @@ hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, in
     }
 #undef NJ_PT
     return hipErrorInvalidValue;
-}
-
-// The column pass of an inverse transform whose tile pass already ran, in place, with
-// the final factor scale[pidx] (N >= 8192); results stored as FP64 values, as above.
-hipError_t launch_intt_cols_scaled(const nj_ctx *c, uint64_t *data, const LimbTab &lt, const double *scale,
-                                   hipStream_t s)
-{
-    const int N = c->N, N1 = N / kT;
-    if (N1 < 2) return hipErrorInvalidValue;
-    if (lt.n == 0) return hipSuccess;
-    return launch_cols<true, true>(c, PROF_NTT_COL_INV, 16.0 * N * lt.n, N1, dim3(kT / kNT, lt.n), s, data, nullptr,
-                                   lt, c->d_itw, c->d_info, c->log_n, scale);
 }
 
 // Centred lift of n_polys coefficient-form limbs (prime src_pidx, at src + z N) into
