@@ -804,15 +804,16 @@ nj_status modraise(nj_ctx *c, const uint64_t *in, int top, uint64_t *out, Arena 
     lt.pidx[0] = lt.pidx[1] = 0;
     lt.off[0] = 0, lt.off[1] = 1;
     lt.soff[0] = 0, lt.soff[1] = 1;
-    NJ_HIP(launch_ntt(c, tmp, lt, true, s, in));  // coefficient form of both level-0 limbs
     LimbTab lo;
     lo.n = 2 * (top + 1);
     for (int k = 0; k < lo.n; k++) lo.pidx[k] = k % (top + 1), lo.off[k] = k;
-    if (N >= 8192) {  // lift fused with the column pass, then the tile pass
+    if (N >= 8192) {  // inverse tile pass, lift fused with both column passes, forward tile pass
+        NJ_HIP(launch_intt_tiles(c, tmp, in, lt, s));
         NJ_HIP(launch_lift_col(c, tmp, 0, 2, top + 1, out, s));
         NJ_HIP(launch_ntt_tiles(c, out, lo, s));
         return NJ_OK;
     }
+    NJ_HIP(launch_ntt(c, tmp, lt, true, s, in));  // coefficient form of both level-0 limbs
     for (int p = 0; p < 2; p++) NJ_HIP(launch_lift_last(c, tmp + p * N, 0, top + 1, out + (size_t)p * (top + 1) * N, s));
     NJ_HIP(launch_ntt(c, out, lo, false, s));
     return NJ_OK;

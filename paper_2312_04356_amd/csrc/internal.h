@@ -343,8 +343,8 @@ hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jo
 // (2 z + p) alpha + a (N >= 8192, 1..4 digits, alpha <= 8)
 hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *pout,
                                hipStream_t s);
-// centred lift of n_polys limbs (prime src_pidx, coefficient form, src + z N) into
-// primes 0..n_out-1 with the column pass applied, out [n_polys][n_out][N] (N >= 8192)
+// centred lift of n_polys limbs after their inverse tile pass (prime src_pidx, src + z N)
+// into primes 0..n_out-1 with the column pass applied, out [n_polys][n_out][N] (N >= 8192)
 hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, int n_polys, int n_out, uint64_t *out,
                            hipStream_t s);
 // (acc0: job 0's previous value read from there instead of its output; last_out, one

@@ -917,28 +917,42 @@ __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_m
     }
 }
 
-// Rescale by q_l, fused into the lifted limbs' transform (N >= 8192).  k_lift_col: the
-// last limb of each polynomial (coefficient form, last [P][N]) lifted centred into
-// target limb i, then the forward column pass; grid (4096/256, n_out, P).
+// Rescale by q_l and ModRaise, fused into the lifted limbs' transform (N >= 8192).
+// k_lift_col: one limb of each polynomial after its inverse tile pass (src [P][N], FP64
+// words): its last log2(N1) inverse stages and N^-1, the centred lift into target limbs
+// i < n_out and their forward column pass; thread = one column, `per` targets in turn;
+// grid (4096/256, ceil(n_out / per), P).
 template <int N1>
-__global__ __launch_bounds__(kNT) void k_lift_col(const uint64_t *last, int src_pidx, int n_out, uint64_t *lifted,
-                                                  const double *tw, const PrimeInfo *info, int logN)
+__global__ __launch_bounds__(kNT) void k_lift_col(const uint64_t *last, int src_pidx, int n_out, int per,
+                                                  uint64_t *lifted, const double *tw, const double *itw,
+                                                  const PrimeInfo *info, int logN)
 {
-    const int N = 1 << logN, i = blockIdx.y, z = blockIdx.z;
+    const int N = 1 << logN, z = blockIdx.z;
     const uint32_t cb = 8u * (blockIdx.x * kNT + threadIdx.x);
-    const Mod ms = info[src_pidx].m, mt = info[i].m;
-    const double half = info[src_pidx].half;
+    const Mod ms = info[src_pidx].m;
+    const double ninv = info[src_pidx].ninv;
     const auto src = buf_rsrc(last + (size_t)z * N, 8u * N);
-    double v[N1];
+    double x[N1];
 #pragma unroll
-    for (int r = 0; r < N1; r++) {
-        const double x = u2d(buf_ld(src, cb, 8u * r * kT));
-        v[r] = reduce_c(x > half ? x - ms.t : x, mt);  // centred, |x| < t_l / 2 < 2^49
+    for (int r = 0; r < N1; r++) x[r] = b2d(buf_ld(src, cb, 8u * r * kT));
+    col_inverse<N1>(x, itw + (size_t)src_pidx * N, ms);
+    // centred exactly, |x| <= (t_l - 1)/2 < 2^49: after the first reduction |x/t| is below
+    // 1/2 + 2/t, the second one's quotient error below 2^-53, and |x|/t at least 1/2t away
+    // from 1/2
+#pragma unroll
+    for (int r = 0; r < N1; r++) x[r] = reduce_c(reduce_c(mul_lazy(x[r], ninv, ms), ms), ms);
+    const int i1 = min(n_out, (int)(blockIdx.y + 1) * per);
+#pragma unroll 1
+    for (int i = blockIdx.y * per; i < i1; i++) {
+        const Mod mt{const_tab(info)[i].m.t, const_tab(info)[i].m.ti};
+        double v[N1];
+#pragma unroll
+        for (int r = 0; r < N1; r++) v[r] = reduce_c(x[r], mt);
+        col_forward<N1>(v, const_tab(tw) + (size_t)i * N, mt);
+        const auto dst = buf_rsrc(lifted + ((size_t)z * n_out + i) * N, 8u * N);
+#pragma unroll
+        for (int r = 0; r < N1; r++) buf_st(dst, cb, 8u * r * kT, d2b(v[r]));
     }
-    col_forward<N1>(v, tw + (size_t)i * N, mt);
-    const auto dst = buf_rsrc(lifted + ((size_t)z * n_out + i) * N, 8u * N);
-#pragma unroll
-    for (int r = 0; r < N1; r++) buf_st(dst, cb, 8u * r * kT, d2b(v[r]));
 }
 
 // k_ntt_tile_rs: the lifted limbs' tile pass with the rescale combine as its epilogue,
@@ -1020,9 +1034,33 @@ hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *sr
                        c->d_itw, c->d_info, c->log_n);
 }
 
+// Centred lift of n_polys limbs after their inverse tile pass (prime src_pidx, at src + z N)
+// into primes 0..n_out-1 with the column passes on both sides, into out [n_polys][n_out][N]
+// (N >= 8192); the tile pass (launch_ntt_tiles, k_ntt_tile_rs) finishes the forward transform.
+hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, int n_polys, int n_out, uint64_t *out,
+                           hipStream_t s)
+{
+    const int N = c->N, N1 = N / kT;
+    if (N1 < 2 || n_out < 1 || n_polys < 1) return hipErrorInvalidValue;
+    // two targets share one inverse column pass: 1, 2, 4 and 8 each measured, mask and HMult
+    // best at 1 and 2, a layer and a batch at 2 and 4 (12.59 / 12.50 / 12.52 / 12.68 ms a layer)
+    const int per = 2;
+    const dim3 g(kT / kNT, (n_out + per - 1) / per, n_polys);
+    const double b = 8.0 * N * n_polys * (1 + n_out);
+#define NJ_LC(NN)                                                                                                 \
+    case NN:                                                                                                      \
+        return launch(c, PROF_OTHER, b, k_lift_col<NN>, g, dim3(kNT), s, src, src_pidx, n_out, per, out, c->d_tw, \
+                      c->d_itw, c->d_info, c->log_n);
+    switch (N1) {
+        NJ_LC(2) NJ_LC(4) NJ_LC(8) NJ_LC(16)
+    }
+#undef NJ_LC
+    return hipErrorInvalidValue;
+}
+
 // Rescale of P packed level-l polynomials (P = 2 per ciphertext; limbs 0..n_out-1 of
-// each kept), N >= 8192: inverse transform of the last limbs read in place (into
-// last [P][N]), lift fused with the column pass (into lifted [P][n_out][N], which may be
+// each kept), N >= 8192: inverse tile pass of the last limbs read in place (into
+// last [P][N]), lift fused with the column passes (into lifted [P][n_out][N], which may be
 // out: each tile block reads its own lifted words before writing them), tile pass
 // fused with the combine.  in must not alias out.
 hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, uint64_t *out, int n_out,
@@ -1033,19 +1071,9 @@ hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, 
     LimbTab lt;
     lt.n = n_polys;
     for (int p = 0; p < n_polys; p++) lt.pidx[p] = level, lt.off[p] = p, lt.soff[p] = p * (level + 1) + level;
-    // last_tiled: the last limbs' inverse tile pass already ran (into last), the column pass follows
-    hipError_t e = last_tiled ? launch_cols<true>(c, PROF_NTT_COL_INV, 16.0 * N * n_polys, N1, dim3(kT / kNT, n_polys), s,
-                                                  last, nullptr, lt, c->d_itw, c->d_info, c->log_n)
-                              : launch_ntt_fast(c, last, in, lt, true, s);
-    if (e != hipSuccess) return e;
-    const dim3 gl(kT / kNT, n_out, n_polys);
-    const double bl = 8.0 * N * n_polys * (1 + n_out);
-    switch (N1) {
-    case 2: e = launch(c, PROF_OTHER, bl, k_lift_col<2>, gl, dim3(kNT), s, last, level, n_out, lifted, c->d_tw, c->d_info, c->log_n); break;
-    case 4: e = launch(c, PROF_OTHER, bl, k_lift_col<4>, gl, dim3(kNT), s, last, level, n_out, lifted, c->d_tw, c->d_info, c->log_n); break;
-    case 8: e = launch(c, PROF_OTHER, bl, k_lift_col<8>, gl, dim3(kNT), s, last, level, n_out, lifted, c->d_tw, c->d_info, c->log_n); break;
-    default: e = launch(c, PROF_OTHER, bl, k_lift_col<16>, gl, dim3(kNT), s, last, level, n_out, lifted, c->d_tw, c->d_info, c->log_n);
-    }
+    // last_tiled: the last limbs' inverse tile pass already ran (into last)
+    hipError_t e = last_tiled ? hipSuccess : launch_intt_tiles(c, last, in, lt, s);
+    if (e == hipSuccess) e = launch_lift_col(c, last, level, n_polys, n_out, lifted, s);
     if (e != hipSuccess) return e;
     return launch(c, PROF_OTHER, 8.0 * N * n_polys * n_out * 4.0, k_ntt_tile_rs, dim3(N1, n_polys * n_out), dim3(kNT),
                   s, lifted, in, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q, c->d_tw, c->d_info, c->log_n);
@@ -1190,24 +1218,6 @@ hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, in
     }
 #undef NJ_PT
     return hipErrorInvalidValue;
-}
-
-// Centred lift of n_polys coefficient-form limbs (prime src_pidx, at src + z N) into
-// primes 0..n_out-1, fused with those limbs' column pass, into out [n_polys][n_out][N]
-// (N >= 8192); the tile pass (launch_ntt_tiles) finishes the forward transform.
-hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, int n_polys, int n_out, uint64_t *out,
-                           hipStream_t s)
-{
-    const int N = c->N, N1 = N / kT;
-    if (N1 < 2 || n_out < 1 || n_polys < 1) return hipErrorInvalidValue;
-    const dim3 g(kT / kNT, n_out, n_polys);
-    const double b = 8.0 * N * n_polys * (1 + n_out);
-    switch (N1) {
-    case 2: return launch(c, PROF_OTHER, b, k_lift_col<2>, g, dim3(kNT), s, src, src_pidx, n_out, out, c->d_tw, c->d_info, c->log_n);
-    case 4: return launch(c, PROF_OTHER, b, k_lift_col<4>, g, dim3(kNT), s, src, src_pidx, n_out, out, c->d_tw, c->d_info, c->log_n);
-    case 8: return launch(c, PROF_OTHER, b, k_lift_col<8>, g, dim3(kNT), s, src, src_pidx, n_out, out, c->d_tw, c->d_info, c->log_n);
-    default: return launch(c, PROF_OTHER, b, k_lift_col<16>, g, dim3(kNT), s, src, src_pidx, n_out, out, c->d_tw, c->d_info, c->log_n);
-    }
 }
 
 }  // namespace nj
