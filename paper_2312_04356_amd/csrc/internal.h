@@ -85,6 +85,21 @@ __device__ __forceinline__ int galois_src2(int k, uint32_t g, int logN)
     return (int)brev_n((eg - 1u) >> 1, logN);
 }
 
+// galois_src2 of words w0 + off for several constant `off` whose bits are clear in w0: the
+// reversed words add up, so one multiply per thread (gal_base) and, for a uniform g, a
+// scalar one per offset do for all of them.
+__device__ __forceinline__ uint32_t gal_base(int w0, uint32_t g, int logN)
+{
+    uint32_t b = (2u * brev_n((uint32_t)w0, logN) + 1u) * g;
+    asm("" : "+v"(b));  // else the sums are formed before the product, one product per offset
+    return b;
+}
+__device__ __forceinline__ int gal_at(uint32_t base, int off, uint32_t g, int logN)
+{
+    const uint32_t eg = (base + 2u * brev_n((uint32_t)off, logN) * g) & ((2u << logN) - 1u);
+    return (int)brev_n(eg >> 1, logN);
+}
+
 // Output limb t of a key inner product at level l: t < l+1 is q_t, else p_(t-l-1); kl
 // = the key's limb of t; own = the digit t belongs to (-1 for special primes).
 // Sums need their operands at one scale: equal up to a relative 1e-9 (scales computed

@@ -10,6 +10,12 @@
 //     each and run 3 rounds of 4 radix-2 stages in registers; between rounds the
 //     tile goes through LDS once (padded by one word every 16 to avoid bank
 //     conflicts).  Global loads and stores are fully coalesced.
+// Which words a thread holds outside its rounds:
+//   across the block (forward in, inverse out): tid + 256 k;
+//   across its wave (forward out, inverse in): wv(tid) + 64 k, wv = 1024 wave + lane.
+// Rounds 1 and 2 stay inside a wave's 1024 words, so a tile pass has one barrier, between
+// round 0 and the others; exchanges inside a wave only keep their order (wave_sync).
+// Round 0's twiddles are the same for every thread of a tile: scalar loads.
 // A round covering strides t0, t0/2, t0/4, t0/8 gives thread (lo, hi) the words
 // x_k = lo + (t0/8) k + 2 t0 hi, k < 16; at stride t0/2^s the pair (k, k + 8>>s)
 // belongs to butterfly block hi 2^s + (k >> (4-s)) of the tile.
@@ -26,6 +32,8 @@ constexpr int kNT = 256;
 __device__ __forceinline__ double b2d(uint64_t x) { return __longlong_as_double((long long)x); }
 __device__ __forceinline__ uint64_t d2b(double x) { return (uint64_t)__double_as_longlong(x); }
 
+// (addresses below are a base per access pattern plus a constant per word: pad16(x + 16 y) =
+// pad16(x) + 17 y, which the compiler does not see through the shift)
 __device__ __forceinline__ int pad16(int x) { return x + (x >> 4); }
 
 // Rounds are lazy in both directions: 4 stages without correction, one centred reduction
@@ -43,8 +51,8 @@ __device__ __forceinline__ int pad16(int x) { return x + (x >> 4); }
 // what leaves a transform is canonical.
 
 // one round of 4 forward stages on 16 registers (strides t0 .. t0/8 within the tile)
-__device__ __forceinline__ void ct_round(double v[16], int t0, int hi, int tile, int logN1, const double *W, int N,
-                                         Mod m)
+template <typename P>
+__device__ __forceinline__ void ct_round(double v[16], int t0, int hi, int tile, int logN1, P W, int N, Mod m)
 {
 #pragma unroll
     for (int s = 0; s < 4; s++) {
@@ -67,9 +75,8 @@ __device__ __forceinline__ void ct_round(double v[16], int t0, int hi, int tile,
 
 // one round of 4 inverse stages (strides t0/8 .. t0); CANON: canonical words on entry, else
 // centred
-template <bool CANON>
-__device__ __forceinline__ void gs_round(double v[16], int t0, int hi, int tile, int logN1, const double *W, int N,
-                                         Mod m)
+template <bool CANON, typename P>
+__device__ __forceinline__ void gs_round(double v[16], int t0, int hi, int tile, int logN1, P W, int N, Mod m)
 {
 #pragma unroll
     for (int s = 3; s >= 0; s--) {
@@ -142,214 +149,77 @@ __device__ __forceinline__ void gs_round_tw(double v[16], const double tw[15], M
     for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
 }
 
+// orders a wave's LDS writes before its own later reads (no other wave is waited for)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a thread's first word across its wave
+__device__ __forceinline__ int wv(int tid) { return ((tid & ~63) << 4) | (tid & 63); }
+
 // The last 12 forward stages of one 4096-word tile: v holds words tid + 256 k (canonical
-// or centred) on entry; on return the transformed tile is in s (word x at pad16(x),
-// centred), after a barrier.
-// Each round's twiddles are requested before the barrier that precedes the round (the
-// registers of v are free there), so their latency overlaps the barrier wait.
+// or centred) on entry; on return the transformed words are in s (word x at pad16(x),
+// centred), and a thread may read its words wv(tid) + 64 k.  No other wave may still be
+// reading s on entry.  A round's twiddles are requested before the exchange that precedes it.
 __device__ __forceinline__ void tile_forward(double v[16], double *s, int tid, int tile, int logN1, const double *W,
                                              int N, Mod m)
 {
-    double tw[15];
-    // round 0: strides 2048..256, thread tid owns x = tid + 256 k
-    round_tw(tw, 2048, 0, tile, logN1, W, N);
-    ct_round_tw(v, tw, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(tid + 256 * k)] = v[k];
-    // round 1: strides 128..16, (lo, hi) = (tid & 15, tid >> 4): x = lo + 16 k + 256 hi
     const int lo = tid & 15, hi = tid >> 4;
+    double *sb = s + pad16(tid), *s1 = s + 272 * hi + lo, *s2 = s + 17 * tid, tw[15];
+    // round 0: strides 2048..256, thread tid owns x = tid + 256 k
+    ct_round(v, 2048, 0, tile, logN1, const_tab(W), N, m);
+#pragma unroll
+    for (int k = 0; k < 16; k++) sb[272 * k] = v[k];
+    // round 1: strides 128..16, (lo, hi) = (tid & 15, tid >> 4): x = lo + 16 k + 256 hi
     round_tw(tw, 128, hi, tile, logN1, W, N);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
+    for (int k = 0; k < 16; k++) v[k] = s1[17 * k];
     ct_round_tw(v, tw, m);
 #pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
+    for (int k = 0; k < 16; k++) s1[17 * k] = v[k];
     // round 2: strides 8..1, thread owns x = 16 tid + k
     round_tw(tw, 8, tid, tile, logN1, W, N);
-    __syncthreads();
+    wave_sync();
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
+    for (int k = 0; k < 16; k++) v[k] = s2[k];
     ct_round_tw(v, tw, m);
 #pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
-    __syncthreads();
+    for (int k = 0; k < 16; k++) s2[k] = v[k];
+    wave_sync();
 }
 
 // The first 12 inverse stages of one 4096-word tile (inverse twiddles W): v holds
-// words tid + 256 k on entry (canonical or centred) and on return (centred); s must be
-// free on entry (callers that used it before put a barrier first).  Twiddles requested
-// ahead as in tile_forward.
+// words wv(tid) + 64 k on entry (canonical or centred) and tid + 256 k on return (centred);
+// no other wave may still be reading s on entry.
 __device__ __forceinline__ void tile_inverse(double v[16], double *s, int tid, int tile, int logN1, const double *W,
                                              int N, Mod m)
 {
-    double tw[15];
+    const int lo = tid & 15, hi = tid >> 4;
+    double *sb = s + pad16(tid), *s1 = s + 272 * hi + lo, *s2 = s + 17 * tid, *sw = s + pad16(wv(tid)), tw[15];
     round_tw(tw, 8, tid, tile, logN1, W, N);
 #pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(tid + 256 * k)] = v[k];
-    __syncthreads();
+    for (int k = 0; k < 16; k++) sw[68 * k] = v[k];
+    wave_sync();
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
+    for (int k = 0; k < 16; k++) v[k] = s2[k];
     gs_round_tw<true>(v, tw, m);
 #pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
-    const int lo = tid & 15, hi = tid >> 4;
+    for (int k = 0; k < 16; k++) s2[k] = v[k];
     round_tw(tw, 128, hi, tile, logN1, W, N);
-    __syncthreads();
+    wave_sync();
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
+    for (int k = 0; k < 16; k++) v[k] = s1[17 * k];
     gs_round_tw<false>(v, tw, m);
 #pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
-    round_tw(tw, 2048, 0, tile, logN1, W, N);
+    for (int k = 0; k < 16; k++) s1[17 * k] = v[k];
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(tid + 256 * k)];
-    gs_round_tw<false>(v, tw, m);
-}
-
-// tile_forward and tile_inverse with each round's twiddles loaded where they are used
-// (fewer live registers, for kernels held to 128 VGPRs)
-__device__ __forceinline__ void tile_forward_lean(double v[16], double *s, int tid, int tile, int logN1, const double *W,
-                                             int N, Mod m)
-{
-    // round 0: strides 2048..256, thread tid owns x = tid + 256 k
-    ct_round(v, 2048, 0, tile, logN1, W, N, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(tid + 256 * k)] = v[k];
-    __syncthreads();
-    // round 1: strides 128..16, (lo, hi) = (tid & 15, tid >> 4): x = lo + 16 k + 256 hi
-    {
-        const int lo = tid & 15, hi = tid >> 4;
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
-        ct_round(v, 128, hi, tile, logN1, W, N, m);
-#pragma unroll
-        for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
-    }
-    __syncthreads();
-    // round 2: strides 8..1, thread owns x = 16 tid + k
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
-    ct_round(v, 8, tid, tile, logN1, W, N, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
-    __syncthreads();
-}
-
-__device__ __forceinline__ void tile_inverse_lean(double v[16], double *s, int tid, int tile, int logN1, const double *W,
-                                             int N, Mod m)
-{
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(tid + 256 * k)] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
-    gs_round<true>(v, 8, tid, tile, logN1, W, N, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
-    __syncthreads();
-    {
-        const int lo = tid & 15, hi = tid >> 4;
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
-        gs_round<false>(v, 128, hi, tile, logN1, W, N, m);
-#pragma unroll
-        for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(tid + 256 * k)];
-    gs_round<false>(v, 2048, 0, tile, logN1, W, N, m);
-}
-
-// The twiddles of one tile's forward pass (last 12 stages), for blocks that transform
-// many limbs of the same prime and tile: staged in LDS once, so that the transform
-// issues no vector memory operation and loads already in flight are never waited for
-// in it.  Round 0, stage s: entry i of 2^s at kTwR1 + kTwR2 + 2^s - 1 + i (every lane
-// reads the same word).  Round 1, stage s: entry (hi, i) of 16 2^s at 16 (2^s - 1) +
-// hi 2^s + i (16 lanes per word).  Round 2, stage s: entry (tid, i) of 256 2^s at kTwR1
-// + 256 (2^s - 1) + 256 i + tid (consecutive lanes, consecutive words).
-constexpr int kTwR1 = 240, kTwR2 = 3840, kTwR0 = 15, kTwAll = kTwR1 + kTwR2 + kTwR0;
-
-__device__ __forceinline__ void stage_tile_twiddles(double *tws, const double *W, int tile, int logN1, int N, int tid)
-{
-    constexpr int kPer = (kTwAll + kNT - 1) / kNT;
-    double w[kPer];
-#pragma unroll
-    for (int q = 0; q < kPer; q++) {  // all loads in flight before the first store
-        const int e = min(tid + kNT * q, kTwAll - 1);
-        int t0, st, ent;
-        if (e < kTwR1) {
-            st = e < 16 ? 0 : e < 48 ? 1 : e < 112 ? 2 : 3;
-            ent = e - 16 * ((1 << st) - 1);
-            t0 = 128;
-        } else if (e < kTwR1 + kTwR2) {
-            const int f = e - kTwR1;
-            st = f < 256 ? 0 : f < 768 ? 1 : f < 1792 ? 2 : 3;
-            const int g = f - 256 * ((1 << st) - 1);
-            ent = (g & 255) * (1 << st) + (g >> 8);
-            t0 = 8;
-        } else {
-            const int f = e - kTwR1 - kTwR2;
-            st = f < 1 ? 0 : f < 3 ? 1 : f < 7 ? 2 : 3;
-            ent = f - ((1 << st) - 1);
-            t0 = 2048;
-        }
-        const int mm = N / (2 * (t0 >> st));
-        w[q] = W[mm + tile * (mm >> logN1) + ent];
-    }
-#pragma unroll
-    for (int q = 0; q < kPer; q++)
-        if (tid + kNT * q < kTwAll) tws[tid + kNT * q] = w[q];
-}
-
-// ct_round of round R (0: hi = 0, 1: hi = tid >> 4, 2: hi = tid) with the twiddles
-// staged by stage_tile_twiddles
-template <int R>
-__device__ __forceinline__ void ct_round_lds(double v[16], const double *tws, int hi, Mod m)
-{
-#pragma unroll
-    for (int st = 0; st < 4; st++) {
-        const int step = 8 >> st;
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (k & step) continue;
-            const int i = k >> (4 - st);
-            const double w = R == 0   ? tws[kTwR1 + kTwR2 + (1 << st) - 1 + i]
-                             : R == 1 ? tws[16 * ((1 << st) - 1) + (hi << st) + i]
-                                      : tws[kTwR1 + 256 * ((1 << st) - 1) + 256 * i + hi];
-            const double U = v[k], V = mul_lazy(v[k + step], w, m);
-            v[k] = U + V;
-            v[k + step] = U - V;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
-}
-
-// tile_forward with the twiddles staged by stage_tile_twiddles
-__device__ __forceinline__ void tile_forward_lds(double v[16], double *s, const double *tws, int tid, Mod m)
-{
-    ct_round_lds<0>(v, tws, 0, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(tid + 256 * k)] = v[k];
-    __syncthreads();
-    {
-        const int lo = tid & 15, hi = tid >> 4;
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = s[pad16(lo + 16 * k + 256 * hi)];
-        ct_round_lds<1>(v, tws, hi, m);
-#pragma unroll
-        for (int k = 0; k < 16; k++) s[pad16(lo + 16 * k + 256 * hi)] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s[pad16(16 * tid + k)];
-    ct_round_lds<2>(v, tws, tid, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s[pad16(16 * tid + k)] = v[k];
-    __syncthreads();
+    for (int k = 0; k < 16; k++) v[k] = sb[272 * k];
+    gs_round<false>(v, 2048, 0, tile, logN1, const_tab(W), N, m);
 }
 
 // rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs).  With a column pass
@@ -367,6 +237,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t
     const uint64_t *in = src ? src + (size_t)lt.soff[limb] * N + (size_t)tile * kT : data + off;
     uint64_t *out = data + off;
     const double *W = tw + (size_t)pidx * N;
+    const int w0 = wv(tid);
     double v[16];
     if (!INV) {
         if (logN1 == 0) {
@@ -378,10 +249,10 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t
         }
         tile_forward(v, s, tid, tile, logN1, W, N, m);
 #pragma unroll
-        for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(corr(s[pad16(tid + 256 * k)], m));
+        for (int k = 0; k < 16; k++) out[w0 + 64 * k] = d2u(corr(s[pad16(w0) + 68 * k], m));
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+        for (int k = 0; k < 16; k++) v[k] = u2d(in[w0 + 64 * k]);
         tile_inverse(v, s, tid, tile, logN1, W, N, m);
         if (logN1 == 0) {
 #pragma unroll
@@ -393,45 +264,203 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t
     }
 }
 
-// Special-prime rows of a key inner product (a0: first half, a1: second, words
-// tid + 256 k of one tile) through the first 12 stages of ModDown's inverse transform
-// (W: inverse twiddles of that prime), stored at out (first half) and out + half_off
-// (second half).  Begins with a barrier, so s may still be in use on entry.
-__device__ __forceinline__ void store_p_rows(double a0[16], double a1[16], double *s, uint64_t *out, size_t half_off,
-                                             size_t w0, int tid, int tile, int logN1, const double *W, int N, Mod m)
+// ------------------------------------------- tile passes of 512 threads, 8 words each
+//
+// For k_ntt_ip, which holds a thread's sums and key words through the transform: 4 rounds
+// of 3 stages.  Round 0 (strides 2048..512) holds words tid + 512 k; after it a wave owns 512
+// contiguous words and the rest needs no barrier: round 1 (256..64) wv8(tid) + 64 k, round 2
+// (32..8) 64 (tid >> 3) + (tid & 7) + 8 k, round 3 (4..1) 8 tid + k.  The twiddles of rounds 0
+// and 1 are the same for a whole wave: scalar loads.  The LDS tile is padded by one word
+// every 8: every access pattern above then spreads over all banks.
+constexpr int kNT8 = 512;
+__device__ __forceinline__ int pad8(int x) { return x + (x >> 3); }
+__device__ __forceinline__ int wv8(int tid) { return ((tid & ~63) << 3) | (tid & 63); }
+
+// Twiddles of one tile's forward pass for blocks that transform many limbs of one prime and
+// tile, so that the transform waits for no vector memory operation: round 2's staged in LDS
+// (stage st: entry (g, i) of 64 2^st, g = tid >> 3, at 64 (2^st - 1) + (g << st) + i), round 3's 7
+// of each thread in its registers.
+constexpr int kTw8R2 = 64 * 7;
+
+__device__ __forceinline__ void load_twiddles8(double *tws, double tw3[7], const double *W, int tile, int logN1, int N,
+                                               int tid)
 {
-    __syncthreads();
-    tile_inverse(a0, s, tid, tile, logN1, W, N, m);
+    if (tid < kTw8R2) {
+        const int st = tid < 64 ? 0 : tid < 192 ? 1 : 2, mm = N / (2 * (32 >> st));
+        tws[tid] = W[mm + tile * (mm >> logN1) + tid - 64 * ((1 << st) - 1)];
+    }
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[w0 + 256 * k] = d2b(a0[k]);
-    __syncthreads();
-    tile_inverse(a1, s, tid, tile, logN1, W, N, m);
+    for (int st = 0; st < 3; st++) {
+        const int mm = N / (2 * (4 >> st));
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[half_off + w0 + 256 * k] = d2b(a1[k]);
+        for (int i = 0; i < (1 << st); i++) tw3[(1 << st) - 1 + i] = W[mm + tile * (mm >> logN1) + (tid << st) + i];
+    }
 }
 
-// x words of step q = z ND + j of a key inner product (job z, digit j) at words
-// w0 + 256 k: the job's own limb through X -> X^g, or the extended digit ([ND][ne][N])
-// as it came out of its column pass.  Buffer loads: one 32-bit offset register per
-// stream, the 256-word steps in the scalar offset.
-template <int ND>
-__device__ __forceinline__ void ip_load_x(const KeyJobs &kj, const IpRow &r, int q, uint32_t w0, int logN, uint32_t N,
-                                          uint64_t *xn)
+// one forward stage of a 3-stage round (st 0..2) on 8 words; tw(i): the stage's twiddle i
+template <typename F>
+__device__ __forceinline__ void ct8(double v[8], int st, Mod m, F tw)
 {
-    const int z = q / ND, j = q - z * ND;
-    if (j == r.own) {
-        const auto d = buf_rsrc(kj.d[z] + r.t * N, 8u * N);
-        const uint32_t g = kj.g[z];
+    const int step = 4 >> st;
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            xn[k] = buf_ld(d, 8u * (uint32_t)galois_src2((int)(w0 + 256u * k), g, logN), 0);  // g = 1: identity
-        }
-    } else {
-        const auto e = buf_rsrc(kj.ext[z], 8u * (uint32_t)(ND * r.ne) * N);
-        const uint32_t vo = 8u * ((uint32_t)(j * r.ne + r.t) * N + w0);
-#pragma unroll
-        for (int k = 0; k < 16; k++) xn[k] = buf_ld(e, vo, 2048u * k);
+    for (int k = 0; k < 8; k++) {
+        if (k & step) continue;
+        const double U = v[k], V = mul_lazy(v[k + step], tw(k >> (3 - st)), m);
+        v[k] = U + V;
+        v[k + step] = U - V;
     }
+}
+__device__ __forceinline__ void reduce8(double v[8], Mod m)
+{
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = reduce_c(v[k], m);
+}
+
+// The last 12 forward stages of one tile from centred words tid + 512 k, left in s at
+// pad8, below 2.2 t: the bound grows 1/2 -> 1.19 -> 2.13 -> 3.43 -> 5.22 -> 7.68 over 5
+// stages, so words are reduced after stages 5 and 10 only.  No other wave may still be
+// reading s on entry; on return a thread may read its words wv8(tid) + 64 k.  `mid` runs
+// after the one barrier.
+template <typename F>
+__device__ __forceinline__ void tile_forward8(double v[8], double *s, const double *tws, const double tw3[7], int tid,
+                                              int tile, int logN1, const double *W, int N, Mod m, F mid)
+{
+    const ConstTab<double> C = const_tab(W);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = tid >> 3;
+    double *sb = s + pad8(tid), *sw = s + pad8(wv8(tid)), *s2 = s + 72 * g + (tid & 7), *s3 = s + 9 * tid;
+    auto uni = [&](int t, int hi) {  // twiddles of stride t in block hi of that stride's round
+        const int mm = N / (2 * t);
+        return C + mm + tile * (mm >> logN1) + hi;
+    };
+#pragma unroll
+    for (int st = 0; st < 3; st++) {
+        const auto w = uni(2048 >> st, 0);
+        ct8(v, st, m, [&](int i) { return w[i]; });
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) sb[576 * k] = v[k];
+    __syncthreads();
+    mid();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = sw[72 * k];
+#pragma unroll
+    for (int st = 0; st < 3; st++) {
+        const auto w = uni(256 >> st, wave << st);
+        if (st == 2) reduce8(v, m);
+        ct8(v, st, m, [&](int i) { return w[i]; });
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) sw[72 * k] = v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = s2[9 * k];
+#pragma unroll
+    for (int st = 0; st < 3; st++) ct8(v, st, m, [&](int i) { return tws[64 * ((1 << st) - 1) + (g << st) + i]; });
+#pragma unroll
+    for (int k = 0; k < 8; k++) s2[9 * k] = v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = s3[k];
+#pragma unroll
+    for (int st = 0; st < 3; st++) {
+        if (st == 1) reduce8(v, m);
+        ct8(v, st, m, [&](int i) { return tw3[(1 << st) - 1 + i]; });
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) s3[k] = v[k];
+    wave_sync();
+}
+
+// one inverse stage of a 3-stage round (st 2..0) on 8 words
+template <typename F>
+__device__ __forceinline__ void gs8(double v[8], int st, Mod m, F tw)
+{
+    const int step = 4 >> st;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        if (k & step) continue;
+        const double U = v[k], V = v[k + step];
+        v[k] = U + V;
+        v[k + step] = mul_lazy(U - V, tw(k >> (3 - st)), m);
+    }
+}
+
+// The first 12 inverse stages of one tile from centred words wv8(tid) + 64 k to centred
+// words tid + 512 k (sums 1/2 -> 4 over a round).  No other wave may still be reading s.
+__device__ __forceinline__ void tile_inverse8(double v[8], double *s, int tid, int tile, int logN1, const double *W,
+                                              int N, Mod m)
+{
+    const ConstTab<double> C = const_tab(W);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = tid >> 3;
+    double *sb = s + pad8(tid), *sw = s + pad8(wv8(tid)), *s2 = s + 72 * g + (tid & 7), *s3 = s + 9 * tid;
+    auto at = [&](int t, int hi) {
+        const int hh = N / (2 * t);
+        return hh + tile * (hh >> logN1) + hi;
+    };
+#pragma unroll
+    for (int k = 0; k < 8; k++) sw[72 * k] = v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = s3[k];
+#pragma unroll
+    for (int st = 2; st >= 0; st--) {
+        const double *w = W + at(4 >> st, tid << st);
+        gs8(v, st, m, [&](int i) { return w[i]; });
+    }
+    reduce8(v, m);
+#pragma unroll
+    for (int k = 0; k < 8; k++) s3[k] = v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = s2[9 * k];
+#pragma unroll
+    for (int st = 2; st >= 0; st--) {
+        const double *w = W + at(32 >> st, g << st);
+        gs8(v, st, m, [&](int i) { return w[i]; });
+    }
+    reduce8(v, m);
+#pragma unroll
+    for (int k = 0; k < 8; k++) s2[9 * k] = v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = sw[72 * k];
+#pragma unroll
+    for (int st = 2; st >= 0; st--) {
+        const auto w = C + at(256 >> st, wave << st);
+        gs8(v, st, m, [&](int i) { return w[i]; });
+    }
+    reduce8(v, m);
+#pragma unroll
+    for (int k = 0; k < 8; k++) sw[72 * k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = sb[576 * k];
+#pragma unroll
+    for (int st = 2; st >= 0; st--) {
+        const auto w = C + at(2048 >> st, 0);
+        gs8(v, st, m, [&](int i) { return w[i]; });
+    }
+    reduce8(v, m);
+}
+
+// Requests the words of step q = z ND + j of a key inner product (job z, digit j) of one
+// tile into LDS (xb, in memory order): the extended digit's tile ([ND][ne][N], as it came out
+// of its column pass), or for the job's own limb the tile that X -> X^g reads (it moves whole
+// tiles).  16 bytes per lane straight to LDS: no registers held while they are under way.
+template <int ND>
+__device__ __forceinline__ void ip_request_x(const KeyJobs &kj, const IpRow &r, int q, int tile, int tid, int logN,
+                                             double *xb)
+{
+    const size_t N = (size_t)1 << logN;
+    const int z = q / ND, j = q - z * ND;
+    const uint64_t *p = j == r.own ? kj.d[z] + r.t * N + (galois_src2(tile * kT, kj.g[z], logN) & ~(kT - 1))
+                                   : kj.ext[z] + (j * r.ne + r.t) * N + tile * kT;
+    const auto rs = buf_rsrc(p, 8u * kT);
+    const uint32_t c0 = 4096u * __builtin_amdgcn_readfirstlane(tid >> 6), vo = 16u * (tid & 63);
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(xb + (c0 + 1024u * i) / 8u),
+                                                 16, vo, c0 + 1024u * i, 0, 0);
 }
 
 // Key inner products fused with the forward tile pass of the extended digits (N >=
@@ -447,88 +476,108 @@ __device__ __forceinline__ void ip_load_x(const KeyJobs &kj, const IpRow &r, int
 // = u_base + z 2 ne N (plus its previous value when accumulate): jobs vary fastest, so
 // jobs sharing one key read each key tile close together in time.  After each job the
 // running sums take at most ND <= 4 lazy terms on a reduced value.
-// Latency: a block works through its (job, digit) steps one after another with two
-// blocks per CU (256 registers per lane), so the words of the next step are requested
-// before this step's transform, and the transform reads its twiddles from LDS (staged
-// once per block) rather than memory: no wait in it holds up those loads.
+// A block works through its (job, digit) steps one after another, and both the memory
+// stream (32 KB of digit and 64 KB of key words a step) and the transform take most of a
+// step, so they have to overlap: a step's key words are requested before its transform, the
+// next step's digit words, straight to LDS, as soon as this step's have left it.  8 words
+// per thread leave room for that in 128 registers (4 waves per SIMD, two blocks per CU by
+// LDS); with 16 per thread at 2 waves per SIMD it spills.  7 giant steps at level 23 of N =
+// 2^16 (704 MB of keys, 352 MB of digits): 258 us with 256 threads and neither request
+// ahead, 236 this way, when the memory stream alone takes 228; one key switch at level 20
+// 48 and 39 us.
 template <int ND, bool SUM>
-__global__ __launch_bounds__(kNT, 2) void k_ntt_ip(KeyJobs kj, int n_jobs, uint64_t *u_base, int accumulate, int level,
-                                                int L, int alpha, int nq, const double *tw, const PrimeInfo *info,
-                                                int logN, uint64_t *pout, const double *itw, int skip)
+__global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint64_t *u_base, int accumulate, int level,
+                                                 int L, int alpha, int nq, const double *tw, const PrimeInfo *info,
+                                                 int logN, uint64_t *pout, const double *itw, int skip)
 {
-    __shared__ double s[kT + kT / 16];
-    __shared__ double tws[kTwAll];
+    __shared__ double s[kT + kT / 8];
+    __shared__ double xb[kT];
+    __shared__ double tws[kTw8R2];
     const int N = 1 << logN, logN1 = logN - 12;
     const int t = blockIdx.z == 0 ? 0 : (int)blockIdx.z + skip, tile = blockIdx.y, tid = threadIdx.x;
     const int pidx = t <= level ? t : nq + (t - level - 1);
     const Mod m = info[pidx].m;
     const double *W = tw + (size_t)pidx * N;
     const IpRow r = ip_row(t, level, L, alpha);
-    const size_t w0 = (size_t)tile * kT + tid;
+    const uint32_t t0 = (uint32_t)tile * kT;
+    const int wl = wv8(tid);
+    double *sw = s + pad8(wl);
+    const size_t w0 = t0 + wl;
     const int z0 = SUM ? 0 : (int)blockIdx.x, z1 = SUM ? n_jobs : z0 + 1;
     uint64_t *u = u_base + (SUM ? 0 : (size_t)z0 * 2 * r.ne * N);
     const size_t o0 = r.t * N + w0, o1 = (r.ne + r.t) * N + w0;
-    // steps q = z ND + j run in order; the words of step q + 1 are requested before step
-    // q's transform, so their latency hides behind it
     const int q0 = z0 * ND, q1 = z1 * ND;
-    uint64_t xn[16];
-    ip_load_x<ND>(kj, r, q0, (uint32_t)w0, logN, (uint32_t)N, xn);
-    stage_tile_twiddles(tws, W, tile, logN1, N, tid);
-    double a0[16], a1[16];
+    double tw3[7], a0[8], a1[8];
+    load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
+    ip_request_x<ND>(kj, r, q0, tile, tid, logN, xb);
     if (accumulate) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) a0[k] = u2d(u[o0 + 256 * k]), a1[k] = u2d(u[o1 + 256 * k]);
+        for (int k = 0; k < 8; k++) a0[k] = u2d(u[o0 + 64 * k]), a1[k] = u2d(u[o1 + 64 * k]);
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) a0[k] = 0.0, a1[k] = 0.0;
+        for (int k = 0; k < 8; k++) a0[k] = 0.0, a1[k] = 0.0;
     }
-    __syncthreads();  // staged twiddles visible
 #pragma unroll 1
     for (int q = q0; q < q1; q++) {
         const int z = q / ND, j = q - z * ND;
-        const bool own = j == r.own;
-        double x[16];
-        if (own) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = u2d(xn[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = b2d(xn[k]);
-        }
-        if (q + 1 < q1) ip_load_x<ND>(kj, r, q + 1, (uint32_t)w0, logN, (uint32_t)N, xn);
-        if (!own) {
-            __syncthreads();  // the previous step's words have been read out of s
-            tile_forward_lds(x, s, tws, tid, m);
-        } else {
-            // words every thread reads back itself (its own positions), as the
-            // transformed tile's are; no other thread touches them before the next barrier
-#pragma unroll
-            for (int k = 0; k < 16; k++) s[pad16(tid + 256 * k)] = x[k];
-        }
         // key [ND][2][nk][N]: words of row kl of digit j, b half then a half
         const auto key = buf_rsrc(kj.key[z], 8u * (uint32_t)(2 * ND * r.nk) * (uint32_t)N);
         const uint32_t vb = 8u * ((uint32_t)(j * 2 * r.nk + r.kl) * (uint32_t)N + (uint32_t)w0),
                        va = vb + 8u * (uint32_t)(r.nk * N);
+        uint64_t kb[8], ka[8];
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's words of step q are in xb
+        __syncthreads();                     // every wave's are, and the previous step's have been read out of s
+        const bool own = j == r.own;
+        double x[8];
+        if (own) {  // these words are the job's own limb's
+            const uint64_t *xu = (const uint64_t *)xb;
+            const uint32_t g = kj.g[z], gb = gal_base((int)w0, g, logN);
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            const double xv = s[pad16(tid + 256 * k)];
-            a0[k] += mul_lazy(xv, u2d(buf_ld(key, vb, 2048u * k)), m);
-            a1[k] += mul_lazy(xv, u2d(buf_ld(key, va, 2048u * k)), m);
-        }
-        if (j == ND - 1) {
+            for (int k = 0; k < 8; k++) x[k] = u2d(xu[gal_at(gb, 64 * k, g, logN) & (kT - 1)]);
+        } else {
 #pragma unroll
-            for (int k = 0; k < 16; k++) a0[k] = reduce_c(a0[k], m), a1[k] = reduce_c(a1[k], m);
+            for (int k = 0; k < 8; k++) x[k] = xb[tid + 512 * k];
         }
+#pragma unroll
+        for (int k = 0; k < 8; k++) kb[k] = buf_ld(key, vb, 512u * k);
+        auto next = [&]() {
+            if (q + 1 < q1) ip_request_x<ND>(kj, r, q + 1, tile, tid, logN, xb);
+        };
+        if (own) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) sw[72 * k] = x[k];  // read back by this thread alone
+            __syncthreads();
+            next();
+        } else {
+            tile_forward8(x, s, tws, tw3, tid, tile, logN1, W, N, m, next);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k++) ka[k] = buf_ld(key, va, 512u * k);
+#pragma unroll
+        for (int k = 0; k < 8; k++) {  // |x| < 2.2 t: products within 1.33 t, at most 4 on a centred sum
+            const double xv = sw[72 * k];
+            a0[k] += mul_lazy(xv, u2d(kb[k]), m);
+            a1[k] += mul_lazy(xv, u2d(ka[k]), m);
+        }
+        if (j == ND - 1) reduce8(a0, m), reduce8(a1, m);
     }
     if (pout && t > level) {  // special-prime rows: on to ModDown's inverse transform
-        store_p_rows(a0, a1, s, pout + ((size_t)2 * z0 * alpha + (t - level - 1)) * N, (size_t)alpha * N, w0, tid,
-                     tile, logN1, itw + (size_t)pidx * N, N, m);
+        uint64_t *out = pout + ((size_t)2 * z0 * alpha + (t - level - 1)) * N + t0 + tid;
+        const double *iW = itw + (size_t)pidx * N;
+        tile_inverse8(a0, s, tid, tile, logN1, iW, N, m);
+#pragma unroll
+        for (int k = 0; k < 8; k++) out[512 * k] = d2b(a0[k]);
+        __syncthreads();
+        tile_inverse8(a1, s, tid, tile, logN1, iW, N, m);
+        out += (size_t)alpha * N;
+#pragma unroll
+        for (int k = 0; k < 8; k++) out[512 * k] = d2b(a1[k]);
         return;
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        u[o0 + 256 * k] = d2u(corr(a0[k], m));
-        u[o1 + 256 * k] = d2u(corr(a1[k], m));
+    for (int k = 0; k < 8; k++) {
+        u[o0 + 64 * k] = d2u(corr(a0[k], m));
+        u[o1 + 64 * k] = d2u(corr(a1[k], m));
     }
 }
 
@@ -551,12 +600,12 @@ __global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, 
     const int t = level + 1 + a, pidx = nq + a;
     const Mod m = info[pidx].m;
     const IpRow r = ip_row(t, level, L, alpha);
-    const uint32_t g = kj.g[z], w0 = (uint32_t)tile * kT + tid;
+    const uint32_t g = kj.g[z], w0 = (uint32_t)tile * kT + wv(tid);
     const auto e = buf_rsrc(kj.ext[z], 8u * (uint32_t)(ND * r.ne) * (uint32_t)N);
     const auto key = buf_rsrc(kj.key[z], 8u * (uint32_t)(2 * ND * r.nk) * (uint32_t)N);
     uint32_t src[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) src[k] = 8u * (uint32_t)galois_src2((int)(w0 + 256u * k), g, logN);
+    for (int k = 0; k < 16; k++) src[k] = 8u * (uint32_t)galois_src2((int)(w0 + 64u * k), g, logN);
     double acc[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) acc[k] = 0.0;
@@ -566,12 +615,12 @@ __global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, 
                        vk = 8u * ((uint32_t)((j * 2 + p) * r.nk + r.kl) * (uint32_t)N + w0);
 #pragma unroll
         for (int k = 0; k < 16; k++)
-            acc[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 2048u * k)), m);
+            acc[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 512u * k)), m);
     }
 #pragma unroll
     for (int k = 0; k < 16; k++) acc[k] = reduce_c(acc[k], m);
     tile_inverse(acc, s, tid, tile, logN1, itw + (size_t)pidx * N, N, m);
-    uint64_t *out = pout + ((size_t)(2 * z + p) * alpha + a) * N + w0;
+    uint64_t *out = pout + ((size_t)(2 * z + p) * alpha + a) * N + (size_t)tile * kT + tid;
 #pragma unroll
     for (int k = 0; k < 16; k++) out[256 * k] = d2b(acc[k]);
 }
@@ -593,7 +642,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_gal(uint64_t *data, const uint
     double v[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        const int w = (int)w0 + 256 * k;
+        const int w = tile * kT + wv(tid) + 64 * k;
         v[k] = u2d(in[g == 1u ? w : galois_src2(w, g, logN)]);
     }
     tile_inverse(v, s, tid, tile, logN1, tw + (size_t)pidx * N, N, m);
@@ -810,17 +859,18 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
     }
-    tile_forward_lean(v, s, tid, tile, logN1, W, N, m);
+    tile_forward(v, s, tid, tile, logN1, W, N, m);
     const uint64_t *u = u_base + ((size_t)z * 2 * ne + (size_t)p * ne + i) * N + t0;
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     const uint32_t g = mj.g_add[z];
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
     const uint64_t *prev = acc0 && z == 0 ? acc0 + ((size_t)p * L1 + i) * N + t0 : out;
+    const int wl = wv(tid);
     const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        const int x = tid + 256 * k;
-        double t = mul_shoup_lazy(u2d(u[x]) - s[pad16(x)], pv, pvq, m);  // u in [0, t), s centred
+        const int x = wl + 64 * k;
+        double t = mul_shoup_lazy(u2d(u[x]) - s[pad16(wv(tid)) + 68 * k], pv, pvq, m);  // u in [0, t), s centred
         if (add) {
             const int kk = (int)t0 + x;
             t += u2d(add[(size_t)i * N + (g <= 1u ? kk : galois_src2(kk, g, logN))]);
@@ -840,9 +890,8 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
     }
     if (last_out && i == level) {  // the rescale's inverse tile pass of this limb
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(out[tid + 256 * k]);  // this thread's own words
-        __syncthreads();
-        tile_inverse_lean(v, s, tid, tile, logN1, itw + (size_t)i * N, N, m);
+        for (int k = 0; k < 16; k++) v[k] = u2d(out[wl + 64 * k]);  // this thread's own words
+        tile_inverse(v, s, tid, tile, logN1, itw + (size_t)i * N, N, m);
 #pragma unroll
         for (int k = 0; k < 16; k++) last_out[(size_t)p * N + t0 + tid + 256 * k] = d2b(v[k]);
     }
@@ -856,7 +905,7 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
 // part, after its tile pass) P^-1 plus add.  The products never go to memory.  Grid
 // (N/4096, 2 K (l+1)).
 template <int ND>
-__global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_md(const uint64_t *conv, KeyJobs kj, MdJobs mj, int level, int L,
+__global__ __launch_bounds__(kNT, ND == 4 ? 2 : 4) void k_key_ip_md(const uint64_t *conv, KeyJobs kj, MdJobs mj, int level, int L,
                                                       int alpha, const double *pinv, const double *pinvq,
                                                       const double *tw, const PrimeInfo *info, int logN)
 {
@@ -867,7 +916,7 @@ __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_m
     const Mod m = info[i].m;
     const size_t t0 = (size_t)tile * kT;
     const IpRow r = ip_row(i, level, L, alpha);
-    const uint32_t g = kj.g[z], w0 = (uint32_t)t0 + tid;
+    const uint32_t g = kj.g[z], w0 = (uint32_t)t0 + wv(tid);
     const auto e = buf_rsrc(kj.ext[z], 8u * (uint32_t)(ND * r.ne) * (uint32_t)N);
     const auto dd = buf_rsrc(kj.d[z] + (size_t)i * N, 8u * (uint32_t)N);
     const auto key = buf_rsrc(kj.key[z], 8u * (uint32_t)(2 * ND * r.nk) * (uint32_t)N);
@@ -876,7 +925,7 @@ __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_m
         uint32_t src[16];
 #pragma unroll
         for (int k = 0; k < 16; k++)
-            src[k] = 8u * (g <= 1u ? w0 + 256u * k : (uint32_t)galois_src2((int)(w0 + 256u * k), g, logN));
+            src[k] = 8u * (g <= 1u ? w0 + 64u * k : (uint32_t)galois_src2((int)(w0 + 64u * k), g, logN));
 #pragma unroll
         for (int k = 0; k < 16; k++) a[k] = 0.0;
 #pragma unroll
@@ -885,12 +934,12 @@ __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_m
             if (j == r.own) {
 #pragma unroll
                 for (int k = 0; k < 16; k++)
-                    a[k] += mul_lazy(u2d(buf_ld(dd, src[k], 0)), u2d(buf_ld(key, vk, 2048u * k)), m);
+                    a[k] += mul_lazy(u2d(buf_ld(dd, src[k], 0)), u2d(buf_ld(key, vk, 512u * k)), m);
             } else {
                 const uint32_t xo = 8u * (uint32_t)((j * r.ne + r.t) * N);
 #pragma unroll
                 for (int k = 0; k < 16; k++)
-                    a[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 2048u * k)), m);
+                    a[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 512u * k)), m);
             }
         }
 #pragma unroll
@@ -900,15 +949,15 @@ __global__ __launch_bounds__(kNT, ND == 1 ? 3 : ND == 4 ? 2 : 4) void k_key_ip_m
     double v[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
-    tile_forward_lean(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
+    tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     const uint32_t ga = mj.g_add[z];
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
     const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        const int x = tid + 256 * k;
-        double t = mul_shoup_lazy(a[k] - s[pad16(x)], pv, pvq, m);  // both centred
+        const int x = wv(tid) + 64 * k;
+        double t = mul_shoup_lazy(a[k] - s[pad16(wv(tid)) + 68 * k], pv, pvq, m);  // both centred
         if (add) {
             const int kk = (int)t0 + x;
             t += u2d(add[(size_t)i * N + (ga <= 1u ? kk : galois_src2(kk, ga, logN))]);
@@ -977,8 +1026,8 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
     const double wl = qlinv[level * nq + i], wlq = qlinvq[level * nq + i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        const int x = tid + 256 * k;
-        o[x] = d2u(corr(mul_shoup_lazy(u2d(a[x]) - s[pad16(x)], wl, wlq, m), m));
+        const int x = wv(tid) + 64 * k;
+        o[x] = d2u(corr(mul_shoup_lazy(u2d(a[x]) - s[pad16(wv(tid)) + 68 * k], wl, wlq, m), m));
     }
 }
 
@@ -1185,11 +1234,11 @@ hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jo
         return hipErrorInvalidValue;
     const double bytes = 8.0 * N * (ne - skip) * (3.0 * nd * n_jobs + 2.0 * (sum ? 1 : n_jobs) * (1 + accumulate));
     const dim3 grid(sum ? 1 : n_jobs, N1, ne - skip);
-#define NJ_IP(ND)                                                                                                   \
-    case ND:                                                                                                        \
-        return sum ? launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, true>, grid, dim3(kNT), s, kj, n_jobs, u, accumulate, \
-                            level, c->L, c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip)     \
-                   : launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, false>, grid, dim3(kNT), s, kj, n_jobs, u, accumulate, \
+#define NJ_IP(ND)                                                                                                    \
+    case ND:                                                                                                         \
+        return sum ? launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, true>, grid, dim3(kNT8), s, kj, n_jobs, u, accumulate, \
+                            level, c->L, c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip)      \
+                   : launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, false>, grid, dim3(kNT8), s, kj, n_jobs, u, accumulate, \
                             level, c->L, c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip);
     switch (nd) {
         NJ_IP(1) NJ_IP(2) NJ_IP(3) NJ_IP(4)
