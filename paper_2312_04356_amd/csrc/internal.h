@@ -141,16 +141,25 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *base, uin
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
 }
+// NT: non-temporal, for words that pass through once.  What a kernel writes otherwise stays
+// dirty in the 256 MiB last-level cache and is written back while the next kernel reads:
+// 341 MB of words written and then read beside 682 MB of keys took 226 us to read, 182 with
+// non-temporal stores, 165 with non-temporal key loads as well; the writes themselves took
+// 53 us either way.  No size was found where the extended digits or keys do better cached:
+// with both non-temporal from 0, 64, 128 or 256 MB per launch on, a rotation at N = 2^16
+// takes 118.6, 121.7, 121.5, 123.5 us, the benchmark's step 3.25, 3.26, 3.28, 3.39 ms.
+template <bool NT = false>
 __device__ __forceinline__ uint64_t buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    const nj_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    const nj_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, NT ? 2 : 0);
     return ((uint64_t)v.y << 32) | v.x;
 }
+template <bool NT = false>
 __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint64_t x)
 {
     nj_u32x2 v;
     v.x = (uint32_t)x, v.y = (uint32_t)(x >> 32);
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, NT ? 2 : 0);
 }
 
 // Real/imaginary split fused into a one-job ModDown combine: with the combined value

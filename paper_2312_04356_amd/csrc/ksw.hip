@@ -114,7 +114,7 @@ __device__ __forceinline__ void load_babies(const MacPlan &mp, size_t zoff, size
 
 // w[b] = word o of diagonal d_of[g][b] (diagonals dstride words apart), zero where
 // absent; false if giant step g has no diagonal at all
-template <int NBM>
+template <int NBM, bool NT = false>
 __device__ __forceinline__ bool load_giant(const MacPlan &mp, int g, const uint64_t *diag, size_t dstride, size_t o,
                                            double *w)
 {
@@ -127,7 +127,8 @@ __device__ __forceinline__ bool load_giant(const MacPlan &mp, int g, const uint6
 #pragma unroll
     for (int b = 0; b < NBM; b++) {
         const int d = b < mp.nb ? mp.d_of[g][b] : -1;
-        r[b] = diag[(size_t)(d < 0 ? any : d) * dstride + o];
+        const uint64_t *dp = diag + (size_t)(d < 0 ? any : d) * dstride + o;
+        r[b] = NT ? __builtin_nontemporal_load(dp) : *dp;
     }
 #pragma unroll
     for (int b = 0; b < NBM; b++) {
@@ -164,14 +165,14 @@ __global__ __launch_bounds__(kBT) void k_bsgs_mac(MacPlan mp, const uint64_t *di
     for (int g = 0; g < mp.ng; g++) {
         uint64_t *o0 = inner + (size_t)g * 2 * L1 * N + o, *o1 = o0 + L1 * N;
         double w[NBM];
-        const bool any = load_giant<NBM>(mp, g, diag, (size_t)mp.dl * N, o, w);
+        const bool any = load_giant<NBM, true>(mp, g, diag, (size_t)mp.dl * N, o, w);
         const double a0 = accumulate ? u2d(*o0) : 0.0, a1 = accumulate ? u2d(*o1) : 0.0;
         if (!any) {
             if (!accumulate) *o0 = 0, *o1 = 0;
             continue;
         }
-        *o0 = d2u(mac_row<NBM>(a0, b0, w, m));
-        *o1 = d2u(mac_row<NBM>(a1, b1, w, m));
+        __builtin_nontemporal_store(d2u(mac_row<NBM>(a0, b0, w, m)), o0);
+        __builtin_nontemporal_store(d2u(mac_row<NBM>(a1, b1, w, m)), o1);
     }
 }
 
@@ -620,14 +621,13 @@ hipError_t launch_bsgs_mac(const nj_ctx *c, int level, const MacPlan &mp, const 
     if (mp.nb < 1 || mp.nb > NJ_MAX_BABY || mp.ng < 0 || mp.ng > NJ_MAX_GIANT) return hipErrorInvalidValue;
     dim3 grid((c->N + kBT - 1) / kBT, level + 1);
     const double bytes = 8.0 * c->N * (level + 1) * (2.0 * mp.nb + n_diag + (2.0 + 2 * accumulate) * mp.ng);
-    if (mp.nb <= 4)
-        return launch(c, PROF_PMAC, bytes, k_bsgs_mac<4>, grid, dim3(kBT), s, mp, diag, inner, level, accumulate,
-                      c->d_info, c->log_n);
-    if (mp.nb <= 8)
-        return launch(c, PROF_PMAC, bytes, k_bsgs_mac<8>, grid, dim3(kBT), s, mp, diag, inner, level, accumulate,
-                      c->d_info, c->log_n);
-    return launch(c, PROF_PMAC, bytes, k_bsgs_mac<16>, grid, dim3(kBT), s, mp, diag, inner, level, accumulate,
-                  c->d_info, c->log_n);
+#define NJ_MAC(NB)                                                                                                 \
+    return launch(c, PROF_PMAC, bytes, k_bsgs_mac<NB>, grid, dim3(kBT), s, mp, diag, inner, level, accumulate, \
+                  c->d_info, c->log_n)
+    if (mp.nb <= 4) NJ_MAC(4);
+    if (mp.nb <= 8) NJ_MAC(8);
+    NJ_MAC(16);
+#undef NJ_MAC
 }
 
 }  // namespace nj

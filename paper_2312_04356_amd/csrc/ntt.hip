@@ -484,8 +484,8 @@ __device__ __forceinline__ void ip_request_x(const KeyJobs &kj, const IpRow &r, 
 // LDS); with 16 per thread at 2 waves per SIMD it spills.  7 giant steps at level 23 of N =
 // 2^16 (704 MB of keys, 352 MB of digits): 258 us with 256 threads and neither request
 // ahead, 236 this way, when the memory stream alone takes 228; one key switch at level 20
-// 48 and 39 us.
-template <int ND, bool SUM>
+// 48 and 39 us.  Non-temporal key words and digits: 216 and 33 us.
+template <int ND, bool SUM, bool NT>
 __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint64_t *u_base, int accumulate, int level,
                                                  int L, int alpha, int nq, const double *tw, const PrimeInfo *info,
                                                  int logN, uint64_t *pout, const double *itw, int skip)
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint
             for (int k = 0; k < 8; k++) x[k] = xb[tid + 512 * k];
         }
 #pragma unroll
-        for (int k = 0; k < 8; k++) kb[k] = buf_ld(key, vb, 512u * k);
+        for (int k = 0; k < 8; k++) kb[k] = buf_ld<NT>(key, vb, 512u * k);
         auto next = [&]() {
             if (q + 1 < q1) ip_request_x<ND>(kj, r, q + 1, tile, tid, logN, xb);
         };
@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint
             tile_forward8(x, s, tws, tw3, tid, tile, logN1, W, N, m, next);
         }
 #pragma unroll
-        for (int k = 0; k < 8; k++) ka[k] = buf_ld(key, va, 512u * k);
+        for (int k = 0; k < 8; k++) ka[k] = buf_ld<NT>(key, va, 512u * k);
 #pragma unroll
         for (int k = 0; k < 8; k++) {  // |x| < 2.2 t: products within 1.33 t, at most 4 on a centred sum
             const double xv = sw[72 * k];
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, 
                        vk = 8u * ((uint32_t)((j * 2 + p) * r.nk + r.kl) * (uint32_t)N + w0);
 #pragma unroll
         for (int k = 0; k < 16; k++)
-            acc[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 512u * k)), m);
+            acc[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld<true>(key, vk, 512u * k)), m);
     }
 #pragma unroll
     for (int k = 0; k < 16; k++) acc[k] = reduce_c(acc[k], m);
@@ -648,7 +648,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_gal(uint64_t *data, const uint
     tile_inverse(v, s, tid, tile, logN1, tw + (size_t)pidx * N, N, m);
     uint64_t *out = data + (size_t)lt.off[limb] * N + w0;
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[256 * k] = d2b(v[k]);
+    for (int k = 0; k < 16; k++) __builtin_nontemporal_store(d2b(v[k]), out + 256 * k);
 }
 
 // The first log2(N1) forward stages on one column of N1 words, canonical or centred (lazy,
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kBcCols * kBcWaves, 4) void k_bconv_col(BconvShared
         col_forward<N1>(v, const_tab(tw) + (size_t)pq * N, mo);
         const auto out = buf_rsrc(jp.out[job] + (size_t)sh.out_off[j][o] * N, 8u * N);
 #pragma unroll
-        for (int r = 0; r < N1; r++) buf_st(out, cb, 8u * r * kT, d2b(v[r]));
+        for (int r = 0; r < N1; r++) buf_st<true>(out, cb, 8u * r * kT, d2b(v[r]));
     }
 }
 
@@ -934,12 +934,12 @@ __global__ __launch_bounds__(kNT, ND == 4 ? 2 : 4) void k_key_ip_md(const uint64
             if (j == r.own) {
 #pragma unroll
                 for (int k = 0; k < 16; k++)
-                    a[k] += mul_lazy(u2d(buf_ld(dd, src[k], 0)), u2d(buf_ld(key, vk, 512u * k)), m);
+                    a[k] += mul_lazy(u2d(buf_ld(dd, src[k], 0)), u2d(buf_ld<true>(key, vk, 512u * k)), m);
             } else {
                 const uint32_t xo = 8u * (uint32_t)((j * r.ne + r.t) * N);
 #pragma unroll
                 for (int k = 0; k < 16; k++)
-                    a[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld(key, vk, 512u * k)), m);
+                    a[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld<true>(key, vk, 512u * k)), m);
             }
         }
 #pragma unroll
@@ -1234,16 +1234,20 @@ hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jo
         return hipErrorInvalidValue;
     const double bytes = 8.0 * N * (ne - skip) * (3.0 * nd * n_jobs + 2.0 * (sum ? 1 : n_jobs) * (1 + accumulate));
     const dim3 grid(sum ? 1 : n_jobs, N1, ne - skip);
-#define NJ_IP(ND)                                                                                                    \
-    case ND:                                                                                                         \
-        return sum ? launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, true>, grid, dim3(kNT8), s, kj, n_jobs, u, accumulate, \
-                            level, c->L, c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip)      \
-                   : launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, false>, grid, dim3(kNT8), s, kj, n_jobs, u, accumulate, \
-                            level, c->L, c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip);
+    // key words stay in the caches only for the jobs that share them (a batch: 33.3 ms cached,
+    // 35.8 non-temporal; giant steps with a key each at N = 2^14: 0.78 and 0.75 ms a step)
+    const bool shared = !sum && n_jobs > 1 && kj.key[0] == kj.key[1];
+#define NJ_IP_K(ND, SUM, NT)                                                                                         \
+    launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, SUM, NT>, grid, dim3(kNT8), s, kj, n_jobs, u, accumulate, level, c->L, \
+           c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip)
+#define NJ_IP(ND)                                                                                                   \
+    case ND:                                                                                                        \
+        return sum ? NJ_IP_K(ND, true, true) : shared ? NJ_IP_K(ND, false, false) : NJ_IP_K(ND, false, true);
     switch (nd) {
         NJ_IP(1) NJ_IP(2) NJ_IP(3) NJ_IP(4)
     }
 #undef NJ_IP
+#undef NJ_IP_K
     return hipErrorInvalidValue;
 }
 
