@@ -149,21 +149,18 @@ class Ev {
         if (ok()) check(launch_zero(c, o.d, K * cstride(l), s));
         return o;
     }
-    // tensor product, relinearisation, rescale
-    Cx hmult(const Cx &a, const Cx &b)
+    // tensor product and relinearisation, at the operands' level
+    Cx hmult_raw(const Cx &a, const Cx &b)
     {
         const int l = std::min(a.l, b.l);
         Cx t = alloc(l, 0.0), d2 = alloc(l, 0.0);  // t [K][2][l+1], d2 [K][l+1]
-        Cx o = alloc(l - 1, a.s * b.s / (double)c->primes[l]);
-        if (!ok()) return o;
-        for (int z = 0; z < K; z++)
-            check(launch_tensor(c, a.d + z * cstride(a.l), N * (a.l + 1), b.d + z * cstride(b.l), N * (b.l + 1),
-                                t.d + z * cstride(l), d2.d + z * N * (l + 1), l, s));
+        if (!ok()) return t;
+        check(launch_tensor(c, a.d, N * (a.l + 1), b.d, N * (b.l + 1), t.d, d2.d, l, K, s));
         Arena A = ks;
         MultiBufs M;  // the batched key-switch path: its fused kernels, one job per ciphertext
         if (!multi_bufs(c, l, K, A, M)) {
             check(fail(NJ_ENOMEM, "ModEval: key-switch scratch"));
-            return o;
+            return t;
         }
         const bool f = fuse_ip(c, l);
         check(modup_multi(c, l, K, d2.d, M, s, -1, !f));
@@ -175,8 +172,56 @@ class Ev {
             mj.add[z] = nullptr, mj.g_add[z] = 1, mj.out[z] = t.d + z * cstride(l);
         }
         check(f ? ks_fused(c, l, K, kj, mj, 0, t.d, M, s) : ks_multi(c, l, K, kj, mj, 0, t.d, M, s));  // t += the switched d2
-        rescale_into(t, o, A);
-        release(t), release(d2);
+        release(d2);
+        return t;
+    }
+    // tensor product, relinearisation, rescale
+    Cx hmult(const Cx &a, const Cx &b)
+    {
+        Cx t = hmult_raw(a, b);
+        Cx o = alloc(t.l - 1, a.s * b.s / (double)c->primes[t.l]);
+        if (!ok()) return o;
+        rescale_into(t, o, ks);
+        release(t);
+        return o;
+    }
+    // Several rescaled terms summed in one go (N >= 8192, see launch_rescale_sum): the words
+    // are those of rescaling each w_j (k_j x_j) by itself and adding the results.
+    bool sums() const { return N >= 8192; }
+    struct Term {
+        const Cx *x;
+        long long k;
+        int w;
+    };
+    Cx rescale_sum(std::initializer_list<Term> terms, int l, double sc, long long cst, const Cx *add = nullptr)
+    {
+        return rescale_sum(std::vector<Term>(terms), l, sc, cst, add);
+    }
+    Cx rescale_sum(const std::vector<Term> &terms, int l, double sc, long long cst, const Cx *add = nullptr)
+    {
+        Cx o = alloc(l - 1, sc);
+        Arena A = ks;
+        uint64_t *last = A.take(terms.size() * 2 * K * N);
+        if (!last && err == NJ_OK) err = fail(NJ_ENOMEM, "ModEval: key-switch scratch");
+        if (!ok()) return o;
+        RsTerms rt;
+        rt.n = 0;
+        const LimbConsts cc = residues(cst, l);
+        for (int i = 0; i < l; i++) rt.c[i] = cc.v[i];
+        rt.add = add ? add->d : nullptr;
+        const unsigned __int128 ninv = (unsigned long long)c->info[l].ninv;
+        for (const Term &t : terms) {
+            const int j = rt.n++;
+            rt.src[j] = t.x->d, rt.stride[j] = t.x->l + 1, rt.w[j] = t.w;
+            const LimbConsts kc = residues(t.k, l + 1);
+            rt.kn[j] = (double)(unsigned long long)(ninv * (unsigned long long)kc.v[l] % c->primes[l]);
+            for (int i = 0; i < l; i++) {
+                const long long q = (long long)c->primes[i];
+                const long long r = (long long)((__int128)(long long)kc.v[i] * t.w % q);
+                rt.kw[j][i] = (double)(r < 0 ? r + q : r);
+            }
+        }
+        check(launch_rescale_sum(c, l, rt, o.d, last, 2 * K, s));
         return o;
     }
     // c * x at level lam with recorded scale tau; d == nullptr when the constant is 0
@@ -195,6 +240,13 @@ class Ev {
     }
     Cx sq_minus1(const Cx &a)  // 2 a^2 - 1
     {
+        if (sums()) {
+            Cx t = hmult_raw(a, a);
+            const double sc = a.s * a.s / (double)c->primes[t.l];
+            Cx o = rescale_sum({{&t, 1, 2}}, t.l, sc, (long long)std::nearbyint(-1.0 * sc));
+            release(t);
+            return o;
+        }
         Cx p = hmult(a, a);
         Cx o = add(p, p, 0);
         release(p);
@@ -203,6 +255,14 @@ class Ev {
     }
     Cx prod_minus(const Cx &a, const Cx &b, const Cx &cc)  // 2 a b - c
     {
+        if (sums()) {  // both terms are rescaled by the same prime
+            Cx t = hmult_raw(a, b);
+            const double ql = (double)c->primes[t.l], sc = a.s * b.s / ql;
+            const long long k = (long long)std::nearbyint(1.0 * sc * ql / cc.s);
+            Cx o = rescale_sum({{&t, 1, 2}, {&cc, k, -1}}, t.l, sc, 0);
+            release(t);
+            return o;
+        }
         Cx p = hmult(a, b);
         Cx c2 = const_mult(cc, 1.0, p.l, p.s);
         Cx p2 = add(p, p, 0);
@@ -253,6 +313,15 @@ class Ev {
         if (d < 8 && c->eval_order == 0) {
             // each term c_j T_j brought to level lam, scale tau by its own constant multiply
             // and rescale, then the terms summed
+            if (sums()) {
+                std::vector<Term> terms;
+                for (int j = 1; j <= d; j++) {
+                    const long long k = (long long)std::nearbyint(cf[j] * tau * (double)c->primes[lam + 1] / T[j].s);
+                    if (k != 0) terms.push_back({&T[j], k, 1});
+                }
+                if (!terms.empty())
+                    return rescale_sum(terms, lam + 1, tau, (long long)std::nearbyint(cf[0] * tau));
+            }
             Cx acc;
             for (int j = 1; j <= d; j++) {
                 if (cf[j] == 0.0) continue;
@@ -314,8 +383,16 @@ class Ev {
         } else {
             Q = eval(q, lam + 1, tau_q);
         }
+        if (sums()) {  // the remainder added where the product is rescaled
+            if (!bm) rr = eval(r, lam, tau);
+            Cx t = hmult_raw(Q, T[G]);
+            release(Q);  // (a branch's slot joins this free list: the branch is done)
+            Cx o = rescale_sum({{&t, 1, 1}}, t.l, tau, 0, &rr);
+            release(t), release(rr);
+            return o;
+        }
         Cx prod = hmult(Q, T[G]);
-        release(Q);  // (a branch's slot joins this free list: the branch is done)
+        release(Q);
         if (!bm) rr = eval(r, lam, tau);
         Cx o = add(prod, rr, 0);
         o.s = tau;

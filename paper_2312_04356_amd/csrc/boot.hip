@@ -11,7 +11,8 @@ constexpr int kT = 256;
 }
 
 // d0 = a0 b0, d1 = a0 b1 + a1 b0 into d01 [2][l+1][N]; d2 = a1 b1 into d2 [l+1][N].
-// a, b are ciphertexts at levels >= l (second polynomial at +astride / +bstride words).
+// a, b are ciphertexts at levels >= l (second polynomial at +astride / +bstride words),
+// blockIdx.z the packed ciphertext.
 __global__ __launch_bounds__(kT) void k_tensor(const uint64_t *a, size_t astride, const uint64_t *b, size_t bstride,
                                                uint64_t *d01, uint64_t *d2, int level, const PrimeInfo *info, int logN)
 {
@@ -19,7 +20,8 @@ __global__ __launch_bounds__(kT) void k_tensor(const uint64_t *a, size_t astride
     const int k = blockIdx.x * kT + threadIdx.x;
     if (k >= N) return;
     const Mod m = info[i].m;
-    const size_t o = (size_t)i * N + k, L1 = level + 1;
+    const size_t o = (size_t)i * N + k, L1 = level + 1, z = blockIdx.z;
+    a += 2 * z * astride, b += 2 * z * bstride, d01 += 2 * z * L1 * N, d2 += z * L1 * N;
     const double x0 = u2d(a[o]), x1 = u2d(a[astride + o]), y0 = u2d(b[o]), y1 = u2d(b[bstride + o]);
     d01[o] = d2u(mul_canon(x0, y0, m));
     d01[L1 * N + o] = d2u(reduce(mul_lazy(x0, y1, m) + mul_lazy(x1, y0, m), m));
@@ -60,10 +62,10 @@ __global__ __launch_bounds__(kT) void k_zero(uint64_t *p, size_t words)
 }
 
 hipError_t launch_tensor(const nj_ctx *c, const uint64_t *a, size_t astride, const uint64_t *b, size_t bstride,
-                         uint64_t *d01, uint64_t *d2, int level, hipStream_t s)
+                         uint64_t *d01, uint64_t *d2, int level, int n_ct, hipStream_t s)
 {
-    dim3 grid((c->N + kT - 1) / kT, level + 1);
-    return launch(c, PROF_OTHER, 8.0 * c->N * (level + 1) * 7.0, k_tensor, grid, dim3(kT), s, a, astride, b, bstride,
+    dim3 grid((c->N + kT - 1) / kT, level + 1, n_ct);
+    return launch(c, PROF_OTHER, 8.0 * c->N * (level + 1) * 7.0 * n_ct, k_tensor, grid, dim3(kT), s, a, astride, b, bstride,
                   d01, d2, level, c->d_info, c->log_n);
 }
 

@@ -201,6 +201,19 @@ struct LimbConsts {
     double v[64];
 };
 
+// Sum of rescaled terms, out = sum_j w_j rescale(k_j x_j) + c + add over P packed polynomials
+// (launch_rescale_sum): x_j's polynomial z, at src[j] + z stride[j] N, has limbs 0..l;
+// kw[j][i] = w_j k_j mod q_i; kn[j] = N^-1 k_j mod q_l; w[j] a small integer; c[i] added to
+// even polynomials (the first of each ciphertext), add [P][l][N] or null.
+#define NJ_MAX_TERMS 8
+struct RsTerms {
+    int n;
+    int stride[NJ_MAX_TERMS];
+    const uint64_t *src[NJ_MAX_TERMS];
+    double w[NJ_MAX_TERMS], kn[NJ_MAX_TERMS], kw[NJ_MAX_TERMS][32], c[32];
+    const uint64_t *add;
+};
+
 struct MacPlan {
     int nb, ng;
     int dl;  // limbs per stored diagonal (the plan's encoding level + 1)
@@ -350,6 +363,11 @@ hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *sr
                              const GalTab *gt = nullptr, int L1 = 0);
 hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, uint64_t *out, int n_out,
                                 uint64_t *last, uint64_t *lifted, hipStream_t s, int n_polys = 2, bool last_tiled = false);
+// sum of the rescaled terms of rt from level l (N >= 8192, at most 8 terms, sum |w_j| <= 8):
+// P polynomials into out [P][l][N]; last: scratch [terms][P][N].  Equal word for word to
+// multiplying, rescaling and adding the terms one by one
+hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uint64_t *out, uint64_t *last,
+                              int n_polys, hipStream_t s);
 hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, hipStream_t s);
 hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs,
                             const double *scale, hipStream_t s);
@@ -423,8 +441,9 @@ hipError_t launch_key_ip_shared(const nj_ctx *c, int level, const KeyJobs &kj, i
 hipError_t launch_bsgs_mac_multi(const nj_ctx *c, int level, const MacPlan &mp, int n_ct, size_t bstride,
                                  size_t istride, const uint64_t *diag, uint64_t *inner, int n_diag, hipStream_t s);
 // inner[g] = sum_b baby_b (.) diag[d_of[g][b]] for every giant g; inner [ng][2][l+1][N]
+// (n_ct packed ciphertexts: a's and b's 2 astride and 2 bstride words apart, d01 [n_ct][2][l+1][N], d2 [n_ct][l+1][N])
 hipError_t launch_tensor(const nj_ctx *c, const uint64_t *a, size_t astride, const uint64_t *b, size_t bstride,
-                         uint64_t *d01, uint64_t *d2, int level, hipStream_t s);
+                         uint64_t *d01, uint64_t *d2, int level, int n_ct, hipStream_t s);
 hipError_t launch_mul_int(const nj_ctx *c, const uint64_t *in, size_t istride, uint64_t *out, int n_limbs,
                           const LimbConsts &kc, hipStream_t s, int accumulate = 0, int n_polys = 2);
 hipError_t launch_add_int(const nj_ctx *c, uint64_t *poly, int n_limbs, const LimbConsts &kc, hipStream_t s);

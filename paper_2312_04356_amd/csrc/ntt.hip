@@ -674,8 +674,8 @@ __device__ __forceinline__ void col_forward(double v[N1], P W, Mod m)
 
 // The last log2(N1) inverse stages on one column of N1 centred words, uncorrected: at
 // most 4 stages, 8 t in magnitude.
-template <int N1>
-__device__ __forceinline__ void col_inverse(double v[N1], const double *W, Mod m)
+template <int N1, typename P>
+__device__ __forceinline__ void col_inverse(double v[N1], P W, Mod m)
 {
 #pragma unroll
     for (int h = N1 / 2; h >= 1; h >>= 1) {
@@ -1031,6 +1031,89 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
     }
 }
 
+// Sums of rescaled terms (RsTerms).  Rescaling is linear modulo each remaining prime:
+// sum_j w_j (k_j x_j - lift_j) q_l^-1, lift_j the centred last limb of k_j x_j, needs one forward
+// transform, of sum_j w_j lift_j (an integer below 8 2^49), however many terms there are.  A
+// baby-step sum of ModEval (7 terms, Re and Im packed, N = 2^16) is 3 launches instead of
+// 36, a layer (activation and StoC1 included) 8.7 ms instead of 11.7.
+// k_lift_sum: the terms' last limbs after their inverse tile pass (last [terms][P][N]),
+// their last log2(N1) inverse stages with the factor N^-1 k_j, centred and summed, lifted
+// into targets i < n_out with their forward column pass; grid as k_lift_col's.
+template <int N1>
+__global__ __launch_bounds__(kNT) void k_lift_sum(const uint64_t *last, RsTerms rt, int level, int n_polys, int n_out,
+                                                  int per, uint64_t *lifted, const double *tw, const double *itw,
+                                                  const PrimeInfo *info, int logN)
+{
+    const int N = 1 << logN, z = blockIdx.z;
+    const uint32_t cb = 8u * (blockIdx.x * kNT + threadIdx.x);
+    const Mod ms = info[level].m;
+    double x[N1];
+#pragma unroll
+    for (int r = 0; r < N1; r++) x[r] = 0.0;
+#pragma unroll 1
+    for (int j = 0; j < rt.n; j++) {
+        const auto src = buf_rsrc(last + ((size_t)j * n_polys + z) * N, 8u * N);
+        double v[N1];
+#pragma unroll
+        for (int r = 0; r < N1; r++) v[r] = b2d(buf_ld(src, cb, 8u * r * kT));
+        col_inverse<N1>(v, const_tab(itw) + (size_t)level * N, ms);
+        const double kn = rt.kn[j], w = rt.w[j];
+#pragma unroll
+        for (int r = 0; r < N1; r++)  // centred exactly, as in k_lift_col
+            x[r] = fma(w, reduce_c(reduce_c(mul_lazy(v[r], kn, ms), ms), ms), x[r]);
+    }
+    const int i1 = min(n_out, (int)(blockIdx.y + 1) * per);
+#pragma unroll 1
+    for (int i = blockIdx.y * per; i < i1; i++) {
+        const Mod mt{const_tab(info)[i].m.t, const_tab(info)[i].m.ti};
+        double v[N1];
+#pragma unroll
+        for (int r = 0; r < N1; r++) v[r] = reduce_c(x[r], mt);
+        col_forward<N1>(v, const_tab(tw) + (size_t)i * N, mt);
+        const auto dst = buf_rsrc(lifted + ((size_t)z * n_out + i) * N, 8u * N);
+#pragma unroll
+        for (int r = 0; r < N1; r++) buf_st(dst, cb, 8u * r * kT, d2b(v[r]));
+    }
+}
+
+// k_ntt_tile_rsum: the lifted sums' tile pass with the combine as its epilogue,
+// out[z][i] = (sum_j kw_j x_j[z][i] - NTT(lift)[z][i]) q_l^-1 + c + add; grid (N/4096, P n_out).
+// The terms' lazy products stay within 8 7/8 t.
+__global__ __launch_bounds__(kNT) void k_ntt_tile_rsum(const uint64_t *lifted, RsTerms rt, uint64_t *out, int level,
+                                                       int n_out, const double *qlinv, const double *qlinvq, int nq,
+                                                       const double *tw, const PrimeInfo *info, int logN)
+{
+    __shared__ double s[kT + kT / 16];
+    const int N = 1 << logN, logN1 = logN - 12;
+    const int w = blockIdx.y, z = w / n_out, i = w - z * n_out;
+    const int tile = blockIdx.x, tid = threadIdx.x, wl = wv(tid);
+    const Mod m = info[i].m;
+    const size_t t0 = (size_t)tile * kT;
+    const uint64_t *src = lifted + (size_t)w * N + t0;
+    double v[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
+    tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = -s[pad16(wl) + 68 * k];
+#pragma unroll 1
+    for (int j = 0; j < rt.n; j++) {
+        const uint64_t *a = rt.src[j] + ((size_t)z * rt.stride[j] + i) * N + t0 + wl;
+        const double kw = rt.kw[j][i];
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] += mul_lazy(u2d(a[64 * k]), kw, m);
+    }
+    uint64_t *o = out + (size_t)w * N + t0 + wl;
+    const uint64_t *add = rt.add ? rt.add + (size_t)w * N + t0 + wl : nullptr;
+    const double wi = qlinv[level * nq + i], wiq = qlinvq[level * nq + i], cc = z & 1 ? 0.0 : rt.c[i];
+#pragma unroll
+    for (int k = 0; k < 16; k++) {
+        double t = corr(mul_shoup_lazy(reduce_c(v[k], m), wi, wiq, m) + cc, m);
+        if (add) t = add_mod(t, u2d(add[64 * k]), m);
+        o[64 * k] = d2u(t);
+    }
+}
+
 template <bool INV>
 static hipError_t launch_cols(const nj_ctx *c, int kind, double bytes, int N1, dim3 grid, hipStream_t s,
                               uint64_t *data, const uint64_t *src, const LimbTab &lt, const double *tw,
@@ -1126,6 +1209,48 @@ hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, 
     if (e != hipSuccess) return e;
     return launch(c, PROF_OTHER, 8.0 * N * n_polys * n_out * 4.0, k_ntt_tile_rs, dim3(N1, n_polys * n_out), dim3(kNT),
                   s, lifted, in, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q, c->d_tw, c->d_info, c->log_n);
+}
+
+hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uint64_t *out, uint64_t *last,
+                              int n_polys, hipStream_t s)
+{
+    const int N = c->N, N1 = N / kT, P = n_polys, n_out = level;
+    if (N1 < 2 || level < 1 || level > 31 || rt.n < 1 || rt.n > NJ_MAX_TERMS || P < 1 || rt.n * P > NJ_MAX_LIMBS)
+        return hipErrorInvalidValue;
+    double wsum = 0;
+    const uint64_t *base = rt.src[0];
+    for (int j = 0; j < rt.n; j++) wsum += std::fabs(rt.w[j]), base = std::min(base, rt.src[j]);
+    if (wsum > 8) return hipErrorInvalidValue;
+    LimbTab lt;
+    lt.n = 0;
+    for (int j = 0; j < rt.n; j++)
+        for (int z = 0; z < P; z++) {
+            const size_t d = rt.src[j] - base;  // the terms live in one scratch buffer, whole limbs apart
+            if (d % N || d / N > (size_t)1 << 30) return hipErrorInvalidValue;
+            lt.pidx[lt.n] = level, lt.off[lt.n] = lt.n, lt.soff[lt.n] = (int)(d / N) + z * rt.stride[j] + level;
+            lt.n++;
+        }
+    hipError_t e = launch_intt_tiles(c, last, base, lt, s);
+    if (e != hipSuccess) return e;
+    // the inverse column passes are repeated per target chunk: two chunks for many terms,
+    // two targets at a time, as launch_lift_col, for one or two
+    const int per = rt.n > 2 ? (n_out + 1) / 2 : 2;
+    const dim3 g(kT / kNT, (n_out + per - 1) / per, P);
+    const double b = 8.0 * N * P * (rt.n + n_out);
+#define NJ_LS(NN)                                                                                                  \
+    case NN:                                                                                                       \
+        e = launch(c, PROF_OTHER, b, k_lift_sum<NN>, g, dim3(kNT), s, last, rt, level, P, n_out, per, out, c->d_tw, \
+                   c->d_itw, c->d_info, c->log_n);                                                                 \
+        break;
+    switch (N1) {
+        NJ_LS(2) NJ_LS(4) NJ_LS(8) NJ_LS(16)
+    default: return hipErrorInvalidValue;
+    }
+#undef NJ_LS
+    if (e != hipSuccess) return e;
+    return launch(c, PROF_OTHER, 8.0 * N * P * n_out * (2.0 + rt.n + (rt.add ? 1 : 0)), k_ntt_tile_rsum,
+                  dim3(N1, P * n_out), dim3(kNT), s, out, rt, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q,
+                  c->d_tw, c->d_info, c->log_n);
 }
 
 // Forward tile pass alone (the column pass already applied), N >= 8192.
