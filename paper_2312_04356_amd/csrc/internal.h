@@ -361,6 +361,8 @@ hipError_t launch_ntt(const nj_ctx *c, uint64_t *data, const LimbTab &lt, bool i
 // src through X -> X^g[job])
 hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt, hipStream_t s,
                              const GalTab *gt = nullptr, int L1 = 0);
+// c0 + c1 s in coefficient form, out [level + 1][N] (N >= 4096)
+hipError_t launch_decrypt_fast(const nj_ctx *c, const uint64_t *ct, int level, uint64_t *out, hipStream_t s);
 hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, uint64_t *out, int n_out,
                                 uint64_t *last, uint64_t *lifted, hipStream_t s, int n_polys = 2, bool last_tiled = false);
 // sum of the rescaled terms of rt from level l (N >= 8192, at most 8 terms, sum |w_j| <= 8):
