@@ -886,18 +886,22 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
     }
+    const int wl = wv(tid);
+    const uint64_t *u = u_base + ((size_t)z * 2 * ne + (size_t)p * ne + i) * N + t0 + wl;
+    uint64_t uv[16];  // requested before the transform, in which their latency passes: conv +
+                      // CoeffToSlot at N = 2^14 750 -> 734 us
+#pragma unroll
+    for (int k = 0; k < 16; k++) uv[k] = u[64 * k];
     tile_forward(v, s, tid, tile, logN1, W, N, m);
-    const uint64_t *u = u_base + ((size_t)z * 2 * ne + (size_t)p * ne + i) * N + t0;
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     const uint32_t g = mj.g_add[z];
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
     const uint64_t *prev = acc0 && z == 0 ? acc0 + ((size_t)p * L1 + i) * N + t0 : out;
-    const int wl = wv(tid);
     const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const int x = wl + 64 * k;
-        double t = mul_shoup_lazy(u2d(u[x]) - s[pad16(wv(tid)) + 68 * k], pv, pvq, m);  // u in [0, t), s centred
+        double t = mul_shoup_lazy(u2d(uv[k]) - s[pad16(wv(tid)) + 68 * k], pv, pvq, m);  // u in [0, t), s centred
         if (add) {
             const int kk = (int)t0 + x;
             t += u2d(add[(size_t)i * N + (g <= 1u ? kk : galois_src2(kk, g, logN))]);
@@ -1047,14 +1051,18 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
     double v[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
+    const uint64_t *a = in + ((size_t)z * (level + 1) + i) * N + t0 + wv(tid);
+    uint64_t av[16];  // requested before the transform, in which their latency passes: a
+                      // mask's product and rescale at level 18, N = 2^16, 65 -> 61.6 us
+#pragma unroll
+    for (int k = 0; k < 16; k++) av[k] = a[64 * k];
     tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
-    const uint64_t *a = in + ((size_t)z * (level + 1) + i) * N + t0;
     uint64_t *o = out + ((size_t)z * n_out + i) * N + t0;
     const double wl = qlinv[level * nq + i], wlq = qlinvq[level * nq + i];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const int x = wv(tid) + 64 * k;
-        o[x] = d2u(corr(mul_shoup_lazy(u2d(a[x]) - s[pad16(wv(tid)) + 68 * k], wl, wlq, m), m));
+        o[x] = d2u(corr(mul_shoup_lazy(u2d(av[k]) - s[pad16(wv(tid)) + 68 * k], wl, wlq, m), m));
     }
 }
 
