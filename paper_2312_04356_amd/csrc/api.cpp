@@ -173,9 +173,6 @@ nj_status modup_multi(nj_ctx *c, int l, int K, const uint64_t *d, MultiBufs &M, 
 
 // K key switches from already-extended digits: inner products, ModDown, combine.
 // sum = 0: job z writes mj.out[z]; sum = 1: mj.out[0] = acc + sum of all jobs.
-nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint64_t *acc, MultiBufs &M,
-                  hipStream_t s, bool p_tiled, uint64_t *last_out, const MdConj *conj, bool drop, const KeyJobs *ipq);
-
 nj_status ks_multi(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj, int sum, const uint64_t *acc,
                    MultiBufs &M, hipStream_t s)
 {
@@ -194,7 +191,8 @@ nj_status ks_multi(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
 // Q limbs' inner products are computed inside the combine from these jobs' extended
 // evaluation-form digits instead of read from M.u; plain combine only).
 nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint64_t *acc, MultiBufs &M,
-                  hipStream_t s, bool p_tiled, uint64_t *last_out, const MdConj *conj, bool drop, const KeyJobs *ipq)
+                  hipStream_t s, bool p_tiled, uint64_t *last_out, const MdConj *conj, bool drop, const KeyJobs *ipq,
+                  size_t acc_stride)
 {
     const int N = c->N, ne = l + 1 + c->alpha, al = c->alpha;
     const bool fused = N >= 8192 && al <= 8;  // as in modup_multi
@@ -256,7 +254,7 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
             }
         }
     NJ_HIP(ntt(lq));
-    NJ_HIP(launch_moddown_multi(c, l, mj, K, sum, M.u, M.conv, acc, s));
+    NJ_HIP(launch_moddown_multi(c, l, mj, K, sum, M.u, M.conv, acc, s, acc_stride));
     return NJ_OK;
 }
 
@@ -264,12 +262,13 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
 // x 16 baby steps (later baby passes accumulate): inner_g = sum over entries (g, b, dg)
 // of diag_dg (.) baby_b.  With no babies the giant steps' inner sums are zero.
 nj_status mac_general(nj_ctx *c, int l, const std::vector<const uint64_t *> &baby, int ng,
-                      const std::vector<MacEntry> &ent, const uint64_t *diag, int dl, uint64_t *inner, hipStream_t s)
+                      const std::vector<MacEntry> &ent, const uint64_t *diag, int dl, uint64_t *inner, hipStream_t s,
+                      int blocks, size_t dblock, size_t iblock)
 {
     const size_t clen = 2 * (size_t)c->N * (l + 1);
     const int nb = (int)baby.size();
     if (nb == 0 || ent.empty()) {  // every diagonal zero: every inner sum is the zero ciphertext
-        if (ng > 0) NJ_HIP(launch_zero(c, inner, (size_t)ng * clen, s));
+        for (int b = 0; ng > 0 && b < blocks; b++) NJ_HIP(launch_zero(c, inner + b * iblock, (size_t)ng * clen, s));
         return NJ_OK;
     }
     for (int g0 = 0; g0 < ng; g0 += NJ_MAX_GIANT) {
@@ -283,7 +282,7 @@ nj_status mac_general(nj_ctx *c, int l, const std::vector<const uint64_t *> &bab
             int used = 0;
             for (const MacEntry &e : ent)
                 if (e.g >= g0 && e.g < g0 + gn && e.b >= b0 && e.b < b0 + mp.nb) mp.d_of[e.g - g0][e.b - b0] = e.dg, used++;
-            NJ_HIP(launch_bsgs_mac(c, l, mp, diag, inner + g0 * clen, used, s, b0 > 0));
+            NJ_HIP(launch_bsgs_mac(c, l, mp, diag, inner + g0 * clen, used, s, b0 > 0, blocks, dblock, iblock));
         }
     }
     return NJ_OK;
@@ -648,10 +647,34 @@ nj_lt_t at_level(const nj_lt_t &lt, int l)
 // each output block's giant-step inner sums run over all its nonzero input blocks in
 // multiply-accumulate passes of at most 16 babies, and each giant rotation is one
 // shared-key key switch over the output blocks, accumulated into the outputs.
+// Where the key switches are fused (fuse_ip) and a block has at most NJ_MAX_JOBS giant steps,
+// all babies (giants) of all inputs (outputs) go through them together, up to NJ_MAX_JOBS at a
+// time, instead of one rotation of up to kBatch ciphertexts per key read: the launches are
+// short, and 16 instead of 48 of them at level 1.  Fused / general, N = 2^16, 4 x 4 blocks of
+// 16 diagonals: 394 / 614 us at level 1, 1.03 / 1.32 ms at level 8, 2.80 / 3.17 ms at level 23;
+// N = 2^14: 127 / 288 us at level 3, 210 / 377 us at level 11.
+static bool block_fused(const nj_ctx *c, const nj_lt_t &lt, int l)
+{
+    int ng = 0;
+    for (int g : lt.giants) ng += g != 0;
+    return fuse_ip(c, l) && ng <= NJ_MAX_JOBS;
+}
+
+// key switches per launch, and the buffers' jobs
+static int block_jobs(const nj_ctx *c, const nj_lt_t &lt, int l)
+{
+    int K = std::min(std::max(lt.bi, lt.bo), kBatch), nb = 0, ng = 0;
+    if (!block_fused(c, lt, l)) return K;
+    for (int b : lt.babies) nb += b != 0;
+    for (int g : lt.giants) ng += g != 0;
+    K = std::max(K, std::min(NJ_MAX_JOBS, nb * std::min(lt.bi, kBatch)));
+    return ng ? std::max(K, ng * std::min(lt.bo, NJ_MAX_JOBS / ng)) : K;
+}
+
 size_t block_words(const nj_ctx *c, const nj_lt_t &lt)
 {
     const size_t N = c->N, l = lt.level, clen = 2 * N * (l + 1);
-    const int K = std::min(std::max(lt.bi, lt.bo), kBatch);
+    const int K = block_jobs(c, lt, (int)l);
     return clen * (lt.bi * lt.babies.size() + lt.bo * lt.giants.size()) + multi_words(c, l, K);
 }
 
@@ -669,15 +692,37 @@ nj_status block_bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uin
     uint64_t *baby_all = A.take(clen * bi * nb);   // [nb][bi][clen], baby 0 is the input itself
     uint64_t *inner_all = A.take(clen * bo * ng);  // [bo][ng][clen]
     MultiBufs M;
-    if (!baby_all || !inner_all || !multi_bufs(c, l, std::min(std::max(bi, bo), kBatch), A, M))
+    if (!baby_all || !inner_all || !multi_bufs(c, l, block_jobs(c, lt, l), A, M))
         return fail(NJ_ENOMEM, "scratch too small");
     const size_t ndig = n_digits(c, l), ne = l + 1 + c->alpha;
+    const bool fused = block_fused(c, lt, l);
     nj_status st;
     // baby steps of every input, kBatch inputs per ModUp
     for (int z0 = 0; nb > 1 && z0 < bi; z0 += kBatch) {
         const int K = std::min(kBatch, bi - z0);
         const uint64_t *x = in + z0 * clen;
         if ((st = modup_multi(c, l, K, x + plen, M, s, 2 * (l + 1)))) return st;
+        if (fused) {
+            KeyJobs kj;
+            MdJobs mj;
+            int J = 0;
+            for (int b = 0, left = (nb - (lt.babies[0] == 0)) * K; b < nb; b++) {
+                if (lt.babies[b] == 0) continue;
+                const uint32_t g = galois_of_rot(c, (long long)lt.babies[b] * lt.u);
+                for (int z = 0; z < K; z++) {
+                    kj.ext[J] = M.ext + (size_t)z * ndig * ne * N, kj.d[J] = x + z * clen + plen, kj.g[J] = g;
+                    kj.key[J] = key_of(c, g);
+                    mj.add[J] = x + z * clen, mj.g_add[J] = g;
+                    mj.out[J] = baby_all + ((size_t)b * bi + z0 + z) * clen;
+                    left--;
+                    if (++J == NJ_MAX_JOBS || left == 0) {
+                        if ((st = ks_multi(c, l, J, kj, mj, 0, nullptr, M, s))) return st;
+                        J = 0;
+                    }
+                }
+            }
+            continue;
+        }
         for (int b = 0; b < nb; b++) {
             if (lt.babies[b] == 0) continue;
             const uint32_t g = galois_of_rot(c, (long long)lt.babies[b] * lt.u);
@@ -698,7 +743,11 @@ nj_status block_bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uin
         bidx[d] = (int)(std::lower_bound(lt.babies.begin(), lt.babies.end(), lt.i_of[d]) - lt.babies.begin());
     }
     auto nonzero = [&](int ob, int ib, int d) { return lt.nz.empty() || lt.nz[((size_t)ob * bi + ib) * nd + d]; };
-    for (int ob = 0; ob < bo; ob++) {
+    bool same = true;  // every output block has the same nonzero diagonals: one launch for all
+    for (int ob = 1; ob < bo && same; ob++)
+        for (int ib = 0; ib < bi && same; ib++)
+            for (int d = 0; d < nd && same; d++) same = nonzero(ob, ib, d) == nonzero(0, ib, d);
+    for (int ob = 0; ob < (same ? 1 : bo); ob++) {
         std::vector<int> ibs;
         for (int ib = 0; ib < bi; ib++)
             for (int d = 0; d < nd; d++)
@@ -717,9 +766,47 @@ nj_status block_bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uin
             for (int d = 0; d < nd; d++)
                 if (nonzero(ob, ib, d)) ent.push_back(MacEntry{gidx[d], b0 + bidx[d], ib * nd + d});
         }
-        if ((st = mac_general(c, l, bs, ng, ent, dbase, lt.dl, inner, s))) return st;
+        if ((st = mac_general(c, l, bs, ng, ent, dbase, lt.dl, inner, s, same ? bo : 1, (size_t)bi * nd * lt.dl * N,
+                              ng * clen)))
+            return st;
     }
     // giant steps
+    if (fused) {
+        const uint64_t *acc = nullptr;
+        std::vector<int> gl;
+        for (int g = 0; g < ng; g++)
+            if (lt.giants[g] == 0) acc = inner_all + (size_t)g * clen;
+            else gl.push_back(g);
+        const int G = (int)gl.size();
+        if (G == 0) {
+            if (acc)
+                NJ_HIP(hipMemcpy2DAsync(out, clen * 8, acc, ng * clen * 8, clen * 8, bo, hipMemcpyDeviceToDevice, s));
+            return NJ_OK;
+        }
+        for (int o0 = 0, B = NJ_MAX_JOBS / G; o0 < bo; o0 += B) {  // job gi B + ob: neighbours share a key
+            const int nB = std::min(B, bo - o0), J = G * nB;
+            KeyJobs kj;
+            MdJobs mj;
+            GalTab gt;
+            int zoff[NJ_MAX_JOBS];
+            for (int gi = 0; gi < G; gi++)
+                for (int ob = 0; ob < nB; ob++) {
+                    const int z = gi * nB + ob, blk = (o0 + ob) * ng + gl[gi];
+                    const uint32_t ge = galois_of_rot(c, (long long)lt.giants[gl[gi]] * lt.n1 * lt.u);
+                    const uint64_t *x = inner_all + (size_t)blk * clen;
+                    kj.ext[z] = M.ext + (size_t)z * ndig * ne * N, kj.d[z] = x + plen, kj.g[z] = gt.g[z] = ge;
+                    kj.key[z] = key_of(c, ge), zoff[z] = blk * 2 * (l + 1);
+                    mj.add[z] = x, mj.g_add[z] = ge;
+                }
+            for (int ob = 0; ob < nB; ob++) mj.out[ob] = out + (o0 + ob) * clen;
+            if ((st = modup_multi(c, l, J, inner_all + plen, M, s, -1, false, &gt, zoff))) return st;
+            NJ_HIP(launch_ntt_ip(c, l, kj, J, M.u, 0, 0, s, M.pc));
+            if ((st = ks_down(c, l, J, mj, nB, acc ? acc + (size_t)o0 * ng * clen : nullptr, M, s, true, nullptr, nullptr,
+                              false, nullptr, ng * clen)))
+                return st;
+        }
+        return NJ_OK;
+    }
     bool have = false;
     for (int g = 0; g < ng; g++)
         if (lt.giants[g] == 0) {

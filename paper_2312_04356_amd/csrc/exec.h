@@ -82,18 +82,20 @@ nj_status ks_multi(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
 // (sum = 0: for K = 1 it may be any ciphertext, else it must be the outputs).
 // last_out, one job, N >= 8192: the output's last limb also leaves through the first
 // 12 stages of its inverse transform into last_out [2][N], for rescale(last_pre))
+// sum > 0: mj.out[g], g < sum, = acc + g acc_stride + the sum of the jobs g, g + sum, ..
 // drop: only output limbs 0 and l (the fused one-job combine, no last_out or conj, l >= 2;
 // the inner products' Q rows 0 and l and special-prime rows are all it reads)
 nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint64_t *acc, MultiBufs &M,
                   hipStream_t s, bool p_tiled = false, uint64_t *last_out = nullptr, const MdConj *conj = nullptr,
-                  bool drop = false, const KeyJobs *ipq = nullptr);
+                  bool drop = false, const KeyJobs *ipq = nullptr, size_t acc_stride = 0);
 
 // inner_g += diag_dg (.) baby_b for each entry, any number of baby and giant steps
 struct MacEntry {
     int g, b, dg;
 };
 nj_status mac_general(nj_ctx *c, int l, const std::vector<const uint64_t *> &baby, int ng,
-                      const std::vector<MacEntry> &ent, const uint64_t *diag, int dl, uint64_t *inner, hipStream_t s);
+                      const std::vector<MacEntry> &ent, const uint64_t *diag, int dl, uint64_t *inner, hipStream_t s,
+                      int blocks = 1, size_t dblock = 0, size_t iblock = 0);
 
 nj_lt_t at_level(const nj_lt_t &lt, int l);
 size_t bsgs_words(const nj_ctx *c, const nj_lt_t &lt);

@@ -434,8 +434,10 @@ hipError_t launch_bconv_multi(const nj_ctx *c, const BconvShared &sh, const Bcon
 // < 0: all l + 1 + alpha; rows = l + 1: the Q limbs alone)
 hipError_t launch_key_ip_multi(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u_base,
                                hipStream_t s, int rows = -1);
-hipError_t launch_moddown_multi(const nj_ctx *c, int level, const MdJobs &mj, int n_jobs, int sum,
-                                const uint64_t *u_base, const uint64_t *conv_base, const uint64_t *acc, hipStream_t s);
+// (groups: 0 = one output per job, else outputs that sum the jobs g, g + groups, ..)
+hipError_t launch_moddown_multi(const nj_ctx *c, int level, const MdJobs &mj, int n_jobs, int groups,
+                                const uint64_t *u_base, const uint64_t *conv_base, const uint64_t *acc, hipStream_t s,
+                                size_t acc_stride = 0);
 hipError_t launch_automorph_multi(const nj_ctx *c, const AutoJobs &aj, int n_jobs, int n_limbs, hipStream_t s);
 hipError_t launch_key_ip_shared(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, const uint64_t *key,
                                 uint64_t *u_base, hipStream_t s,
@@ -456,9 +458,11 @@ hipError_t launch_key_ip_sum(const nj_ctx *c, int level, const KeyJobs &kj, int 
 hipError_t launch_automorph_acc(const nj_ctx *c, const AutoJobs &aj, int n_jobs, int n_limbs, uint64_t *out,
                                 size_t ostride, int mode, hipStream_t s, int skip = 0);
 hipError_t launch_key_ip_mixed(const nj_ctx *c, const KeyJobsX &kj, int n_jobs, const uint64_t *key, hipStream_t s);
+// (blocks: that many transforms of one structure at once, their diagonals dblock and their
+// sums iblock words apart)
 hipError_t launch_bsgs_mac(const nj_ctx *c, int level, const MacPlan &mp, const uint64_t *diag, uint64_t *inner,
-                           int n_diag, hipStream_t s,
-                           int accumulate = 0);
+                           int n_diag, hipStream_t s, int accumulate = 0, int blocks = 1, size_t dblock = 0,
+                           size_t iblock = 0);
 
 // --------------------------------------------------------------- noalloc.hip
 // looks up (once per device, the device current) the static scratch of

@@ -152,9 +152,11 @@ __device__ __forceinline__ double mac_row(double a, const double *x, const doubl
 }
 
 template <int NBM>
-__global__ __launch_bounds__(kBT) void k_bsgs_mac(MacPlan mp, const uint64_t *diag, uint64_t *inner, int level,
-                                                 int accumulate, const PrimeInfo *info, int logN)
+__global__ __launch_bounds__(kBT) void k_bsgs_mac(MacPlan mp, const uint64_t *diag, uint64_t *inner, size_t dblock,
+                                                 size_t iblock, int level, int accumulate, const PrimeInfo *info,
+                                                 int logN)
 {
+    diag += blockIdx.z * dblock, inner += blockIdx.z * iblock;
     const int N = 1 << logN, i = blockIdx.y;
     const int k = blockIdx.x * kBT + threadIdx.x;
     if (k >= N) return;
@@ -334,23 +336,24 @@ hipError_t launch_key_ip_multi(const nj_ctx *c, int level, const KeyJobs &kj, in
                             dim3(kBT), s, kj, u_base, nd, level, c->L, c->alpha, c->n_q, c->d_info, c->log_n));
 }
 
-// ModDown combine of many jobs.  sum == 0: job z writes out[z] (blockIdx.z = 2 job + half),
-// adding the previous out[z] when acc is non-null; sum == 1: out[0] = acc + sum over jobs
-// (blockIdx.z = half).  Job z's u at u_base + z 2 ne N,
-// its converted limbs at conv_base + z 2 (l+1) N, its c0 (read through X -> X^g_add[z]) at add[z].
-__global__ __launch_bounds__(kBT) void k_moddown_multi(MdJobs mj, int n_jobs, int sum, const uint64_t *u_base,
-                                                      const uint64_t *conv_base, const uint64_t *acc, int level,
-                                                      int ne, const double *pinv, const PrimeInfo *info, int logN)
+// ModDown combine of many jobs.  groups == 0: job z writes out[z] (blockIdx.z = 2 job + half),
+// adding the previous out[z] when acc is non-null; groups > 0: out[g] = acc + g acc_stride +
+// the sum over the jobs g, g + groups, .. (blockIdx.z = 2 g + half).  Job z's u at u_base +
+// z 2 ne N, its converted limbs at conv_base + z 2 (l+1) N, its c0 (read through
+// X -> X^g_add[z]) at add[z].
+__global__ __launch_bounds__(kBT) void k_moddown_multi(MdJobs mj, int n_jobs, int groups, const uint64_t *u_base,
+                                                      const uint64_t *conv_base, const uint64_t *acc,
+                                                      size_t acc_stride, int level, int ne, const double *pinv,
+                                                      const PrimeInfo *info, int logN)
 {
     const int N = 1 << logN, i = blockIdx.y;
     const int k = blockIdx.x * kBT + threadIdx.x;
     if (k >= N) return;
     const Mod m = info[i].m;
     const int L1 = level + 1;
-    const int p = sum ? blockIdx.z : (blockIdx.z & 1);
-    const int z0 = sum ? 0 : (blockIdx.z >> 1), z1 = sum ? n_jobs : z0 + 1;
+    const int p = blockIdx.z & 1, z0 = blockIdx.z >> 1, z1 = groups ? n_jobs : z0 + 1, step = groups ? groups : 1;
     double r = 0.0;
-    for (int z = z0; z < z1; z++) {
+    for (int z = z0; z < z1; z += step) {
         const uint64_t *u = u_base + (size_t)z * 2 * ne * N, *cv = conv_base + (size_t)z * 2 * L1 * N;
         double t = mul_canon(sub_mod(u2d(u[((size_t)p * ne + i) * N + k]), u2d(cv[((size_t)p * L1 + i) * N + k]), m),
                              pinv[i], m);
@@ -362,22 +365,20 @@ __global__ __launch_bounds__(kBT) void k_moddown_multi(MdJobs mj, int n_jobs, in
         r = add_mod(r, t, m);
     }
     const size_t o = ((size_t)p * L1 + i) * N + k;
-    if (sum) {
-        if (acc) r = add_mod(r, u2d(acc[o]), m);
-        mj.out[0][o] = d2u(r);
-    } else {
-        if (acc) r = add_mod(r, u2d(mj.out[z0][o]), m);  // accumulate into the job's own output
-        mj.out[z0][o] = d2u(r);
-    }
+    if (acc) r = add_mod(r, u2d(groups ? acc[z0 * acc_stride + o] : mj.out[z0][o]), m);
+    mj.out[z0][o] = d2u(r);
 }
 
-hipError_t launch_moddown_multi(const nj_ctx *c, int level, const MdJobs &mj, int n_jobs, int sum,
-                                const uint64_t *u_base, const uint64_t *conv_base, const uint64_t *acc, hipStream_t s)
+hipError_t launch_moddown_multi(const nj_ctx *c, int level, const MdJobs &mj, int n_jobs, int groups,
+                                const uint64_t *u_base, const uint64_t *conv_base, const uint64_t *acc, hipStream_t s,
+                                size_t acc_stride)
 {
-    dim3 grid((c->N + kBT - 1) / kBT, level + 1, sum ? 2 : 2 * n_jobs);
-    const double bytes = 8.0 * c->N * (level + 1) * (n_jobs * 5.0 + (sum ? 2.0 : 2.0 * n_jobs) + (acc ? 2.0 : 0.0));
-    return launch(c, PROF_OTHER, bytes, k_moddown_multi, grid, dim3(kBT), s, mj, n_jobs, sum, u_base, conv_base, acc,
-                  level, level + 1 + c->alpha, c->d_pinv, c->d_info, c->log_n);
+    if (groups < 0 || groups > n_jobs) return hipErrorInvalidValue;
+    const int n = groups ? groups : n_jobs;
+    dim3 grid((c->N + kBT - 1) / kBT, level + 1, 2 * n);
+    const double bytes = 8.0 * c->N * (level + 1) * (n_jobs * 5.0 + 2.0 * n + (acc ? 2.0 * n : 0.0));
+    return launch(c, PROF_OTHER, bytes, k_moddown_multi, grid, dim3(kBT), s, mj, n_jobs, groups, u_base, conv_base, acc,
+                  acc_stride, level, level + 1 + c->alpha, c->d_pinv, c->d_info, c->log_n);
 }
 
 // Key inner products of many ciphertexts with ONE key (batched execution): each key
@@ -616,14 +617,14 @@ hipError_t launch_automorph_multi(const nj_ctx *c, const AutoJobs &aj, int n_job
 }
 
 hipError_t launch_bsgs_mac(const nj_ctx *c, int level, const MacPlan &mp, const uint64_t *diag, uint64_t *inner,
-                           int n_diag, hipStream_t s, int accumulate)
+                           int n_diag, hipStream_t s, int accumulate, int blocks, size_t dblock, size_t iblock)
 {
     if (mp.nb < 1 || mp.nb > NJ_MAX_BABY || mp.ng < 0 || mp.ng > NJ_MAX_GIANT) return hipErrorInvalidValue;
-    dim3 grid((c->N + kBT - 1) / kBT, level + 1);
-    const double bytes = 8.0 * c->N * (level + 1) * (2.0 * mp.nb + n_diag + (2.0 + 2 * accumulate) * mp.ng);
+    dim3 grid((c->N + kBT - 1) / kBT, level + 1, blocks);
+    const double bytes = 8.0 * c->N * (level + 1) * blocks * (2.0 * mp.nb + n_diag + (2.0 + 2 * accumulate) * mp.ng);
 #define NJ_MAC(NB)                                                                                                 \
-    return launch(c, PROF_PMAC, bytes, k_bsgs_mac<NB>, grid, dim3(kBT), s, mp, diag, inner, level, accumulate, \
-                  c->d_info, c->log_n)
+    return launch(c, PROF_PMAC, bytes, k_bsgs_mac<NB>, grid, dim3(kBT), s, mp, diag, inner, dblock, iblock, \
+                  level, accumulate, c->d_info, c->log_n)
     if (mp.nb <= 4) NJ_MAC(4);
     if (mp.nb <= 8) NJ_MAC(8);
     NJ_MAC(16);
