@@ -28,14 +28,14 @@ const uint64_t *key_of(const nj_ctx *c, uint32_t g)
     return nullptr;
 }
 
-// N >= 8192 with at most 4 digits: ModUp stops after the column pass and the key inner
-// product runs the extended digits' tile pass itself (jobs with g = 1)
-bool fuse_ip(const nj_ctx *c, int l) { return c->N >= 8192 && c->alpha <= 8 && n_digits(c, l) <= 4; }
+// N >= 4096 with at most 4 digits: ModUp stops after the column pass (N = 4096: before the
+// conversion) and the key inner product runs the extended digits' tile pass itself
+bool fuse_ip(const nj_ctx *c, int l) { return c->N >= 4096 && c->alpha <= 8 && n_digits(c, l) <= 4; }
 
 nj_status ks_fused(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj, int sum, const uint64_t *acc,
                    MultiBufs &M, hipStream_t s, const MdConj *conj)
 {
-    NJ_HIP(launch_ntt_ip(c, l, kj, K, M.u, 0, 0, s, M.pc));
+    NJ_HIP(launch_ntt_ip(c, l, kj, K, M.u, 0, 0, s, M.pc, 0, M.part));
     return ks_down(c, l, K, mj, sum, acc, M, s, true, nullptr, conj);
 }
 
@@ -92,10 +92,17 @@ nj_status apply_galois(nj_ctx *c, int l, const uint64_t *in, uint32_t g, uint64_
 int galois_of_rot(const nj_ctx *c, long long r) { return (int)nj_galois_elt(c, (int)(((r % (c->N / 2)) + c->N / 2) % (c->N / 2))); }
 
 
+// limbs of a key switch's unsummed products (N = 4096, at most 4 digits: launch_ntt_ip); also
+// counted where more digits leave them unused, so that a level's buffers hold any lower one's
+static size_t ip_parts(const nj_ctx *c, int l)
+{
+    return c->N == 4096 && c->alpha <= 8 ? 2 * (size_t)std::min(n_digits(c, l), 4) * (l + 1 + c->alpha) : 0;
+}
+
 size_t multi_words(const nj_ctx *c, int l, int K)
 {
     const size_t N = c->N, ne = l + 1 + c->alpha, nd = n_digits(c, l);
-    return N * K * (2 * (l + 1) + nd * ne + 2 * ne + 2 * c->alpha + 2 * (l + 1));
+    return N * K * (2 * (l + 1) + nd * ne + 2 * ne + 2 * c->alpha + 2 * (l + 1) + ip_parts(c, l));
 }
 
 bool multi_bufs(const nj_ctx *c, int l, int K, Arena &A, MultiBufs &M)
@@ -107,7 +114,9 @@ bool multi_bufs(const nj_ctx *c, int l, int K, Arena &A, MultiBufs &M)
     M.u = A.take(N * K * 2 * ne);
     M.pc = A.take(N * K * 2 * c->alpha);
     M.conv = A.take(N * K * 2 * (l + 1));
-    return M.conv != nullptr;
+    const size_t parts = ip_parts(c, l);
+    M.part = parts ? A.take(N * K * parts) : nullptr;
+    return M.conv != nullptr && (M.part || !parts);
 }
 
 // ModUp of K polynomials stored at d + z dstride N (evaluation form; dstride in limbs,
@@ -118,25 +127,31 @@ nj_status modup_multi(nj_ctx *c, int l, int K, const uint64_t *d, MultiBufs &M, 
     const auto &tabs = drop ? c->modup_drop[l] : c->modup[l];
     const int N = c->N, ne = l + 1 + c->alpha, nd = n_digits(c, l);
     // N >= 8192: the conversion finishes its inputs' inverse transform (their factors ride on
-    // it) and starts its outputs' forward one
-    const bool fused = N >= 8192 && c->alpha <= 8;
-    if (gt && !fused) return fail(NJ_EUNSUPPORTED, "ModUp through an automorphism needs N >= 8192");
+    // it) and starts its outputs' forward one; N = 4096: it runs the outputs' whole transform
+    const bool fused = N >= 4096 && c->alpha <= 8;
+    if (gt && !fused) return fail(NJ_EUNSUPPORTED, "ModUp through an automorphism needs N >= 4096");
+    if (dstride < 0) dstride = l + 1;
+    // one tile (N = 4096): the key inner product converts, from ext + z dnum ne N
+    const bool conv_later = fused && !tiles && N == 4096;
+    const int cs = conv_later ? nd * ne : l + 1;
+    if (conv_later && drop) return fail(NJ_EUNSUPPORTED, "ModUp of some targets only needs N >= 8192");
     auto intt = [&](const LimbTab &t) {
-        return fused ? launch_intt_tiles(c, M.coef, d, t, s, gt, l + 1)
+        return fused ? launch_intt_tiles(c, conv_later ? M.ext : M.coef, d, t, s, gt, cs,
+                                         N == 4096 ? c->d_upscale[l] : nullptr)
                      : launch_ntt(c, M.coef, t, true, s, d);
     };
-    if (dstride < 0) dstride = l + 1;
     LimbTab lt;
     lt.n = 0;
     for (int z = 0; z < K; z++)
         for (int i = 0; i <= l; i++) {
-            lt.pidx[lt.n] = i, lt.off[lt.n] = z * (l + 1) + i, lt.soff[lt.n] = (zoff ? zoff[z] : z * dstride) + i;
+            lt.pidx[lt.n] = i, lt.off[lt.n] = z * cs + i, lt.soff[lt.n] = (zoff ? zoff[z] : z * dstride) + i;
             if (++lt.n == NJ_MAX_LIMBS) {
                 NJ_HIP(intt(lt));
                 lt.n = 0;
             }
         }
     NJ_HIP(intt(lt));
+    if (conv_later) return NJ_OK;
     for (int j0 = 0; j0 < nd; j0 += 4) {
         BconvShared sh;
         sh.nd = std::min(4, nd - j0);
@@ -152,7 +167,7 @@ nj_status modup_multi(nj_ctx *c, int l, int K, const uint64_t *d, MultiBufs &M, 
         for (int z = 0; z < K; z++) jp.in[z] = M.coef + (size_t)z * (l + 1) * N, jp.out[z] = M.ext + (size_t)z * nd * ne * N;
         NJ_HIP(fused ? launch_bconv_col(c, sh, jp, K, c->d_upscale[l], s) : launch_bconv_multi(c, sh, jp, K, s));
     }
-    if (fused && !tiles) return NJ_OK;  // the key inner product runs the tile pass
+    if (fused && (!tiles || N == 4096)) return NJ_OK;  // the key inner product runs the tile pass, or it is done
     auto ntt = [&](const LimbTab &t) { return fused ? launch_ntt_tiles(c, M.ext, t, s) : launch_ntt(c, M.ext, t, false, s); };
     lt.n = 0;
     for (int z = 0; z < K; z++)
@@ -195,12 +210,12 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
                   size_t acc_stride)
 {
     const int N = c->N, ne = l + 1 + c->alpha, al = c->alpha;
-    const bool fused = N >= 8192 && al <= 8;  // as in modup_multi
-    if (p_tiled && !fused) return fail(NJ_EUNSUPPORTED, "ModDown: pre-transformed special-prime rows need N >= 8192");
+    const bool fused = N >= 4096 && al <= 8;  // as in modup_multi
+    if (p_tiled && !fused) return fail(NJ_EUNSUPPORTED, "ModDown: pre-transformed special-prime rows need N >= 4096");
     const bool one = !sum && N >= 4096 && K == 1;  // the fused combine of one job
     if (drop && (sum || !fused || last_out || conj || l < 2))
         return fail(NJ_EUNSUPPORTED, "ModDown: limbs 0 and l only with the fused combine, no hand-off, level >= 2");
-    if (last_out && !(one && fused)) return fail(NJ_EUNSUPPORTED, "ModDown: the rescale hand-off needs one job, N >= 8192");
+    if (last_out && !(one && fused)) return fail(NJ_EUNSUPPORTED, "ModDown: the rescale hand-off needs one job, N >= 4096");
     if (ipq && (sum || acc || last_out || conj || drop || !fused || !fuse_ip(c, l)))
         return fail(NJ_EUNSUPPORTED, "ModDown: inner products in the combine need the plain fused combine");
     if (conj && !one) return fail(NJ_EUNSUPPORTED, "ModDown: the fused split needs one job, N >= 4096");
@@ -209,7 +224,8 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
     if (acc && !sum && K == 1 && acc != mj.out[0] && !one)
         NJ_HIP(hipMemcpyAsync(mj.out[0], acc, 2 * (size_t)(l + 1) * N * 8, hipMemcpyDeviceToDevice, s));
     auto intt = [&](const LimbTab &t) {
-        return fused ? launch_intt_tiles(c, M.pc, M.u, t, s) : launch_ntt(c, M.pc, t, true, s, M.u);
+        return fused ? launch_intt_tiles(c, M.pc, M.u, t, s, nullptr, 0, N == 4096 ? c->d_downscale : nullptr)
+                     : launch_ntt(c, M.pc, t, true, s, M.u);
     };
     LimbTab lp;
     lp.n = 0;
@@ -232,13 +248,15 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
     for (int o = 0; o < bt.n_out; o++) sh.out_pidx[0][o] = bt.out_pidx[o], sh.out_off[0][o] = bt.out_limb[o];
     BconvPtrs jp;
     for (int h = 0; h < 2 * K; h++) jp.in[h] = M.pc + (size_t)h * al * N, jp.out[h] = M.conv + (size_t)h * (l + 1) * N;
-    NJ_HIP(fused ? launch_bconv_col(c, sh, jp, 2 * K, c->d_downscale, s) : launch_bconv_multi(c, sh, jp, 2 * K, s));
+    const bool conv_in = fused && !sum && N == 4096;  // the combine's tile pass converts
+    if (!conv_in)
+        NJ_HIP(fused ? launch_bconv_col(c, sh, jp, 2 * K, c->d_downscale, s) : launch_bconv_multi(c, sh, jp, 2 * K, s));
     if (ipq) {
-        NJ_HIP(launch_key_ip_moddown(c, l, K, M.conv, *ipq, mj, s));
+        NJ_HIP(launch_key_ip_moddown(c, l, K, conv_in ? M.pc : M.conv, *ipq, mj, s));
         return NJ_OK;
     }
     if (!sum && N >= 4096) {  // the combine runs inside the transform's tile pass
-        NJ_HIP(launch_ntt_moddown(c, l, K, M.conv, M.u, mj, acc != nullptr, fused, s, acc0, last_out, conj,
+        NJ_HIP(launch_ntt_moddown(c, l, K, conv_in ? M.pc : M.conv, M.u, mj, acc != nullptr, fused, s, acc0, last_out, conj,
                                   drop ? l - 1 : 0));
         return NJ_OK;
     }
@@ -249,11 +267,11 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
         for (int i = 0; i <= l; i++) {
             lq.pidx[lq.n] = i, lq.off[lq.n] = h * (l + 1) + i;
             if (++lq.n == NJ_MAX_LIMBS) {
-                NJ_HIP(ntt(lq));
+                if (!fused || N > 4096) NJ_HIP(ntt(lq));
                 lq.n = 0;
             }
         }
-    NJ_HIP(ntt(lq));
+    if (!fused || N > 4096) NJ_HIP(ntt(lq));
     NJ_HIP(launch_moddown_multi(c, l, mj, K, sum, M.u, M.conv, acc, s, acc_stride));
     return NJ_OK;
 }
@@ -387,7 +405,7 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
         // drop: the output goes on to a rescale and a drop to level 0, which read only its
         // Q limbs 0 and l; the giant steps' digits, inner products, c0 sums and ModDown
         // are computed for those limbs (and the special primes) alone
-        const bool dr = drop && fuse_ip(c, l) && l >= 2 && !last_out;
+        const bool dr = drop && fuse_ip(c, l) && N > 4096 && l >= 2 && !last_out;
         const int skip = dr ? l - 1 : 0;
         for (size_t c0 = 0; c0 < gl.size(); c0 += kGiantChunk) {
             const int K = (int)std::min((size_t)kGiantChunk, gl.size() - c0);
@@ -413,7 +431,7 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
                 if ((st = modup_multi(c, l, K, M.d, M, s, -1, !f))) return st;
             }
             const bool last = c0 + K == gl.size();  // its special-prime rows go on to ModDown's inverse transform
-            NJ_HIP(f ? launch_ntt_ip(c, l, kj, K, usum, 1, c0 ? 1 : 0, s, last ? M.pc : nullptr, skip)
+            NJ_HIP(f ? launch_ntt_ip(c, l, kj, K, usum, 1, c0 ? 1 : 0, s, last ? M.pc : nullptr, skip, M.part)
                      : launch_key_ip_sum(c, l, kj, K, usum, c0 ? 1 : 0, s));
             NJ_HIP(launch_automorph_acc(c, ac, K, l + 1, c0sum, 0, c0 ? 3 : 2, s, skip));
         }
@@ -421,7 +439,7 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
         M1.u = usum;
         MdJobs mj;
         mj.add[0] = c0sum, mj.g_add[0] = 1, mj.out[0] = out;
-        const bool hand = last_out && N >= 8192 && c->alpha <= 8;  // the rescale's first pass rides along
+        const bool hand = last_out && N >= 4096 && c->alpha <= 8;  // the rescale's first pass rides along
         if (hand && last_done) *last_done = true;
         return ks_down(c, l, 1, mj, 0, acc, M1, s, fuse_ip(c, l), hand ? last_out : nullptr, nullptr, dr);
     }
@@ -539,7 +557,7 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
         usum = A.take(N * K * 2 * ne), c0sum = A.take(N * K * (l + 1));
         if (!c0sum) return fail(NJ_ENOMEM, "scratch too small");
     }
-    // fused (N >= 8192): tau_ge rides on ModUp's inverse transform and on the own-limb
+    // fused (N >= 4096): tau_ge rides on ModUp's inverse transform and on the own-limb
     // reads, and the key inner product (one key, one job per ciphertext) runs the digits'
     // tile pass; the last giant step's special-prime rows go on to ModDown's inverse
     // transform there
@@ -573,7 +591,7 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
         }
         if (lt.lazy) {  // per ciphertext: inner products and rotated c0 parts summed
             if (f)
-                NJ_HIP(launch_ntt_ip(c, l, kj, K, usum, 0, first ? 0 : 1, s, g == g_last ? M.pc : nullptr));
+                NJ_HIP(launch_ntt_ip(c, l, kj, K, usum, 0, first ? 0 : 1, s, g == g_last ? M.pc : nullptr, 0, M.part));
             else
                 NJ_HIP(launch_key_ip_shared(c, l, kj, K, key_of(c, ge), usum, s, first ? 0 : 1));
             NJ_HIP(launch_automorph_acc(c, ac, K, l + 1, c0sum, plen, first ? 0 : 1, s));
@@ -800,7 +818,7 @@ nj_status block_bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uin
                 }
             for (int ob = 0; ob < nB; ob++) mj.out[ob] = out + (o0 + ob) * clen;
             if ((st = modup_multi(c, l, J, inner_all + plen, M, s, -1, false, &gt, zoff))) return st;
-            NJ_HIP(launch_ntt_ip(c, l, kj, J, M.u, 0, 0, s, M.pc));
+            NJ_HIP(launch_ntt_ip(c, l, kj, J, M.u, 0, 0, s, M.pc, 0, M.part));
             if ((st = ks_down(c, l, J, mj, nB, acc ? acc + (size_t)o0 * ng * clen : nullptr, M, s, true, nullptr, nullptr,
                               false, nullptr, ng * clen)))
                 return st;
@@ -844,14 +862,14 @@ nj_status rescale(nj_ctx *c, int l, const uint64_t *in, uint64_t *out, Arena A, 
 {
     const size_t N = c->N;
     if (n_out < 0) n_out = l;
-    if (last_pre && (N < 8192 || n_polys != 2)) return fail(NJ_EUNSUPPORTED, "rescale: hand-off needs N >= 8192");
-    if (N >= 8192) {  // the lifted limbs stay in out, transformed and combined in place
+    if (last_pre && (N < 4096 || n_polys != 2)) return fail(NJ_EUNSUPPORTED, "rescale: hand-off needs N >= 4096");
+    if (N >= 4096) {  // the lifted limbs stay in out, transformed and combined in place
         uint64_t *last = last_pre ? last_pre : A.take(n_polys * N);
         if (!last) return fail(NJ_ENOMEM, "scratch too small");
         NJ_HIP(launch_rescale_fused(c, l, in, out, n_out, last, out, s, n_polys, last_pre != nullptr));
         return NJ_OK;
     }
-    if (n_polys != 2) return fail(NJ_EUNSUPPORTED, "rescale: packed ciphertexts need N >= 8192");
+    if (n_polys != 2) return fail(NJ_EUNSUPPORTED, "rescale: packed ciphertexts need N >= 4096");
     uint64_t *last = A.take(2 * N), *lifted = A.take(N * l);
     if (!lifted) return fail(NJ_ENOMEM, "scratch too small");
     for (int p = 0; p < 2; p++)
@@ -872,10 +890,10 @@ nj_status rescale(nj_ctx *c, int l, const uint64_t *in, uint64_t *out, Arena A, 
 
 nj_status rescale_batch(nj_ctx *c, int l, int K, const uint64_t *in, uint64_t *out, Arena A, hipStream_t s)
 {
-    if (c->N >= 8192) return rescale(c, l, in, out, A, s, -1, 2 * K);
+    const int per = c->N >= 4096 ? NJ_MAX_LIMBS / 2 : 1;
     const size_t cl = 2 * (size_t)c->N * (l + 1), cl1 = 2 * (size_t)c->N * l;
-    for (int z = 0; z < K; z++) {
-        nj_status st = rescale(c, l, in + z * cl, out + z * cl1, A, s);
+    for (int z = 0; z < K; z += per) {
+        nj_status st = rescale(c, l, in + z * cl, out + z * cl1, A, s, -1, 2 * std::min(per, K - z));
         if (st) return st;
     }
     return NJ_OK;
@@ -894,7 +912,7 @@ nj_status modraise(nj_ctx *c, const uint64_t *in, int top, uint64_t *out, Arena 
     LimbTab lo;
     lo.n = 2 * (top + 1);
     for (int k = 0; k < lo.n; k++) lo.pidx[k] = k % (top + 1), lo.off[k] = k;
-    if (N >= 8192) {  // inverse tile pass, lift fused with both column passes, forward tile pass
+    if (N >= 4096) {  // inverse tile pass, lift fused with both column passes, forward tile pass
         NJ_HIP(launch_intt_tiles(c, tmp, in, lt, s));
         NJ_HIP(launch_lift_col(c, tmp, 0, 2, top + 1, out, s));
         NJ_HIP(launch_ntt_tiles(c, out, lo, s));
@@ -999,13 +1017,13 @@ nj_status cts_batch(nj_ctx *c, const nj_plan *p, const uint64_t *in, int n, uint
 }
 
 // One BSGS transform then a rescale: x -> y (scratch) -> out (level l-1).  When the
-// transform's last step is a one-job ModDown (lazy giant steps, N >= 8192) it also
+// transform's last step is a one-job ModDown (lazy giant steps, N >= 4096) it also
 // runs the first pass of the rescale's inverse transform.
 nj_status bsgs_rescale(nj_ctx *c, const nj_lt_t &lt, const uint64_t *x, uint64_t *y, uint64_t *out, Arena A,
                        hipStream_t s)
 {
-    uint64_t *last = c->N >= 8192 ? A.take(2 * (size_t)c->N) : nullptr;
-    if (c->N >= 8192 && !last) return fail(NJ_ENOMEM, "scratch too small");
+    uint64_t *last = c->N >= 4096 ? A.take(2 * (size_t)c->N) : nullptr;
+    if (c->N >= 4096 && !last) return fail(NJ_ENOMEM, "scratch too small");
     bool done = false;
     nj_status st = bsgs_apply(c, lt, x, y, lt.hoist ? 1 : 0, A, s, last, &done);
     if (st) return st;

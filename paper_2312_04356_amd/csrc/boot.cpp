@@ -42,7 +42,7 @@ struct BranchMem {
 
 // Ciphertext buffers of one evaluation: fixed-size slots (K level-lmax ciphertexts
 // each) from an arena with a free list; the key-switch scratch is a separate arena.
-// Every operation applies to the K packed ciphertexts at once (K > 1 needs N >= 8192).
+// Every operation applies to the K packed ciphertexts at once (K > 1 needs N >= 4096).
 // Independent products can run as branches: an Ev on a worker stream with its own slots
 // and scratch, forked after the values it reads are enqueued and joined before its
 // result is used, so every value is computed by the same kernels as in one stream.
@@ -185,9 +185,9 @@ class Ev {
         release(t);
         return o;
     }
-    // Several rescaled terms summed in one go (N >= 8192, see launch_rescale_sum): the words
+    // Several rescaled terms summed in one go (N >= 4096, see launch_rescale_sum): the words
     // are those of rescaling each w_j (k_j x_j) by itself and adding the results.
-    bool sums() const { return N >= 8192; }
+    bool sums() const { return N >= 4096; }
     struct Term {
         const Cx *x;
         long long k;
@@ -413,7 +413,7 @@ size_t eval_mod_words(const nj_ctx *c, int l0, int K = 1)
 }
 
 // ModEval of K ciphertexts in[z] (level l0, scale s0) evaluated together (packed; K > 1
-// needs N >= 8192): out[z] at level l0 - 11
+// needs N >= 4096): out[z] at level l0 - 11
 nj_status eval_mod(nj_ctx *c, int K, const uint64_t *const *in, int l0, double s0, double Kr, const double *cf,
                    uint64_t *const *out, double *out_scale, Arena A, hipStream_t s)
 {
@@ -569,13 +569,13 @@ nj_status nj_eval_mod(nj_ctx *c, const nj_ct *in, int K, int r, const double *co
 
 }  // extern "C"
 
-// ModEval of Re and Im together (one packed evaluation, N >= 8192; else one after the
+// ModEval of Re and Im together (one packed evaluation, N >= 4096; else one after the
 // other): the same results as two nj_eval_mod calls
 nj_status nj::ex::eval_mod_pair(nj_ctx *c, const nj_ct *re, const nj_ct *im, int K, int r, const double *coeffs,
                                 int n_coeffs, nj_ct *out_re, nj_ct *out_im, void *stream)
 {
     nj_status st;
-    if (c->N < 8192) {
+    if (c->N < 4096) {
         if ((st = nj_eval_mod(c, re, K, r, coeffs, n_coeffs, out_re, stream))) return st;
         return nj_eval_mod(c, im, K, r, coeffs, n_coeffs, out_im, stream);
     }

@@ -28,7 +28,7 @@ struct Arena {
 // products [K][2][l+1+alpha], special-prime limbs [K][2][alpha], converted limbs
 // [K][2][l+1] (all x N words).
 struct MultiBufs {
-    uint64_t *d, *coef, *ext, *u, *pc, *conv;
+    uint64_t *d, *coef, *ext, *u, *pc, *conv, *part;
 };
 
 constexpr int kGiantChunk = 8;  // giant-step key switches per batch in a single-ciphertext transform
@@ -51,9 +51,9 @@ nj_status apply_galois(nj_ctx *c, int l, const uint64_t *in, uint32_t g, uint64_
 size_t multi_words(const nj_ctx *c, int l, int K);
 bool multi_bufs(const nj_ctx *c, int l, int K, Arena &A, MultiBufs &M);
 // ModUp of K polynomials at d + z dstride N (dstride in limbs, l+1 when packed)
-// (tiles = false: at N >= 8192 the converted limbs are left after their column pass,
+// (tiles = false: at N >= 4096 the converted limbs are left after their column pass,
 // for the fused key inner product)
-// (gt: job z's polynomial is read through X -> X^g[z], N >= 8192; zoff: job z's
+// (gt: job z's polynomial is read through X -> X^g[z], N >= 4096; zoff: job z's
 // polynomial at d + zoff[z] N instead of d + z dstride N)
 // (drop: only the targets a rescale followed by a drop to level 0 needs, Q limbs 0 and l
 // and the special primes)
@@ -61,12 +61,12 @@ nj_status modup_multi(nj_ctx *c, int l, int K, const uint64_t *d, MultiBufs &M, 
                       bool tiles = true, const GalTab *gt = nullptr, const int *zoff = nullptr, bool drop = false);
 // whether ModUp leaves the tile pass to the key inner product (launch_ntt_ip)
 bool fuse_ip(const nj_ctx *c, int l);
-// ModEval of Re and Im evaluated together (packed) when N >= 8192
+// ModEval of Re and Im evaluated together (packed) when N >= 4096
 nj_status eval_mod_pair(nj_ctx *c, const nj_ct *re, const nj_ct *im, int K, int r, const double *coeffs,
                         int n_coeffs, nj_ct *out_re, nj_ct *out_im, void *stream);
 // one key switch of tau_g(d): out = (ModDown_0 + add read through X -> X^g_add, ModDown_1)
 // (conj: the output is replaced by the real/imaginary split with add's ciphertext, see
-// MdConj; N >= 8192)
+// MdConj; N >= 4096)
 nj_status ks_one(nj_ctx *c, int l, const uint64_t *d, uint32_t g, const uint64_t *key, const uint64_t *add,
                  uint32_t g_add, uint64_t *out, MultiBufs &M, hipStream_t s, const MdConj *conj = nullptr);
 // as ks_multi, on digits of tau_g(d) that modup_multi left column-passed (tiles =
@@ -78,9 +78,9 @@ nj_status ks_multi(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
                    MultiBufs &M, hipStream_t s);
 // ModDown of K jobs' inner products (M.u) and the combine into their outputs
 // (p_tiled: the inner products already left their special-prime rows in M.pc after the
-// first 12 stages of the inverse transform; N >= 8192.  acc: the previous value added
+// first 12 stages of the inverse transform; N >= 4096.  acc: the previous value added
 // (sum = 0: for K = 1 it may be any ciphertext, else it must be the outputs).
-// last_out, one job, N >= 8192: the output's last limb also leaves through the first
+// last_out, one job, N >= 4096: the output's last limb also leaves through the first
 // 12 stages of its inverse transform into last_out [2][N], for rescale(last_pre))
 // sum > 0: mj.out[g], g < sum, = acc + g acc_stride + the sum of the jobs g, g + sum, ..
 // drop: only output limbs 0 and l (the fused one-job combine, no last_out or conj, l >= 2;
@@ -119,10 +119,10 @@ nj_status block_bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uin
 
 // rescale [2][l+1] -> [2][l]; n_out < l keeps only the first n_out limbs of the result
 // (rescale followed by a level drop, computing only the kept limbs)
-// n_polys > 2 (several ciphertexts packed at level l) needs N >= 8192
+// n_polys > 2 (several ciphertexts packed at level l) needs N >= 4096
 nj_status rescale(nj_ctx *c, int l, const uint64_t *in, uint64_t *out, Arena A, hipStream_t s, int n_out = -1,
                   int n_polys = 2, uint64_t *last_pre = nullptr);
-// rescale of K packed ciphertexts [K][2][l+1] -> [K][2][l] (one set of launches when N >= 8192)
+// rescale of K packed ciphertexts [K][2][l+1] -> [K][2][l] (one set of launches when N >= 4096)
 nj_status rescale_batch(nj_ctx *c, int l, int K, const uint64_t *in, uint64_t *out, Arena A, hipStream_t s);
 nj_status modraise(nj_ctx *c, const uint64_t *in, int top, uint64_t *out, Arena A, hipStream_t s);
 nj_status conj_split(nj_ctx *c, int l, const uint64_t *x, uint64_t *re, uint64_t *im, Arena A, hipStream_t s);

@@ -358,14 +358,14 @@ namespace nj {
 hipError_t launch_ntt(const nj_ctx *c, uint64_t *data, const LimbTab &lt, bool inverse, hipStream_t s,
                       const uint64_t *src = nullptr);
 // inverse tile pass alone, for launch_bconv_col (gt: limb b of job off[b] / L1 is read from
-// src through X -> X^g[job])
+// src through X -> X^g[job]; scale, N = 4096: canonical words times the prime's factor)
 hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt, hipStream_t s,
-                             const GalTab *gt = nullptr, int L1 = 0);
+                             const GalTab *gt = nullptr, int L1 = 0, const double *scale = nullptr);
 // c0 + c1 s in coefficient form, out [level + 1][N] (N >= 4096)
 hipError_t launch_decrypt_fast(const nj_ctx *c, const uint64_t *ct, int level, uint64_t *out, hipStream_t s);
 hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, uint64_t *out, int n_out,
                                 uint64_t *last, uint64_t *lifted, hipStream_t s, int n_polys = 2, bool last_tiled = false);
-// sum of the rescaled terms of rt from level l (N >= 8192, at most 8 terms, sum |w_j| <= 8):
+// sum of the rescaled terms of rt from level l (N >= 4096, at most 8 terms, sum |w_j| <= 8):
 // P polynomials into out [P][l][N]; last: scratch [terms][P][N].  Equal word for word to
 // multiplying, rescaling and adding the terms one by one
 hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uint64_t *out, uint64_t *last,
@@ -373,22 +373,25 @@ hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uin
 hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, hipStream_t s);
 hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs,
                             const double *scale, hipStream_t s);
-// key inner products fused with the extended digits' forward tile pass (N >= 8192,
+// key inner products fused with the extended digits' forward tile pass (N >= 4096,
 // 1..4 digits, every g = 1): per job u_base + z 2 ne N, or (sum) one output summed over
 // the jobs; accumulate adds to the output's previous value
 hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u, int sum,
-                         int accumulate, hipStream_t s, uint64_t *pout = nullptr, int skip = 0);
-// (pout given: the special-prime rows skip u and leave through the first 12 stages of
-// ModDown's inverse transform, job z's halves at rows (2 z + p) alpha + a of pout;
-// skip > 0: Q limbs 1..skip are not computed, skip = l - 1 keeping Q limbs 0 and l)
+                         int accumulate, hipStream_t s, uint64_t *pout = nullptr, int skip = 0,
+                         uint64_t *part = nullptr);
+// (part: N = 4096, room for the unsummed products, [n_jobs][digits][2][ne][N]; pout given: the
+// special-prime rows skip u and leave through the first 12 stages of ModDown's inverse
+// transform, job z's halves at rows (2 z + p) alpha + a of pout (N = 4096: canonical and
+// scaled); skip > 0, N >= 8192: Q limbs 1..skip are not computed, skip = l - 1 keeping Q
+// limbs 0 and l)
 // special-prime rows of n_jobs key inner products whose digits are extended and in
 // evaluation form (KeyJobs as for launch_key_ip_multi): the products pass through the
 // first 12 stages of ModDown's inverse transform into pout, job z's halves at rows
-// (2 z + p) alpha + a (N >= 8192, 1..4 digits, alpha <= 8)
+// (2 z + p) alpha + a (N >= 4096, 1..4 digits, alpha <= 8)
 hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *pout,
                                hipStream_t s);
 // centred lift of n_polys limbs after their inverse tile pass (prime src_pidx, src + z N)
-// into primes 0..n_out-1 with the column pass applied, out [n_polys][n_out][N] (N >= 8192)
+// into primes 0..n_out-1 with the column pass applied, out [n_polys][n_out][N] (N >= 4096)
 hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, int n_polys, int n_out, uint64_t *out,
                            hipStream_t s);
 // (acc0: job 0's previous value read from there instead of its output; last_out, one
@@ -397,7 +400,7 @@ hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, i
 // skip > 0 (with cols_done, no last_out or conj): only output limbs 0 and 1 + skip ..
 // the plain combine of launch_ntt_moddown (no accumulation, converted limbs column-passed)
 // with the jobs' Q-limb key inner products computed inside it from extended
-// evaluation-form digits (KeyJobs as for launch_key_ip_multi; N >= 8192, 1..4 digits)
+// evaluation-form digits (KeyJobs as for launch_key_ip_multi; N >= 4096, 1..4 digits)
 hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64_t *conv, const KeyJobs &kj,
                                  const MdJobs &mj, hipStream_t s);
 hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv, const uint64_t *u_base,

@@ -1,6 +1,6 @@
 // Hybrid key switching and BSGS accumulation kernels (gfx950).  Every key switch runs
 // as a batch of jobs (one job being the plain case): ModUp's basis conversion
-// (k_bconv_multi; at N >= 8192 the fused conversion + column pass in ntt.hip), key inner
+// (k_bconv_multi; at N >= 4096 the fused conversion + column pass in ntt.hip), key inner
 // products (k_key_ip_multi / _sum / _shared / _mixed: one job per key, a sum over jobs,
 // one key for many ciphertexts, one key for jobs at mixed levels), the ModDown combine
 // (k_moddown_multi, or fused into the tile pass in ntt.hip) and the automorphisms.

@@ -222,11 +222,12 @@ __device__ __forceinline__ void tile_inverse(double v[16], double *s, int tid, i
     gs_round<false>(v, 2048, 0, tile, logN1, const_tab(W), N, m);
 }
 
-// rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs).  With a column pass
-// beside it (N > 4096) the forward's input and the inverse's output are its FP64 words.
+// rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs).  part: the forward's
+// input and the inverse's output are FP64 words of the pass beside it (a column pass, or a
+// kernel that does its work); else the tile is the whole transform, N = 4096.
 template <bool INV>
-__global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t *src, LimbTab lt, const double *tw,
-                                                  const PrimeInfo *info, int logN)
+__global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t *src, LimbTab lt, int part,
+                                                  const double *tw, const PrimeInfo *info, int logN)
 {
     __shared__ double s[kT + kT / 16];
     const int N = 1 << logN, logN1 = logN - 12;
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t
     const int w0 = wv(tid);
     double v[16];
     if (!INV) {
-        if (logN1 == 0) {
+        if (!part) {
 #pragma unroll
             for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
         } else {
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = u2d(in[w0 + 64 * k]);
         tile_inverse(v, s, tid, tile, logN1, W, N, m);
-        if (logN1 == 0) {
+        if (!part) {
 #pragma unroll
             for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(corr(mul_lazy(v[k], pi.ninv, m), m));
         } else {
@@ -443,6 +444,39 @@ __device__ __forceinline__ void tile_inverse8(double v[8], double *s, int tid, i
     reduce8(v, m);
 }
 
+// Rings of one tile (N = 4096) have no column pass, and their launches are a few blocks each:
+// what bounds them is the chain of launches, so the basis conversion runs inside the kernels
+// that transform its result.  v = words tid + 256 k of sum_a x_a hat[a n_out] mod t, centred: x_a
+// the canonical words of limb a of `in` ([m][N], scaled by launch_intt_tiles), m <= 8.
+template <int W>  // words per thread: tid + (4096 / W) k
+__device__ __forceinline__ void tile_convert(double v[W], const uint64_t *in, int m, const double *hat, int n_out,
+                                             Mod mo, int tid)
+{
+    constexpr int kA = W == 8 ? 4 : 2;  // limbs requested at once
+#pragma unroll
+    for (int k = 0; k < W; k++) v[k] = 0.0;
+#pragma unroll 1
+    for (int a = 0; a < m; a += kA) {
+        uint64_t x[kA][W];
+        double h[kA];
+#pragma unroll
+        for (int i = 0; i < kA; i++) {
+            const int ai = min(a + i, m - 1);
+            h[i] = a + i < m ? const_tab(hat)[ai * n_out] : 0.0;
+#pragma unroll
+            for (int k = 0; k < W; k++) x[i][k] = in[(size_t)ai * kT + tid + kT / W * k];
+        }
+#pragma unroll
+        for (int i = 0; i < kA; i++) {
+            if (a + i >= m) break;
+#pragma unroll
+            for (int k = 0; k < W; k++) v[k] += mul_lazy(u2d(x[i][k]), h[i], mo);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < W; k++) v[k] = reduce_c(v[k], mo);
+}
+
 // Requests the words of step q = z ND + j of a key inner product (job z, digit j) of one
 // tile into LDS (xb, in memory order): the extended digit's tile ([ND][ne][N], as it came out
 // of its column pass), or for the job's own limb the tile that X -> X^g reads (it moves whole
@@ -581,6 +615,146 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint
     }
 }
 
+// Key inner products on the ring of one tile (N = 4096).  One compute unit takes 1.6 us for
+// one tile's transform alone, so every (job, limb, digit) is a block of its own: k_conv_ip
+// converts the digit to its limb (kj.ext[z]: the [l+1][N] words of tau_g(d_z), canonical and
+// scaled; the own limb is d_z[t] read through X -> X^g), transforms it and multiplies it by
+// both key halves, into part [job][digit][2][ne][N] (lazy FP64 words); k_ip_reduce adds the
+// products up, special-prime rows on through ModDown's inverse transform.  grid (jobs, ne, digits).
+// A rotation's key switch is 4 launches this way.  What bounds it is their round trips to memory
+// (about 2 us each from a cold L2, a block alone on its compute unit): 512 threads of 8 words,
+// everything a block reads requested at once.  One rotation at level 7 (4 digits): 29.3 us; 47.8
+// with the general kernels (8 launches), 45 with k_ntt_ip, which works through the digits one
+// after another, 59 with 256 threads of 16 words.  CoeffToSlot with lazy giant steps (28 of them
+// summed): a step 373 us, 525 with the general kernels, 662 with k_ntt_ip.
+struct IpTiles {
+    const double *hat[4];  // digit j's conversion table [m_j][n_out_j]
+};
+__global__ __launch_bounds__(kNT8, 4) void k_conv_ip(KeyJobs kj, IpTiles it, uint64_t *part, int level, int L,
+                                                     int alpha, int nq, const double *tw, const PrimeInfo *info)
+{
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
+    constexpr int logN = 12;
+    const int z = blockIdx.x, t = blockIdx.y, j = blockIdx.z, tid = threadIdx.x, w0 = wv8(tid);
+    const int pidx = t <= level ? t : nq + (t - level - 1);
+    const IpRow r = ip_row(t, level, L, alpha);
+    const double *W = tw + (size_t)pidx * kT;
+    double v[8], tw3[7];
+    const uint64_t *kp = kj.key[z] + ((size_t)j * 2 * r.nk + r.kl) * kT + w0, *kq = kp + r.nk * kT;
+    uint64_t kb[8], ka[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) kb[k] = kp[64 * k], ka[k] = kq[64 * k];
+    const Mod m = info[pidx].m;
+    if (j == r.own) {
+        const uint64_t *d = kj.d[z] + (size_t)t * kT;
+        const uint32_t g = kj.g[z], gb = gal_base(w0, g, logN);
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = u2d(d[gal_at(gb, 64 * k, g, logN)]);
+    } else {
+        const int a0 = j * alpha, mj = min(alpha, level + 1 - a0);
+        load_twiddles8(tws, tw3, W, 0, 0, kT, tid);
+        tile_convert<8>(v, kj.ext[z] + (size_t)a0 * kT, mj, it.hat[j] + (t < a0 ? t : t - mj), level + 1 + alpha - mj,
+                        m, tid);
+        tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = s[pad8(wv8(tid)) + 72 * k];
+    }
+    uint64_t *o = part + (((size_t)z * gridDim.z + j) * 2 * r.ne + t) * kT + w0;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {  // |v| < 2.2 t: within 1.33 t
+        o[64 * k] = d2b(mul_lazy(v[k], u2d(kb[k]), m));
+        o[r.ne * kT + 64 * k] = d2b(mul_lazy(v[k], u2d(ka[k]), m));
+    }
+}
+
+// u_z = (accumulate ? u_z : 0) + the sum of n parts (n = digits, times the jobs where one sum
+// is wanted); with pout the special-prime rows go through their inverse transform to row
+// (2 z + p) alpha + a of pout instead, canonical and scaled.  grid (sums, 2 ne).
+__global__ __launch_bounds__(kNT8, 4) void k_ip_reduce(const uint64_t *part, int n, uint64_t *u_base, int accumulate,
+                                                    int level, int alpha, int nq, const PrimeInfo *info,
+                                                    uint64_t *pout, const double *itw, const double *scale)
+{
+    __shared__ double s[kT + kT / 8];
+    const int ne = level + 1 + alpha, z = blockIdx.x, row = blockIdx.y, p = row >= ne, t = row - p * ne;
+    const int pidx = t <= level ? t : nq + (t - level - 1), tid = threadIdx.x;
+    const size_t o = (size_t)row * kT + wv8(tid), stride = (size_t)2 * ne * kT;
+    const uint64_t *in = part + (size_t)z * n * stride + o;
+    uint64_t *u = u_base + z * stride + o;
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = accumulate ? u2d(u[64 * k]) : 0.0;
+    const Mod m = info[pidx].m;
+#pragma unroll 1
+    for (int i = 0; i < n; i += 4) {  // 4 parts requested at once
+        uint64_t x[4][8];
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int k = 0; k < 8; k++) x[q][k] = in[min(i + q, n - 1) * stride + 64 * k];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            if (i + q >= n) break;
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[k] += b2d(x[q][k]);
+        }
+        reduce8(v, m);  // below t + 4 1.33 t before
+    }
+    if (!pout || t <= level) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) u[64 * k] = d2u(corr(v[k], m));
+        return;
+    }
+    const double sc = scale[pidx];
+    tile_inverse8(v, s, tid, 0, 0, itw + (size_t)pidx * kT, kT, m);
+    uint64_t *out = pout + ((size_t)(2 * z + p) * alpha + (t - level - 1)) * kT + tid;
+#pragma unroll
+    for (int k = 0; k < 8; k++) out[512 * k] = d2u(corr(mul_lazy(v[k], sc, m), m));
+}
+
+// The inverse transform of the ring of one tile, read through X -> X^gt.g[off / L1] when L1 > 0.
+// scale: canonical words times the prime's factor, for tile_convert; else FP64 words without
+// their N^-1, as the tile pass of a larger ring.  grid (limbs).
+__global__ __launch_bounds__(kNT8) void k_intt_tile(uint64_t *data, const uint64_t *src, LimbTab lt, GalTab gt, int L1,
+                                                    const double *scale, const double *itw, const PrimeInfo *info)
+{
+    __shared__ double s[kT + kT / 8];
+    constexpr int logN = 12;
+    const int limb = blockIdx.x, pidx = lt.pidx[limb], tid = threadIdx.x, w0 = wv8(tid);
+    const Mod m = info[pidx].m;
+    const uint64_t *in = src ? src + (size_t)lt.soff[limb] * kT : data + (size_t)lt.off[limb] * kT;
+    const uint32_t g = L1 ? gt.g[lt.off[limb] / L1] : 1u, gb = gal_base(w0, g, logN);
+    const double f = scale ? scale[pidx] : 0.0;
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = reduce_c(u2d(in[gal_at(gb, 64 * k, g, logN)]), m);
+    tile_inverse8(v, s, tid, 0, 0, itw + (size_t)pidx * kT, kT, m);
+    uint64_t *out = data + (size_t)lt.off[limb] * kT + tid;
+#pragma unroll
+    for (int k = 0; k < 8; k++) out[512 * k] = scale ? d2u(corr(mul_lazy(v[k], f, m), m)) : d2b(v[k]);
+}
+
+// Conversion and transform on the ring of one tile: limb o of digit j of job z into jp.out,
+// evaluation form (inputs canonical and scaled).  grid (jobs nd, targets).
+__global__ __launch_bounds__(kNT8, 4) void k_conv_tile(BconvShared sh, BconvPtrs jp, const double *tw,
+                                                       const PrimeInfo *info)
+{
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
+    const int z = blockIdx.x / sh.nd, j = blockIdx.x % sh.nd, o = blockIdx.y, tid = threadIdx.x;
+    if (o >= sh.n_out[j]) return;
+    const int pidx = sh.out_pidx[j][o];
+    const double *W = tw + (size_t)pidx * kT;
+    const Mod m = info[pidx].m;
+    double v[8], tw3[7];
+    load_twiddles8(tws, tw3, W, 0, 0, kT, tid);
+    tile_convert<8>(v, jp.in[z] + (size_t)sh.in_off0[j] * kT, sh.m[j], sh.hat[j] + o, sh.n_out[j], m, tid);
+    tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
+    uint64_t *out = jp.out[z] + (size_t)sh.out_off[j][o] * kT + wv8(tid);
+#pragma unroll
+    for (int k = 0; k < 8; k++) out[64 * k] = d2u(corr(reduce_c(s[pad8(wv8(tid)) + 72 * k], m), m));
+}
+
 // Decryption's inverse tile pass: limb i of c0 + c1 s (evaluation form, c1 at c0 + half N) enters
 // the transform of that limb (a product and a sum per word on the way in instead of two
 // passes over memory: 20.3 us instead of 39.1 for the whole call at level 20, N = 2^16, whose
@@ -619,7 +793,7 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_dec(uint64_t *data, const uint
 template <int ND>
 __global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, int L, int alpha, int nq,
                                                          const PrimeInfo *info, int logN, uint64_t *pout,
-                                                         const double *itw)
+                                                         const double *itw, const double *scale)
 {
     __shared__ double s[kT + kT / 16];
     const int N = 1 << logN, logN1 = logN - 12;
@@ -648,6 +822,12 @@ __global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, 
     for (int k = 0; k < 16; k++) acc[k] = reduce_c(acc[k], m);
     tile_inverse(acc, s, tid, tile, logN1, itw + (size_t)pidx * N, N, m);
     uint64_t *out = pout + ((size_t)(2 * z + p) * alpha + a) * N + (size_t)tile * kT + tid;
+    if (logN1 == 0) {  // as launch_intt_tiles with its scale
+        const double sc = scale[pidx];
+#pragma unroll
+        for (int k = 0; k < 16; k++) out[256 * k] = d2u(corr(mul_lazy(acc[k], sc, m), m));
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < 16; k++) out[256 * k] = d2b(acc[k]);
 }
@@ -868,7 +1048,7 @@ template <bool CONJ>
 __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, const uint64_t *u_base, MdJobs mj, int acc,
                                                      int level, int ne, const double *pinv, const double *pinvq,
                                                      const double *tw, const PrimeInfo *info, int logN, const uint64_t *acc0,
-                                                     uint64_t *last_out, const double *itw, MdConj cj, int skip)
+                                                     uint64_t *last_out, const double *itw, MdConj cj, int skip, int part)
 {
     __shared__ double s[kT + kT / 16];
     const int N = 1 << logN, logN1 = logN - 12, L1 = level + 1, L1e = L1 - skip;
@@ -879,19 +1059,19 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
     const size_t t0 = (size_t)tile * kT;
     const uint64_t *in = conv + ((size_t)h * L1 + i) * N + t0;
     double v[16];
-    if (logN1 == 0) {
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
-    }
     const int wl = wv(tid);
     const uint64_t *u = u_base + ((size_t)z * 2 * ne + (size_t)p * ne + i) * N + t0 + wl;
     uint64_t uv[16];  // requested before the transform, in which their latency passes: conv +
                       // CoeffToSlot at N = 2^14 750 -> 734 us
 #pragma unroll
     for (int k = 0; k < 16; k++) uv[k] = u[64 * k];
+    if (!part) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
+    }
     tile_forward(v, s, tid, tile, logN1, W, N, m);
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     const uint32_t g = mj.g_add[z];
@@ -997,7 +1177,86 @@ __global__ __launch_bounds__(kNT, ND == 4 ? 2 : 4) void k_key_ip_md(const uint64
     }
 }
 
-// Rescale by q_l and ModRaise, fused into the lifted limbs' transform (N >= 8192).
+// The ModDown combine on the ring of one tile, with its conversion: pc [2 K][alpha][N], the
+// special-prime rows after their inverse transform, canonical and scaled.  ND = 0: as
+// k_ntt_tile_md (u read, all its options); else the key inner products of ND extended
+// evaluation-form digits, as k_key_ip_md.  8 words per thread, everything requested before the
+// transform: a block alone on its compute unit waits for each round trip in full.  grid
+// 2 K (l+1) blocks.
+template <int ND>
+__global__ __launch_bounds__(kNT8, ND ? 2 : 4) void k_md_tile(const uint64_t *pc, const double *hat, const uint64_t *u_base,
+                                                     KeyJobs kj, MdJobs mj, int acc, const uint64_t *acc0, int level,
+                                                     int L, int alpha, const double *pinv, const double *pinvq,
+                                                     const double *tw, const PrimeInfo *info, uint64_t *last_out,
+                                                     const double *itw, MdConj cj)
+{
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
+    constexpr int logN = 12;
+    const int L1 = level + 1, w = blockIdx.x, h = w / L1, i = w - h * L1, z = h >> 1, p = h & 1, tid = threadIdx.x;
+    const int wl = wv8(tid);
+    const IpRow r = ip_row(i, level, L, alpha);
+    const Mod m = info[i].m;
+    const double *W = tw + (size_t)i * kT;
+    double a[8], v[8], tw3[7];
+    load_twiddles8(tws, tw3, W, 0, 0, kT, tid);
+    if (ND == 0) {
+        const uint64_t *u = u_base + ((size_t)h * r.ne + i) * kT + wl;
+#pragma unroll
+        for (int k = 0; k < 8; k++) a[k] = u2d(u[64 * k]);
+    } else {
+        const uint32_t g = kj.g[z], gb = gal_base(wl, g, logN);
+        const uint64_t *key = kj.key[z] + ((size_t)p * r.nk + r.kl) * kT + wl;
+#pragma unroll
+        for (int k = 0; k < 8; k++) a[k] = 0.0;
+#pragma unroll
+        for (int j = 0; j < ND; j++) {
+            const uint64_t *x = j == r.own ? kj.d[z] + (size_t)i * kT : kj.ext[z] + (j * r.ne + i) * kT;
+#pragma unroll
+            for (int k = 0; k < 8; k++)
+                a[k] += mul_lazy(u2d(x[gal_at(gb, 64 * k, g, logN)]), u2d(key[(size_t)j * 2 * r.nk * kT + 64 * k]), m);
+        }
+        reduce8(a, m);
+    }
+    const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
+    uint64_t av[8];
+    if (add) {
+        const uint32_t g = mj.g_add[z], gb = gal_base(wl, g, logN);
+        add += (size_t)i * kT;
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[k] = 0;
+    }
+    tile_convert<8>(v, pc + (size_t)h * alpha * kT, alpha, hat + i, L1, m, tid);
+    tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
+    const size_t o = ((size_t)p * L1 + i) * kT + wl;
+    const uint64_t *prev = acc0 && z == 0 ? acc0 : mj.out[z];
+    const double pv = pinv[i], pvq = pinvq[i];
+#pragma unroll
+    for (int k = 0; k < 8; k++) {  // a in [0, t) or centred, s below 2.2 t
+        double t = corr(mul_shoup_lazy(reduce_c(a[k] - s[pad8(wl) + 72 * k], m), pv, pvq, m) + u2d(av[k]), m);
+        if (acc) t = add_mod(t, u2d(prev[o + 64 * k]), m);
+        if (cj.x) {  // the real/imaginary split, as in k_conj_split
+            const double x = u2d(cj.x[o + 64 * k]);
+            cj.re[o + 64 * k] = d2u(add_mod(x, t, m));
+            double q = mul_canon(sub_mod(x, t, m), W[1], m);
+            if ((brev_n((uint32_t)(wl + 64 * k), logN) & 1u) == 0u) q = q == 0.0 ? 0.0 : m.t - q;
+            cj.im[o + 64 * k] = d2u(q);
+        } else {
+            mj.out[z][o + 64 * k] = d2u(t);
+        }
+        v[k] = reduce_c(t, m);
+    }
+    if (last_out && i == level) {  // the rescale's inverse tile pass of this limb
+        tile_inverse8(v, s, tid, 0, 0, itw + (size_t)i * kT, kT, m);
+#pragma unroll
+        for (int k = 0; k < 8; k++) last_out[(size_t)p * kT + tid + 512 * k] = d2b(v[k]);
+    }
+}
+
+// Rescale by q_l and ModRaise, fused into the lifted limbs' transform (N >= 4096).
 // k_lift_col: one limb of each polynomial after its inverse tile pass (src [P][N], FP64
 // words): its last log2(N1) inverse stages and N^-1, the centred lift into target limbs
 // i < n_out and their forward column pass; thread = one column, `per` targets in turn;
@@ -1049,8 +1308,16 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, con
     const size_t t0 = (size_t)tile * kT;
     const uint64_t *src = lifted + (size_t)w * N + t0;
     double v[16];
+    if (logN1 == 0) {  // `lifted` is the last limbs after their inverse tile pass: lifted here
+        const PrimeInfo pl = info[level];
+        const uint64_t *last = lifted + (size_t)z * N;
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
+        for (int k = 0; k < 16; k++)
+            v[k] = reduce_c(reduce_c(reduce_c(mul_lazy(b2d(last[tid + 256 * k]), pl.ninv, pl.m), pl.m), pl.m), m);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
+    }
     const uint64_t *a = in + ((size_t)z * (level + 1) + i) * N + t0 + wv(tid);
     uint64_t av[16];  // requested before the transform, in which their latency passes: a
                       // mask's product and rescale at level 18, N = 2^16, 65 -> 61.6 us
@@ -1178,10 +1445,11 @@ hipError_t launch_ntt_fast(const nj_ctx *c, uint64_t *data, const uint64_t *src,
             if (e != hipSuccess) return e;
             src = nullptr;
         }
-        return launch(c, PROF_NTT_TILE, bytes, k_ntt_tile<false>, gt, dim3(kNT), s, data, src, lt, tw, c->d_info,
+        return launch(c, PROF_NTT_TILE, bytes, k_ntt_tile<false>, gt, dim3(kNT), s, data, src, lt, N1 > 1, tw, c->d_info,
                       c->log_n);
     }
-    e = launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, gt, dim3(kNT), s, data, src, lt, tw, c->d_info, c->log_n);
+    e = launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, gt, dim3(kNT), s, data, src, lt, N1 > 1, tw, c->d_info,
+               c->log_n);
     if (e != hipSuccess || N1 == 1) return e;
     return launch_cols<true>(c, PROF_NTT_COL_INV, bytes, N1, gc, s, data, nullptr, lt, tw, c->d_info, c->log_n);
 }
@@ -1199,29 +1467,33 @@ hipError_t launch_decrypt_fast(const nj_ctx *c, const uint64_t *ct, int level, u
                              c->d_info, c->log_n);
 }
 
-// Inverse tile pass alone, into data from src (N >= 8192): the basis conversion runs the
-// column pass.  With gt, the input limbs are read through X -> X^g of their job (off / L1).
+// Inverse tile pass alone, into data from src (N >= 4096): the basis conversion runs the
+// column pass.  With gt, the input limbs are read through X -> X^g of their job (off / L1);
+// with scale (N = 4096) canonical words times the prime's factor.
 hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt, hipStream_t s,
-                             const GalTab *gt, int L1)
+                             const GalTab *gt, int L1, const double *scale)
 {
     const int N = c->N, N1 = N / kT;
-    if (N1 < 2 || (gt && (!src || L1 < 1))) return hipErrorInvalidValue;
+    if (N1 < 1 || (scale && N1 > 1) || (gt && (!src || L1 < 1))) return hipErrorInvalidValue;
     if (lt.n == 0) return hipSuccess;
     const double bytes = 16.0 * N * lt.n;
+    if (N1 == 1)
+        return launch(c, PROF_NTT_TILE_INV, bytes, k_intt_tile, dim3(lt.n), dim3(kNT8), s, data, src, lt,
+                      gt ? *gt : GalTab{}, gt ? L1 : 0, scale, c->d_itw, c->d_info);
     return gt ? launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile_gal, dim3(N1, lt.n), dim3(kNT), s, data, src, lt, *gt,
                        L1, c->d_itw, c->d_info, c->log_n)
               : launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, dim3(N1, lt.n), dim3(kNT), s, data, src, lt,
-                       c->d_itw, c->d_info, c->log_n);
+                       1, c->d_itw, c->d_info, c->log_n);
 }
 
 // Centred lift of n_polys limbs after their inverse tile pass (prime src_pidx, at src + z N)
 // into primes 0..n_out-1 with the column passes on both sides, into out [n_polys][n_out][N]
-// (N >= 8192); the tile pass (launch_ntt_tiles, k_ntt_tile_rs) finishes the forward transform.
+// (N >= 4096); the tile pass (launch_ntt_tiles, k_ntt_tile_rs) finishes the forward transform.
 hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, int n_polys, int n_out, uint64_t *out,
                            hipStream_t s)
 {
     const int N = c->N, N1 = N / kT;
-    if (N1 < 2 || n_out < 1 || n_polys < 1) return hipErrorInvalidValue;
+    if (N1 < 1 || n_out < 1 || n_polys < 1) return hipErrorInvalidValue;
     // two targets share one inverse column pass: 1, 2, 4 and 8 each measured, mask and HMult
     // best at 1 and 2, a layer and a batch at 2 and 4 (12.59 / 12.50 / 12.52 / 12.68 ms a layer)
     const int per = 2;
@@ -1232,14 +1504,14 @@ hipError_t launch_lift_col(const nj_ctx *c, const uint64_t *src, int src_pidx, i
         return launch(c, PROF_OTHER, b, k_lift_col<NN>, g, dim3(kNT), s, src, src_pidx, n_out, per, out, c->d_tw, \
                       c->d_itw, c->d_info, c->log_n);
     switch (N1) {
-        NJ_LC(2) NJ_LC(4) NJ_LC(8) NJ_LC(16)
+        NJ_LC(1) NJ_LC(2) NJ_LC(4) NJ_LC(8) NJ_LC(16)
     }
 #undef NJ_LC
     return hipErrorInvalidValue;
 }
 
 // Rescale of P packed level-l polynomials (P = 2 per ciphertext; limbs 0..n_out-1 of
-// each kept), N >= 8192: inverse tile pass of the last limbs read in place (into
+// each kept), N >= 4096: inverse tile pass of the last limbs read in place (into
 // last [P][N]), lift fused with the column passes (into lifted [P][n_out][N], which may be
 // out: each tile block reads its own lifted words before writing them), tile pass
 // fused with the combine.  in must not alias out.
@@ -1247,13 +1519,14 @@ hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, 
                                 uint64_t *last, uint64_t *lifted, hipStream_t s, int n_polys, bool last_tiled)
 {
     const int N = c->N, N1 = N / kT;
-    if (N1 < 2 || n_out < 1 || n_out > level || n_polys < 1 || n_polys > NJ_MAX_LIMBS) return hipErrorInvalidValue;
+    if (N1 < 1 || n_out < 1 || n_out > level || n_polys < 1 || n_polys > NJ_MAX_LIMBS) return hipErrorInvalidValue;
     LimbTab lt;
     lt.n = n_polys;
     for (int p = 0; p < n_polys; p++) lt.pidx[p] = level, lt.off[p] = p, lt.soff[p] = p * (level + 1) + level;
     // last_tiled: the last limbs' inverse tile pass already ran (into last)
     hipError_t e = last_tiled ? hipSuccess : launch_intt_tiles(c, last, in, lt, s);
-    if (e == hipSuccess) e = launch_lift_col(c, last, level, n_polys, n_out, lifted, s);
+    if (e == hipSuccess && N1 > 1) e = launch_lift_col(c, last, level, n_polys, n_out, lifted, s);
+    if (N1 == 1) lifted = last;
     if (e != hipSuccess) return e;
     return launch(c, PROF_OTHER, 8.0 * N * n_polys * n_out * 4.0, k_ntt_tile_rs, dim3(N1, n_polys * n_out), dim3(kNT),
                   s, lifted, in, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q, c->d_tw, c->d_info, c->log_n);
@@ -1263,7 +1536,7 @@ hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uin
                               int n_polys, hipStream_t s)
 {
     const int N = c->N, N1 = N / kT, P = n_polys, n_out = level;
-    if (N1 < 2 || level < 1 || level > 31 || rt.n < 1 || rt.n > NJ_MAX_TERMS || P < 1 || rt.n * P > NJ_MAX_LIMBS)
+    if (N1 < 1 || level < 1 || level > 31 || rt.n < 1 || rt.n > NJ_MAX_TERMS || P < 1 || rt.n * P > NJ_MAX_LIMBS)
         return hipErrorInvalidValue;
     double wsum = 0;
     const uint64_t *base = rt.src[0];
@@ -1291,7 +1564,7 @@ hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uin
                    c->d_itw, c->d_info, c->log_n);                                                                 \
         break;
     switch (N1) {
-        NJ_LS(2) NJ_LS(4) NJ_LS(8) NJ_LS(16)
+        NJ_LS(1) NJ_LS(2) NJ_LS(4) NJ_LS(8) NJ_LS(16)
     default: return hipErrorInvalidValue;
     }
 #undef NJ_LS
@@ -1301,24 +1574,25 @@ hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uin
                   c->d_tw, c->d_info, c->log_n);
 }
 
-// Forward tile pass alone (the column pass already applied), N >= 8192.
+// Forward tile pass alone (the column pass already applied), N >= 4096.
 hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, hipStream_t s)
 {
     const int N = c->N, N1 = N / kT;
-    if (N1 < 2) return hipErrorInvalidValue;
+    if (N1 < 1) return hipErrorInvalidValue;
     if (lt.n == 0) return hipSuccess;
     return launch(c, PROF_NTT_TILE, 16.0 * N * lt.n, k_ntt_tile<false>, dim3(N1, lt.n), dim3(kNT), s, data, nullptr,
-                  lt, c->d_tw, c->d_info, c->log_n);
+                  lt, 1, c->d_tw, c->d_info, c->log_n);
 }
 
 // Basis conversion of n_jobs (job, digit) pairs with the column passes on both sides
 // (inputs after their inverse tile pass; scale: [n_primes] factor of each input's inverse
-// transform), N >= 8192, at most 8 input limbs per digit.
+// transform), N >= 4096, at most 8 input limbs per digit.  N = 4096: the whole forward
+// transform, inputs canonical and scaled.
 hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs,
                             const double *scale, hipStream_t s)
 {
     const int N = c->N, N1 = N / kT;
-    if (N1 < 2 || n_jobs == 0) return N1 < 2 ? hipErrorInvalidValue : hipSuccess;
+    if (N1 < 1 || n_jobs == 0) return N1 < 1 ? hipErrorInvalidValue : hipSuccess;
     int max_out = 0, mmax = 0;
     double bytes = 0;
     for (int j = 0; j < sh.nd; j++) {
@@ -1327,6 +1601,9 @@ hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvP
         bytes += 8.0 * N * (sh.m[j] + sh.n_out[j]) * n_jobs;
     }
     if (mmax > kBcWaves) return hipErrorInvalidValue;
+    if (N1 == 1)  // inputs scaled by their inverse transform; outputs in evaluation form
+        return launch(c, PROF_BCONV, bytes, k_conv_tile, dim3(n_jobs * sh.nd, max_out), dim3(kNT8), s, sh, jp, c->d_tw,
+                      c->d_info);
     // targets per wave: step 1 is half a target's work, so a block takes all targets once
     // there are blocks enough to fill the chip (256 CUs, two blocks each by their LDS: 8
     // digits of one size), and one per wave below that.  N = 2^16, 24 targets: 21 digits
@@ -1346,7 +1623,8 @@ hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvP
 }
 
 // ModDown combine of K jobs fused into the forward transform of their converted
-// limbs (N >= 4096; cols_done: the column pass was already applied); same results
+// limbs (N >= 4096; cols_done: the column pass was already applied, N = 4096: conv is the
+// special-prime rows, converted here); same results
 // as the transform followed by the combine.
 hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv, const uint64_t *u_base,
                               const MdJobs &mj, int acc, int cols_done, hipStream_t s, const uint64_t *acc0,
@@ -1358,6 +1636,12 @@ hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv,
         return hipErrorInvalidValue;
     MdConj cj{nullptr, nullptr, nullptr};
     if (conj) cj = *conj;
+    if (N1 == 1 && cols_done) {
+        if (skip || c->alpha > 8) return hipErrorInvalidValue;
+        return launch(c, PROF_NTT_MD, 8.0 * N * (n * 3.0 + K * L1 + (acc ? n : 0)), k_md_tile<0>, dim3(n), dim3(kNT8), s,
+                      conv, c->moddown[level].hat, u_base, KeyJobs{}, mj, acc, acc0, level, c->L, c->alpha, c->d_pinv,
+                      c->d_pinvq, c->d_tw, c->d_info, last_out, c->d_itw, cj);
+    }
     if (N1 > 1 && !cols_done) {
         LimbTab lt;
         for (int b = 0; b < n; b += NJ_MAX_LIMBS) {
@@ -1371,22 +1655,28 @@ hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv,
     const double bytes = 8.0 * N * (n * 3.0 + K * (L1 - skip) + (acc ? n : 0));
     if (conj)
         return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<true>, dim3(N1, n), dim3(kNT), s, conv, u_base, mj, acc,
-                      level, L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip);
+                      level, L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip,
+                      N1 > 1);
     return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<false>, dim3(N1, n), dim3(kNT), s, conv, u_base, mj, acc, level,
-                  L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip);
+                  L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip,
+                      N1 > 1);
 }
 
 // The plain ModDown combine of K key switches (converted limbs column-passed) with their
 // Q-limb key inner products computed inside it from extended evaluation-form digits
-// (N >= 8192, 1..4 digits).
+// (N >= 4096, 1..4 digits).
 hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64_t *conv, const KeyJobs &kj,
                                  const MdJobs &mj, hipStream_t s)
 {
     const int N = c->N, N1 = N / kT, L1 = level + 1, n = 2 * K * L1, nd = n_digits(c, level);
-    if (N1 < 2 || K < 1 || K > NJ_MAX_JOBS || nd < 1 || nd > 4) return hipErrorInvalidValue;
+    if (N1 < 1 || K < 1 || K > NJ_MAX_JOBS || nd < 1 || nd > 4) return hipErrorInvalidValue;
     const double bytes = 8.0 * N * (n * (2.0 * nd + 2.0) + K * L1);
 #define NJ_IPMD(ND)                                                                                                \
     case ND:                                                                                                       \
+        if (N1 == 1)                                                                                               \
+            return launch(c, PROF_KEYIP, bytes, k_md_tile<ND>, dim3(n), dim3(kNT8), s, conv, c->moddown[level].hat, \
+                          nullptr, kj, mj, 0, nullptr, level, c->L, c->alpha, c->d_pinv, c->d_pinvq, c->d_tw,      \
+                          c->d_info, nullptr, c->d_itw, MdConj{nullptr, nullptr, nullptr});                        \
         return launch(c, PROF_KEYIP, bytes, k_key_ip_md<ND>, dim3(N1, n), dim3(kNT), s, conv, kj, mj, level, c->L, \
                       c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n);
     switch (nd) {
@@ -1400,12 +1690,23 @@ hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64
 // read from d through X -> X^g) fused with the digits' tile pass; sum = 1: one output,
 // summed over the jobs; accumulate: added to the output's previous value.
 hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u, int sum,
-                         int accumulate, hipStream_t s, uint64_t *pout, int skip)
+                         int accumulate, hipStream_t s, uint64_t *pout, int skip, uint64_t *part)
 {
     const int N = c->N, N1 = N / kT, nd = n_digits(c, level), ne = level + 1 + c->alpha;
-    if (N1 < 2 || nd < 1 || nd > 4 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || skip < 0 || skip > std::max(0, level - 1))
+    if (N1 < 1 || nd < 1 || nd > 4 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || skip < 0 || skip > std::max(0, level - 1))
         return hipErrorInvalidValue;
     const double bytes = 8.0 * N * (ne - skip) * (3.0 * nd * n_jobs + 2.0 * (sum ? 1 : n_jobs) * (1 + accumulate));
+    if (N1 == 1) {
+        if (!part || skip || c->alpha > 8) return hipErrorInvalidValue;
+        IpTiles it;
+        for (int j = 0; j < nd; j++) it.hat[j] = c->modup[level][j].hat;
+        hipError_t e = launch(c, PROF_KEYIP, bytes, k_conv_ip, dim3(n_jobs, ne, nd), dim3(kNT8), s, kj, it, part, level,
+                              c->L, c->alpha, c->n_q, c->d_tw, c->d_info);
+        if (e != hipSuccess) return e;
+        return launch(c, PROF_KEYIP, 16.0 * N * ne * (nd * n_jobs + (sum ? 1 : n_jobs)), k_ip_reduce,
+                      dim3(sum ? 1 : n_jobs, 2 * ne), dim3(kNT8), s, part, sum ? nd * n_jobs : nd, u, accumulate, level,
+                      c->alpha, c->n_q, c->d_info, pout, c->d_itw, c->d_downscale);
+    }
     const dim3 grid(sum ? 1 : n_jobs, N1, ne - skip);
     // key words stay in the caches only for the jobs that share them (a batch: 33.3 ms cached,
     // 35.8 non-temporal; giant steps with a key each at N = 2^14: 0.78 and 0.75 ms a step)
@@ -1425,20 +1726,20 @@ hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jo
 }
 
 // Special-prime rows of n_jobs key inner products from extended evaluation-form digits,
-// through the first 12 stages of ModDown's inverse transform into pout (N >= 8192,
+// through the first 12 stages of ModDown's inverse transform into pout (N >= 4096,
 // 1..4 digits, alpha <= 8).
 hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *pout,
                                hipStream_t s)
 {
     const int N = c->N, N1 = N / kT, nd = n_digits(c, level);
-    if (N1 < 2 || nd < 1 || nd > 4 || c->alpha > 8 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || !pout)
+    if (N1 < 1 || nd < 1 || nd > 4 || c->alpha > 8 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || !pout)
         return hipErrorInvalidValue;
     const double bytes = 8.0 * N * c->alpha * (3.0 * nd + 2.0) * n_jobs;
     const dim3 grid(2 * n_jobs, N1, c->alpha);
 #define NJ_PT(ND)                                                                                             \
     case ND:                                                                                                  \
         return launch(c, PROF_KEYIP, bytes, k_key_ip_ptile<ND>, grid, dim3(kNT), s, kj, level, c->L, c->alpha, \
-                      c->n_q, c->d_info, c->log_n, pout, c->d_itw);
+                      c->n_q, c->d_info, c->log_n, pout, c->d_itw, c->d_downscale);
     switch (nd) {
         NJ_PT(1) NJ_PT(2) NJ_PT(3) NJ_PT(4)
     }
