@@ -6,19 +6,12 @@
 //   * N = N1 * 4096.  The first log2(N1) stages couple words with equal index
 //     mod 4096: one thread owns a whole column of N1 words (coalesced loads at
 //     stride 4096, twiddles uniform across the wavefront) - no LDS at all.
-//   * The last 12 stages stay inside a 4096-word tile: 256 threads own 16 words
-//     each and run 3 rounds of 4 radix-2 stages in registers; between rounds the
-//     tile goes through LDS once (padded by one word every 16 to avoid bank
-//     conflicts).  Global loads and stores are fully coalesced.
+//   * The last 12 stages stay inside a 4096-word tile: 512 threads own 8 words each
+//     and run 4 rounds of 3 radix-2 stages in registers; between rounds the tile goes
+//     through LDS once.  Global loads and stores are fully coalesced.
 // Which words a thread holds outside its rounds:
-//   across the block (forward in, inverse out): tid + 256 k;
-//   across its wave (forward out, inverse in): wv(tid) + 64 k, wv = 1024 wave + lane.
-// Rounds 1 and 2 stay inside a wave's 1024 words, so a tile pass has one barrier, between
-// round 0 and the others; exchanges inside a wave only keep their order (wave_sync).
-// Round 0's twiddles are the same for every thread of a tile: scalar loads.
-// A round covering strides t0, t0/2, t0/4, t0/8 gives thread (lo, hi) the words
-// x_k = lo + (t0/8) k + 2 t0 hi, k < 16; at stride t0/2^s the pair (k, k + 8>>s)
-// belongs to butterfly block hi 2^s + (k >> (4-s)) of the tile.
+//   across the block (forward in, inverse out): tid + 512 k;
+//   across its wave (forward out, inverse in): wv8(tid) + 64 k, wv8 = 512 wave + lane.
 #include <algorithm>
 
 #include "internal.h"
@@ -32,122 +25,18 @@ constexpr int kNT = 256;
 __device__ __forceinline__ double b2d(uint64_t x) { return __longlong_as_double((long long)x); }
 __device__ __forceinline__ uint64_t d2b(double x) { return (uint64_t)__double_as_longlong(x); }
 
-// (addresses below are a base per access pattern plus a constant per word: pad16(x + 16 y) =
-// pad16(x) + 17 y, which the compiler does not see through the shift)
-__device__ __forceinline__ int pad16(int x) { return x + (x >> 4); }
-
-// Rounds are lazy in both directions: 4 stages without correction, one centred reduction
-// (reduce_c) per word at the end.  With t < 2^50 the lazy product of a word below B t in
+// Rounds are lazy in both directions: no correction inside, centred reductions (reduce_c)
+// where the bound asks for one.  With t < 2^50 the lazy product of a word below B t in
 // magnitude lies within (1/2 + 3B/8) t (the quotient estimate is off by at most 1/2 + 3
 // ulp-relative errors of a value below B 2^50).
-//   Forward: the bound grows 1 -> 1.875 -> 3.08 -> 4.73 -> 7.01 over 4 stages from
-//   canonical words (1/2 -> 5.22 from centred ones).
+//   Forward: the bound grows 1/2 -> 1.19 -> 2.13 -> 3.43 -> 5.22 -> 7.68 over 5 stages from
+//   centred words (1 -> 7.01 over 4 from canonical ones).
 //   Inverse: sums double, 1/2 -> 1 -> 2 -> 4 -> 8 from centred words (products of
-//   differences stay below 3.5); from canonical words the two words that are sums all the
-//   way reach 8 after 3 stages and are reduced before the last one (7 for the others).
+//   differences stay below 3.5).
 // So every intermediate is an integer below 2^53 (8 t + 32 < 2^53 for t <= 2^50 - 4),
-// computed exactly.  A butterfly costs 9.5 FP64 operations, rounds included, in either
+// computed exactly.  A butterfly costs 9 to 9.5 FP64 operations, rounds included, in either
 // direction.  Words travel between the passes of one transform as FP64 values, centred;
 // what leaves a transform is canonical.
-
-// one round of 4 forward stages on 16 registers (strides t0 .. t0/8 within the tile)
-template <typename P>
-__device__ __forceinline__ void ct_round(double v[16], int t0, int hi, int tile, int logN1, P W, int N, Mod m)
-{
-#pragma unroll
-    for (int s = 0; s < 4; s++) {
-        const int t = t0 >> s;               // tile stride
-        const int mm = N / (2 * t);          // global stage
-        const int base = mm + tile * (mm >> logN1) + (hi << s);
-        const int step = 8 >> s;
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (k & step) continue;
-            const double w = W[base + (k >> (4 - s))];
-            const double U = v[k], V = mul_lazy(v[k + step], w, m);
-            v[k] = U + V;
-            v[k + step] = U - V;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
-}
-
-// one round of 4 inverse stages (strides t0/8 .. t0); CANON: canonical words on entry, else
-// centred
-template <bool CANON, typename P>
-__device__ __forceinline__ void gs_round(double v[16], int t0, int hi, int tile, int logN1, P W, int N, Mod m)
-{
-#pragma unroll
-    for (int s = 3; s >= 0; s--) {
-        if (CANON && s == 0) v[0] = reduce_c(v[0], m), v[8] = reduce_c(v[8], m);
-        const int t = t0 >> s;
-        const int hh = N / (2 * t);
-        const int base = hh + tile * (hh >> logN1) + (hi << s);
-        const int step = 8 >> s;
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (k & step) continue;
-            const double w = W[base + (k >> (4 - s))];
-            const double U = v[k], V = v[k + step];
-            v[k] = U + V;
-            v[k + step] = mul_lazy(U - V, w, m);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
-}
-
-// The 15 twiddles of one round (tile strides t0 .. t0/8) of butterfly block hi: stage
-// s's 2^s words at tw[2^s - 1 + i], W[mm + tile (mm >> logN1) + (hi << s) + i] with
-// mm = N / (2 (t0 >> s)).  The forward and the inverse table are indexed alike.
-__device__ __forceinline__ void round_tw(double tw[15], int t0, int hi, int tile, int logN1, const double *W, int N)
-{
-#pragma unroll
-    for (int st = 0; st < 4; st++) {
-        const int mm = N / (2 * (t0 >> st));
-        const int base = mm + tile * (mm >> logN1) + (hi << st);
-#pragma unroll
-        for (int i = 0; i < (1 << st); i++) tw[(1 << st) - 1 + i] = W[base + i];
-    }
-}
-
-// ct_round / gs_round with the round's twiddles given (round_tw)
-__device__ __forceinline__ void ct_round_tw(double v[16], const double tw[15], Mod m)
-{
-#pragma unroll
-    for (int st = 0; st < 4; st++) {
-        const int step = 8 >> st;
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (k & step) continue;
-            const double U = v[k], V = mul_lazy(v[k + step], tw[(1 << st) - 1 + (k >> (4 - st))], m);
-            v[k] = U + V;
-            v[k + step] = U - V;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
-}
-
-template <bool CANON>
-__device__ __forceinline__ void gs_round_tw(double v[16], const double tw[15], Mod m)
-{
-#pragma unroll
-    for (int st = 3; st >= 0; st--) {
-        const int step = 8 >> st;
-        if (CANON && st == 0) v[0] = reduce_c(v[0], m), v[8] = reduce_c(v[8], m);
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (k & step) continue;
-            const double U = v[k], V = v[k + step];
-            v[k] = U + V;
-            v[k + step] = mul_lazy(U - V, tw[(1 << st) - 1 + (k >> (4 - st))], m);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = reduce_c(v[k], m);
-}
 
 // orders a wave's LDS writes before its own later reads (no other wave is waited for)
 __device__ __forceinline__ void wave_sync()
@@ -157,122 +46,18 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// a thread's first word across its wave
-__device__ __forceinline__ int wv(int tid) { return ((tid & ~63) << 4) | (tid & 63); }
-
-// The last 12 forward stages of one 4096-word tile: v holds words tid + 256 k (canonical
-// or centred) on entry; on return the transformed words are in s (word x at pad16(x),
-// centred), and a thread may read its words wv(tid) + 64 k.  No other wave may still be
-// reading s on entry.  A round's twiddles are requested before the exchange that precedes it.
-__device__ __forceinline__ void tile_forward(double v[16], double *s, int tid, int tile, int logN1, const double *W,
-                                             int N, Mod m)
-{
-    const int lo = tid & 15, hi = tid >> 4;
-    double *sb = s + pad16(tid), *s1 = s + 272 * hi + lo, *s2 = s + 17 * tid, tw[15];
-    // round 0: strides 2048..256, thread tid owns x = tid + 256 k
-    ct_round(v, 2048, 0, tile, logN1, const_tab(W), N, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) sb[272 * k] = v[k];
-    // round 1: strides 128..16, (lo, hi) = (tid & 15, tid >> 4): x = lo + 16 k + 256 hi
-    round_tw(tw, 128, hi, tile, logN1, W, N);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s1[17 * k];
-    ct_round_tw(v, tw, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s1[17 * k] = v[k];
-    // round 2: strides 8..1, thread owns x = 16 tid + k
-    round_tw(tw, 8, tid, tile, logN1, W, N);
-    wave_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s2[k];
-    ct_round_tw(v, tw, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s2[k] = v[k];
-    wave_sync();
-}
-
-// The first 12 inverse stages of one 4096-word tile (inverse twiddles W): v holds
-// words wv(tid) + 64 k on entry (canonical or centred) and tid + 256 k on return (centred);
-// no other wave may still be reading s on entry.
-__device__ __forceinline__ void tile_inverse(double v[16], double *s, int tid, int tile, int logN1, const double *W,
-                                             int N, Mod m)
-{
-    const int lo = tid & 15, hi = tid >> 4;
-    double *sb = s + pad16(tid), *s1 = s + 272 * hi + lo, *s2 = s + 17 * tid, *sw = s + pad16(wv(tid)), tw[15];
-    round_tw(tw, 8, tid, tile, logN1, W, N);
-#pragma unroll
-    for (int k = 0; k < 16; k++) sw[68 * k] = v[k];
-    wave_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s2[k];
-    gs_round_tw<true>(v, tw, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s2[k] = v[k];
-    round_tw(tw, 128, hi, tile, logN1, W, N);
-    wave_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = s1[17 * k];
-    gs_round_tw<false>(v, tw, m);
-#pragma unroll
-    for (int k = 0; k < 16; k++) s1[17 * k] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = sb[272 * k];
-    gs_round<false>(v, 2048, 0, tile, logN1, const_tab(W), N, m);
-}
-
-// rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs).  part: the forward's
-// input and the inverse's output are FP64 words of the pass beside it (a column pass, or a
-// kernel that does its work); else the tile is the whole transform, N = 4096.
-template <bool INV>
-__global__ __launch_bounds__(kNT) void k_ntt_tile(uint64_t *data, const uint64_t *src, LimbTab lt, int part,
-                                                  const double *tw, const PrimeInfo *info, int logN)
-{
-    __shared__ double s[kT + kT / 16];
-    const int N = 1 << logN, logN1 = logN - 12;
-    const int limb = blockIdx.y, pidx = lt.pidx[limb], tile = blockIdx.x, tid = threadIdx.x;
-    const PrimeInfo pi = info[pidx];
-    const Mod m = pi.m;
-    const size_t off = (size_t)lt.off[limb] * N + (size_t)tile * kT;
-    const uint64_t *in = src ? src + (size_t)lt.soff[limb] * N + (size_t)tile * kT : data + off;
-    uint64_t *out = data + off;
-    const double *W = tw + (size_t)pidx * N;
-    const int w0 = wv(tid);
-    double v[16];
-    if (!INV) {
-        if (!part) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
-        }
-        tile_forward(v, s, tid, tile, logN1, W, N, m);
-#pragma unroll
-        for (int k = 0; k < 16; k++) out[w0 + 64 * k] = d2u(corr(s[pad16(w0) + 68 * k], m));
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(in[w0 + 64 * k]);
-        tile_inverse(v, s, tid, tile, logN1, W, N, m);
-        if (!part) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2u(corr(mul_lazy(v[k], pi.ninv, m), m));
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; k++) out[tid + 256 * k] = d2b(v[k]);
-        }
-    }
-}
-
-// ------------------------------------------- tile passes of 512 threads, 8 words each
+// ------------------------------------------- tile passes: 512 threads, 8 words each
 //
-// For k_ntt_ip, which holds a thread's sums and key words through the transform: 4 rounds
-// of 3 stages.  Round 0 (strides 2048..512) holds words tid + 512 k; after it a wave owns 512
-// contiguous words and the rest needs no barrier: round 1 (256..64) wv8(tid) + 64 k, round 2
-// (32..8) 64 (tid >> 3) + (tid & 7) + 8 k, round 3 (4..1) 8 tid + k.  The twiddles of rounds 0
-// and 1 are the same for a whole wave: scalar loads.  The LDS tile is padded by one word
-// every 8: every access pattern above then spreads over all banks.
+// 4 rounds of 3 stages.  Round 0 (strides 2048..512) holds words tid + 512 k; after it a wave
+// owns 512 contiguous words and the rest needs no barrier: round 1 (256..64) wv8(tid) + 64 k,
+// round 2 (32..8) 64 (tid >> 3) + (tid & 7) + 8 k, round 3 (4..1) 8 tid + k.  The twiddles of
+// rounds 0 and 1 are the same for a whole wave: scalar loads.  The LDS tile is padded by one
+// word every 8: every access pattern above then spreads over all banks.
+// Eight words leave registers for what else a kernel reads or sums through the transform, all of
+// it requested before, and 8 waves per SIMD by LDS where it reads little.  Against 256 threads
+// of 16 words in 3 rounds of 4 stages (one LDS exchange less): a conv at level 1, N = 2^16, 158
+// against 169 us, conv + CoeffToSlot at N = 2^14 685 / 733, one rotation at level 23 113 / 117,
+// a batch of 11 32.8 / 33.2 ms.
 constexpr int kNT8 = 512;
 __device__ __forceinline__ int pad8(int x) { return x + (x >> 3); }
 __device__ __forceinline__ int wv8(int tid) { return ((tid & ~63) << 3) | (tid & 63); }
@@ -442,6 +227,46 @@ __device__ __forceinline__ void tile_inverse8(double v[8], double *s, int tid, i
         gs8(v, st, m, [&](int i) { return w[i]; });
     }
     reduce8(v, m);
+}
+
+// rows pass: last 12 stages on 4096-word tiles.  grid (N/4096, limbs).  part: the forward's
+// input and the inverse's output are FP64 words of the pass beside it (a column pass, or a
+// kernel that does its work); else the tile is the whole transform, N = 4096.
+template <bool INV>
+__global__ __launch_bounds__(kNT8) void k_ntt_tile(uint64_t *data, const uint64_t *src, LimbTab lt, int part,
+                                                   const double *tw, const PrimeInfo *info, int logN)
+{
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[INV ? 1 : kTw8R2];
+    const int N = 1 << logN, logN1 = logN - 12;
+    const int limb = blockIdx.y, pidx = lt.pidx[limb], tile = blockIdx.x, tid = threadIdx.x;
+    const PrimeInfo pi = info[pidx];
+    const Mod m = pi.m;
+    const size_t off = (size_t)lt.off[limb] * N + (size_t)tile * kT;
+    const uint64_t *in = src ? src + (size_t)lt.soff[limb] * N + (size_t)tile * kT : data + off;
+    const double *W = tw + (size_t)pidx * N;
+    const int w0 = wv8(tid);
+    double v[8];
+    if (!INV) {
+        uint64_t *out = data + off + w0;
+        double tw3[7];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const uint64_t x = in[tid + 512 * k];
+            v[k] = part ? b2d(x) : reduce_c(u2d(x), m);
+        }
+        load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
+        tile_forward8(v, s, tws, tw3, tid, tile, logN1, W, N, m, [] {});
+#pragma unroll
+        for (int k = 0; k < 8; k++) out[64 * k] = d2u(corr(reduce_c(s[pad8(w0) + 72 * k], m), m));
+    } else {
+        uint64_t *out = data + off + tid;
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = reduce_c(u2d(in[w0 + 64 * k]), m);
+        tile_inverse8(v, s, tid, tile, logN1, W, N, m);
+#pragma unroll
+        for (int k = 0; k < 8; k++) out[512 * k] = part ? d2b(v[k]) : d2u(corr(mul_lazy(v[k], pi.ninv, m), m));
+    }
 }
 
 // Rings of one tile (N = 4096) have no column pass, and their launches are a few blocks each:
@@ -759,26 +584,26 @@ __global__ __launch_bounds__(kNT8, 4) void k_conv_tile(BconvShared sh, BconvPtrs
 // the transform of that limb (a product and a sum per word on the way in instead of two
 // passes over memory: 20.3 us instead of 39.1 for the whole call at level 20, N = 2^16, whose
 // words take 6.6 us to read and write once).  grid (N/4096, limbs); output as k_ntt_tile<true>'s.
-__global__ __launch_bounds__(kNT) void k_ntt_tile_dec(uint64_t *data, const uint64_t *c0, size_t half, const uint64_t *sk,
+__global__ __launch_bounds__(kNT8) void k_ntt_tile_dec(uint64_t *data, const uint64_t *c0, size_t half, const uint64_t *sk,
                                                       const double *tw, const PrimeInfo *info, int logN)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
     const int N = 1 << logN, logN1 = logN - 12, limb = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x;
     const PrimeInfo pi = info[limb];
     const Mod m = pi.m;
-    const size_t o = (size_t)limb * N + (size_t)tile * kT, w0 = o + wv(tid);
-    double v[16];
+    const size_t o = (size_t)limb * N + (size_t)tile * kT, w0 = o + wv8(tid);
+    double v[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++)  // within 1.88 t
+    for (int k = 0; k < 8; k++)  // within 1.88 t
         v[k] = reduce_c(mul_lazy(u2d(c0[half * N + w0 + 64 * k]), u2d(sk[w0 + 64 * k]), m) + u2d(c0[w0 + 64 * k]), m);
-    tile_inverse(v, s, tid, tile, logN1, tw + (size_t)limb * N, N, m);
+    tile_inverse8(v, s, tid, tile, logN1, tw + (size_t)limb * N, N, m);
     uint64_t *out = data + o + tid;
     if (logN1 == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) out[256 * k] = d2u(corr(mul_lazy(v[k], pi.ninv, m), m));
+        for (int k = 0; k < 8; k++) out[512 * k] = d2u(corr(mul_lazy(v[k], pi.ninv, m), m));
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) out[256 * k] = d2b(v[k]);
+        for (int k = 0; k < 8; k++) out[512 * k] = d2b(v[k]);
     }
 }
 
@@ -791,71 +616,70 @@ __global__ __launch_bounds__(kNT) void k_ntt_tile_dec(uint64_t *data, const uint
 // evaluation form.  Grid (2 jobs, N/4096, alpha): blockIdx.x = 2 z + p, so the two
 // halves of one tile, which read the same digit words, are dispatched together.
 template <int ND>
-__global__ __launch_bounds__(kNT, 4) void k_key_ip_ptile(KeyJobs kj, int level, int L, int alpha, int nq,
+__global__ __launch_bounds__(kNT8, 4) void k_key_ip_ptile(KeyJobs kj, int level, int L, int alpha, int nq,
                                                          const PrimeInfo *info, int logN, uint64_t *pout,
                                                          const double *itw, const double *scale)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
     const int N = 1 << logN, logN1 = logN - 12;
     const int z = blockIdx.x >> 1, p = blockIdx.x & 1, tile = blockIdx.y, a = blockIdx.z, tid = threadIdx.x;
     const int t = level + 1 + a, pidx = nq + a;
     const Mod m = info[pidx].m;
     const IpRow r = ip_row(t, level, L, alpha);
-    const uint32_t g = kj.g[z], w0 = (uint32_t)tile * kT + wv(tid);
+    const uint32_t g = kj.g[z], w0 = (uint32_t)tile * kT + wv8(tid);
     const auto e = buf_rsrc(kj.ext[z], 8u * (uint32_t)(ND * r.ne) * (uint32_t)N);
     const auto key = buf_rsrc(kj.key[z], 8u * (uint32_t)(2 * ND * r.nk) * (uint32_t)N);
-    uint32_t src[16];
+    const uint32_t gb = gal_base((int)w0, g, logN);
+    uint32_t src[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++) src[k] = 8u * (uint32_t)galois_src2((int)(w0 + 64u * k), g, logN);
-    double acc[16];
+    for (int k = 0; k < 8; k++) src[k] = 8u * (uint32_t)gal_at(gb, 64 * k, g, logN);
+    double acc[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++) acc[k] = 0.0;
+    for (int k = 0; k < 8; k++) acc[k] = 0.0;
 #pragma unroll
     for (int j = 0; j < ND; j++) {
         const uint32_t xo = 8u * (uint32_t)((j * r.ne + r.t) * N),
                        vk = 8u * ((uint32_t)((j * 2 + p) * r.nk + r.kl) * (uint32_t)N + w0);
 #pragma unroll
-        for (int k = 0; k < 16; k++)
+        for (int k = 0; k < 8; k++)
             acc[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld<true>(key, vk, 512u * k)), m);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) acc[k] = reduce_c(acc[k], m);
-    tile_inverse(acc, s, tid, tile, logN1, itw + (size_t)pidx * N, N, m);
+    for (int k = 0; k < 8; k++) acc[k] = reduce_c(acc[k], m);
+    tile_inverse8(acc, s, tid, tile, logN1, itw + (size_t)pidx * N, N, m);
     uint64_t *out = pout + ((size_t)(2 * z + p) * alpha + a) * N + (size_t)tile * kT + tid;
     if (logN1 == 0) {  // as launch_intt_tiles with its scale
         const double sc = scale[pidx];
 #pragma unroll
-        for (int k = 0; k < 16; k++) out[256 * k] = d2u(corr(mul_lazy(acc[k], sc, m), m));
+        for (int k = 0; k < 8; k++) out[512 * k] = d2u(corr(mul_lazy(acc[k], sc, m), m));
         return;
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[256 * k] = d2b(acc[k]);
+    for (int k = 0; k < 8; k++) out[512 * k] = d2b(acc[k]);
 }
 
 // Inverse tile pass whose input limbs are read through X -> X^g (the automorphism of a
 // key switch folded into ModUp's inverse transform): limb lt[b] is of job off / L1,
 // read from src + soff N at the words the Galois element gt.g[job] moves to each
 // position.  grid (N/4096, limbs).
-__global__ __launch_bounds__(kNT) void k_ntt_tile_gal(uint64_t *data, const uint64_t *src, LimbTab lt, GalTab gt,
+__global__ __launch_bounds__(kNT8) void k_ntt_tile_gal(uint64_t *data, const uint64_t *src, LimbTab lt, GalTab gt,
                                                       int L1, const double *tw, const PrimeInfo *info, int logN)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
     const int N = 1 << logN, logN1 = logN - 12;
     const int limb = blockIdx.y, pidx = lt.pidx[limb], tile = blockIdx.x, tid = threadIdx.x;
     const Mod m = info[pidx].m;
     const uint32_t g = gt.g[lt.off[limb] / L1];
     const uint64_t *in = src + (size_t)lt.soff[limb] * N;
     const size_t w0 = (size_t)tile * kT + tid;
-    double v[16];
+    double v[8];
+    const uint32_t gb = gal_base(tile * kT + wv8(tid), g, logN);
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const int w = tile * kT + wv(tid) + 64 * k;
-        v[k] = u2d(in[g == 1u ? w : galois_src2(w, g, logN)]);
-    }
-    tile_inverse(v, s, tid, tile, logN1, tw + (size_t)pidx * N, N, m);
+    for (int k = 0; k < 8; k++) v[k] = reduce_c(u2d(in[gal_at(gb, 64 * k, g, logN)]), m);
+    tile_inverse8(v, s, tid, tile, logN1, tw + (size_t)pidx * N, N, m);
     uint64_t *out = data + (size_t)lt.off[limb] * N + w0;
 #pragma unroll
-    for (int k = 0; k < 16; k++) __builtin_nontemporal_store(d2b(v[k]), out + 256 * k);
+    for (int k = 0; k < 8; k++) __builtin_nontemporal_store(d2b(v[k]), out + 512 * k);
 }
 
 // The first log2(N1) forward stages on one column of N1 words, canonical or centred (lazy,
@@ -1045,12 +869,13 @@ __global__ __launch_bounds__(kBcCols * kBcWaves, 4) void k_bconv_col(BconvShared
 // the words they wrote and store them at last_out + p N, ready for a rescale.
 // grid (N/4096, 2 K (l+1)): limb w = (2 z + p)(l+1) + i.
 template <bool CONJ>
-__global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, const uint64_t *u_base, MdJobs mj, int acc,
+__global__ __launch_bounds__(kNT8, 4) void k_ntt_tile_md(const uint64_t *conv, const uint64_t *u_base, MdJobs mj, int acc,
                                                      int level, int ne, const double *pinv, const double *pinvq,
                                                      const double *tw, const PrimeInfo *info, int logN, const uint64_t *acc0,
                                                      uint64_t *last_out, const double *itw, MdConj cj, int skip, int part)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
     const int N = 1 << logN, logN1 = logN - 12, L1 = level + 1, L1e = L1 - skip;
     const int w = blockIdx.y, h = w / L1e, ie = w - h * L1e, i = ie == 0 ? 0 : ie + skip, z = h >> 1, p = h & 1;
     const int tile = blockIdx.x, tid = threadIdx.x;
@@ -1058,35 +883,42 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
     const double *W = tw + (size_t)i * N;
     const size_t t0 = (size_t)tile * kT;
     const uint64_t *in = conv + ((size_t)h * L1 + i) * N + t0;
-    double v[16];
-    const int wl = wv(tid);
+    double v[8];
+    const int wl = wv8(tid);
     const uint64_t *u = u_base + ((size_t)z * 2 * ne + (size_t)p * ne + i) * N + t0 + wl;
-    uint64_t uv[16];  // requested before the transform, in which their latency passes: conv +
+    uint64_t uv[8];  // requested before the transform, in which their latency passes: conv +
                       // CoeffToSlot at N = 2^14 750 -> 734 us
 #pragma unroll
-    for (int k = 0; k < 16; k++) uv[k] = u[64 * k];
+    for (int k = 0; k < 8; k++) uv[k] = u[64 * k];
     if (!part) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(in[tid + 256 * k]);
+        for (int k = 0; k < 8; k++) v[k] = reduce_c(u2d(in[tid + 512 * k]), m);
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
+        for (int k = 0; k < 8; k++) v[k] = b2d(in[tid + 512 * k]);
     }
-    tile_forward(v, s, tid, tile, logN1, W, N, m);
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
-    const uint32_t g = mj.g_add[z];
+    uint64_t av[8];
+    if (add) {
+        const uint32_t g = mj.g_add[z], gb = gal_base((int)t0 + wl, g, logN);
+        add += (size_t)i * N;
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[k] = 0;
+    }
+    double tw3[7];
+    load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
+    tile_forward8(v, s, tws, tw3, tid, tile, logN1, W, N, m, [] {});
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
     const uint64_t *prev = acc0 && z == 0 ? acc0 + ((size_t)p * L1 + i) * N + t0 : out;
     const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
+    for (int k = 0; k < 8; k++) {
         const int x = wl + 64 * k;
-        double t = mul_shoup_lazy(u2d(uv[k]) - s[pad16(wv(tid)) + 68 * k], pv, pvq, m);  // u in [0, t), s centred
-        if (add) {
-            const int kk = (int)t0 + x;
-            t += u2d(add[(size_t)i * N + (g <= 1u ? kk : galois_src2(kk, g, logN))]);
-        }
-        t = corr(t, m);
+        // u in [0, t), s below 2.2 t
+        double t = corr(mul_shoup_lazy(reduce_c(u2d(uv[k]) - s[pad8(wl) + 72 * k], m), pv, pvq, m) + u2d(av[k]), m);
         if (acc) t = add_mod(t, u2d(prev[x]), m);
         if (CONJ) {  // the real/imaginary split, as in k_conj_split
             const size_t o = ((size_t)p * L1 + i) * N + t0 + x;
@@ -1101,10 +933,10 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
     }
     if (last_out && i == level) {  // the rescale's inverse tile pass of this limb
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = u2d(out[wl + 64 * k]);  // this thread's own words
-        tile_inverse(v, s, tid, tile, logN1, itw + (size_t)i * N, N, m);
+        for (int k = 0; k < 8; k++) v[k] = reduce_c(u2d(out[wl + 64 * k]), m);  // this thread's own words
+        tile_inverse8(v, s, tid, tile, logN1, itw + (size_t)i * N, N, m);
 #pragma unroll
-        for (int k = 0; k < 16; k++) last_out[(size_t)p * N + t0 + tid + 256 * k] = d2b(v[k]);
+        for (int k = 0; k < 8; k++) last_out[(size_t)p * N + t0 + tid + 512 * k] = d2b(v[k]);
     }
 }
 
@@ -1116,65 +948,69 @@ __global__ __launch_bounds__(kNT, 4) void k_ntt_tile_md(const uint64_t *conv, co
 // part, after its tile pass) P^-1 plus add.  The products never go to memory.  Grid
 // (N/4096, 2 K (l+1)).
 template <int ND>
-__global__ __launch_bounds__(kNT, ND == 4 ? 2 : 4) void k_key_ip_md(const uint64_t *conv, KeyJobs kj, MdJobs mj, int level, int L,
-                                                      int alpha, const double *pinv, const double *pinvq,
-                                                      const double *tw, const PrimeInfo *info, int logN)
+__global__ __launch_bounds__(kNT8, 4) void k_key_ip_md(const uint64_t *conv, KeyJobs kj, MdJobs mj, int level, int L,
+                                                       int alpha, const double *pinv, const double *pinvq,
+                                                       const double *tw, const PrimeInfo *info, int logN)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
     const int N = 1 << logN, logN1 = logN - 12, L1 = level + 1;
     const int w = blockIdx.y, h = w / L1, i = w - h * L1, z = h >> 1, p = h & 1;
     const int tile = blockIdx.x, tid = threadIdx.x;
     const Mod m = info[i].m;
     const size_t t0 = (size_t)tile * kT;
     const IpRow r = ip_row(i, level, L, alpha);
-    const uint32_t g = kj.g[z], w0 = (uint32_t)t0 + wv(tid);
+    const uint32_t g = kj.g[z], w0 = (uint32_t)t0 + wv8(tid);
     const auto e = buf_rsrc(kj.ext[z], 8u * (uint32_t)(ND * r.ne) * (uint32_t)N);
     const auto dd = buf_rsrc(kj.d[z] + (size_t)i * N, 8u * (uint32_t)N);
     const auto key = buf_rsrc(kj.key[z], 8u * (uint32_t)(2 * ND * r.nk) * (uint32_t)N);
-    double a[16];
+    double a[8];
     {
-        uint32_t src[16];
+        const uint32_t gb = gal_base((int)w0, g, logN);
+        uint32_t src[8];
 #pragma unroll
-        for (int k = 0; k < 16; k++)
-            src[k] = 8u * (g <= 1u ? w0 + 64u * k : (uint32_t)galois_src2((int)(w0 + 64u * k), g, logN));
+        for (int k = 0; k < 8; k++) src[k] = 8u * (uint32_t)gal_at(gb, 64 * k, g, logN);
 #pragma unroll
-        for (int k = 0; k < 16; k++) a[k] = 0.0;
+        for (int k = 0; k < 8; k++) a[k] = 0.0;
 #pragma unroll
         for (int j = 0; j < ND; j++) {
             const uint32_t vk = 8u * ((uint32_t)((j * 2 + p) * r.nk + r.kl) * (uint32_t)N + w0);
             if (j == r.own) {
 #pragma unroll
-                for (int k = 0; k < 16; k++)
+                for (int k = 0; k < 8; k++)
                     a[k] += mul_lazy(u2d(buf_ld(dd, src[k], 0)), u2d(buf_ld<true>(key, vk, 512u * k)), m);
             } else {
                 const uint32_t xo = 8u * (uint32_t)((j * r.ne + r.t) * N);
 #pragma unroll
-                for (int k = 0; k < 16; k++)
+                for (int k = 0; k < 8; k++)
                     a[k] += mul_lazy(u2d(buf_ld(e, src[k], xo)), u2d(buf_ld<true>(key, vk, 512u * k)), m);
             }
         }
+        reduce8(a, m);
+    }
+    const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
+    uint64_t av[8];
+    if (add) {
+        const uint32_t ga = mj.g_add[z], gb = gal_base((int)w0, ga, logN);
+        add += (size_t)i * N;
 #pragma unroll
-        for (int k = 0; k < 16; k++) a[k] = reduce_c(a[k], m);
+        for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, ga, logN)];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[k] = 0;
     }
     const uint64_t *in = conv + ((size_t)h * L1 + i) * N + t0;
-    double v[16];
+    const double *W = tw + (size_t)i * N;
+    double v[8], tw3[7];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = b2d(in[tid + 256 * k]);
-    tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
-    const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
-    const uint32_t ga = mj.g_add[z];
-    uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
+    for (int k = 0; k < 8; k++) v[k] = b2d(in[tid + 512 * k]);
+    load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
+    tile_forward8(v, s, tws, tw3, tid, tile, logN1, W, N, m, [] {});
+    uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + w0;
     const double pv = pinv[i], pvq = pinvq[i];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const int x = wv(tid) + 64 * k;
-        double t = mul_shoup_lazy(a[k] - s[pad16(wv(tid)) + 68 * k], pv, pvq, m);  // both centred
-        if (add) {
-            const int kk = (int)t0 + x;
-            t += u2d(add[(size_t)i * N + (ga <= 1u ? kk : galois_src2(kk, ga, logN))]);
-        }
-        out[x] = d2u(corr(t, m));
-    }
+    for (int k = 0; k < 8; k++)  // a centred, s below 2.2 t
+        out[64 * k] = d2u(corr(mul_shoup_lazy(reduce_c(a[k] - s[pad8(wv8(tid)) + 72 * k], m), pv, pvq, m) + u2d(av[k]), m));
 }
 
 // The ModDown combine on the ring of one tile, with its conversion: pc [2 K][alpha][N], the
@@ -1296,40 +1132,44 @@ __global__ __launch_bounds__(kNT) void k_lift_col(const uint64_t *last, int src_
 
 // k_ntt_tile_rs: the lifted limbs' tile pass with the rescale combine as its epilogue,
 // out[z][i] = (in[z][i] - NTT(lift)[z][i]) q_l^-1 mod q_i; grid (N/4096, P n_out).
-__global__ __launch_bounds__(kNT) void k_ntt_tile_rs(const uint64_t *lifted, const uint64_t *in, uint64_t *out,
+__global__ __launch_bounds__(kNT8) void k_ntt_tile_rs(const uint64_t *lifted, const uint64_t *in, uint64_t *out,
                                                      int level, int n_out, const double *qlinv, const double *qlinvq,
                                                      int nq, const double *tw, const PrimeInfo *info, int logN)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
     const int N = 1 << logN, logN1 = logN - 12;
     const int w = blockIdx.y, z = w / n_out, i = w - z * n_out;
     const int tile = blockIdx.x, tid = threadIdx.x;
     const Mod m = info[i].m;
     const size_t t0 = (size_t)tile * kT;
+    const double *W = tw + (size_t)i * N;
+    double tw3[7];
+    load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
     const uint64_t *src = lifted + (size_t)w * N + t0;
-    double v[16];
+    double v[8];
     if (logN1 == 0) {  // `lifted` is the last limbs after their inverse tile pass: lifted here
         const PrimeInfo pl = info[level];
         const uint64_t *last = lifted + (size_t)z * N;
 #pragma unroll
-        for (int k = 0; k < 16; k++)
-            v[k] = reduce_c(reduce_c(reduce_c(mul_lazy(b2d(last[tid + 256 * k]), pl.ninv, pl.m), pl.m), pl.m), m);
+        for (int k = 0; k < 8; k++)
+            v[k] = reduce_c(reduce_c(reduce_c(mul_lazy(b2d(last[tid + 512 * k]), pl.ninv, pl.m), pl.m), pl.m), m);
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
+        for (int k = 0; k < 8; k++) v[k] = b2d(src[tid + 512 * k]);
     }
-    const uint64_t *a = in + ((size_t)z * (level + 1) + i) * N + t0 + wv(tid);
-    uint64_t av[16];  // requested before the transform, in which their latency passes: a
+    const uint64_t *a = in + ((size_t)z * (level + 1) + i) * N + t0 + wv8(tid);
+    uint64_t av[8];  // requested before the transform, in which their latency passes: a
                       // mask's product and rescale at level 18, N = 2^16, 65 -> 61.6 us
 #pragma unroll
-    for (int k = 0; k < 16; k++) av[k] = a[64 * k];
-    tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
+    for (int k = 0; k < 8; k++) av[k] = a[64 * k];
+    tile_forward8(v, s, tws, tw3, tid, tile, logN1, W, N, m, [] {});
     uint64_t *o = out + ((size_t)z * n_out + i) * N + t0;
     const double wl = qlinv[level * nq + i], wlq = qlinvq[level * nq + i];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const int x = wv(tid) + 64 * k;
-        o[x] = d2u(corr(mul_shoup_lazy(u2d(av[k]) - s[pad16(wv(tid)) + 68 * k], wl, wlq, m), m));
+    for (int k = 0; k < 8; k++) {
+        const int x = wv8(tid) + 64 * k;
+        __builtin_nontemporal_store(d2u(corr(mul_shoup_lazy(reduce_c(u2d(av[k]) - s[pad8(wv8(tid)) + 72 * k], m), wl, wlq, m), m)), o + x);
     }
 }
 
@@ -1381,35 +1221,39 @@ __global__ __launch_bounds__(kNT) void k_lift_sum(const uint64_t *last, RsTerms 
 // k_ntt_tile_rsum: the lifted sums' tile pass with the combine as its epilogue,
 // out[z][i] = (sum_j kw_j x_j[z][i] - NTT(lift)[z][i]) q_l^-1 + c + add; grid (N/4096, P n_out).
 // The terms' lazy products stay within 8 7/8 t.
-__global__ __launch_bounds__(kNT) void k_ntt_tile_rsum(const uint64_t *lifted, RsTerms rt, uint64_t *out, int level,
+__global__ __launch_bounds__(kNT8) void k_ntt_tile_rsum(const uint64_t *lifted, RsTerms rt, uint64_t *out, int level,
                                                        int n_out, const double *qlinv, const double *qlinvq, int nq,
                                                        const double *tw, const PrimeInfo *info, int logN)
 {
-    __shared__ double s[kT + kT / 16];
+    __shared__ double s[kT + kT / 8];
+    __shared__ double tws[kTw8R2];
     const int N = 1 << logN, logN1 = logN - 12;
     const int w = blockIdx.y, z = w / n_out, i = w - z * n_out;
-    const int tile = blockIdx.x, tid = threadIdx.x, wl = wv(tid);
+    const int tile = blockIdx.x, tid = threadIdx.x, wl = wv8(tid);
     const Mod m = info[i].m;
     const size_t t0 = (size_t)tile * kT;
     const uint64_t *src = lifted + (size_t)w * N + t0;
-    double v[16];
+    double v[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = b2d(src[tid + 256 * k]);
-    tile_forward(v, s, tid, tile, logN1, tw + (size_t)i * N, N, m);
+    for (int k = 0; k < 8; k++) v[k] = b2d(src[tid + 512 * k]);
+    const double *W = tw + (size_t)i * N;
+    double tw3[7];
+    load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
+    tile_forward8(v, s, tws, tw3, tid, tile, logN1, W, N, m, [] {});
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = -s[pad16(wl) + 68 * k];
+    for (int k = 0; k < 8; k++) v[k] = -reduce_c(s[pad8(wl) + 72 * k], m);
 #pragma unroll 1
     for (int j = 0; j < rt.n; j++) {
         const uint64_t *a = rt.src[j] + ((size_t)z * rt.stride[j] + i) * N + t0 + wl;
         const double kw = rt.kw[j][i];
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] += mul_lazy(u2d(a[64 * k]), kw, m);
+        for (int k = 0; k < 8; k++) v[k] += mul_lazy(u2d(a[64 * k]), kw, m);
     }
     uint64_t *o = out + (size_t)w * N + t0 + wl;
     const uint64_t *add = rt.add ? rt.add + (size_t)w * N + t0 + wl : nullptr;
     const double wi = qlinv[level * nq + i], wiq = qlinvq[level * nq + i], cc = z & 1 ? 0.0 : rt.c[i];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
+    for (int k = 0; k < 8; k++) {
         double t = corr(mul_shoup_lazy(reduce_c(v[k], m), wi, wiq, m) + cc, m);
         if (add) t = add_mod(t, u2d(add[64 * k]), m);
         o[64 * k] = d2u(t);
@@ -1445,10 +1289,10 @@ hipError_t launch_ntt_fast(const nj_ctx *c, uint64_t *data, const uint64_t *src,
             if (e != hipSuccess) return e;
             src = nullptr;
         }
-        return launch(c, PROF_NTT_TILE, bytes, k_ntt_tile<false>, gt, dim3(kNT), s, data, src, lt, N1 > 1, tw, c->d_info,
+        return launch(c, PROF_NTT_TILE, bytes, k_ntt_tile<false>, gt, dim3(kNT8), s, data, src, lt, N1 > 1, tw, c->d_info,
                       c->log_n);
     }
-    e = launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, gt, dim3(kNT), s, data, src, lt, N1 > 1, tw, c->d_info,
+    e = launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, gt, dim3(kNT8), s, data, src, lt, N1 > 1, tw, c->d_info,
                c->log_n);
     if (e != hipSuccess || N1 == 1) return e;
     return launch_cols<true>(c, PROF_NTT_COL_INV, bytes, N1, gc, s, data, nullptr, lt, tw, c->d_info, c->log_n);
@@ -1459,7 +1303,7 @@ hipError_t launch_decrypt_fast(const nj_ctx *c, const uint64_t *ct, int level, u
 {
     const int N = c->N, N1 = N / kT, L1 = level + 1;
     if (N < kT) return hipErrorInvalidValue;
-    hipError_t e = launch(c, PROF_NTT_TILE_INV, 32.0 * N * L1, k_ntt_tile_dec, dim3(N1, L1), dim3(kNT), s, out, ct,
+    hipError_t e = launch(c, PROF_NTT_TILE_INV, 32.0 * N * L1, k_ntt_tile_dec, dim3(N1, L1), dim3(kNT8), s, out, ct,
                           (size_t)L1, c->d_s, c->d_itw, c->d_info, c->log_n);
     if (e != hipSuccess || N1 == 1) return e;
     const LimbTab lt = limbs_q(level);
@@ -1480,9 +1324,9 @@ hipError_t launch_intt_tiles(const nj_ctx *c, uint64_t *data, const uint64_t *sr
     if (N1 == 1)
         return launch(c, PROF_NTT_TILE_INV, bytes, k_intt_tile, dim3(lt.n), dim3(kNT8), s, data, src, lt,
                       gt ? *gt : GalTab{}, gt ? L1 : 0, scale, c->d_itw, c->d_info);
-    return gt ? launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile_gal, dim3(N1, lt.n), dim3(kNT), s, data, src, lt, *gt,
+    return gt ? launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile_gal, dim3(N1, lt.n), dim3(kNT8), s, data, src, lt, *gt,
                        L1, c->d_itw, c->d_info, c->log_n)
-              : launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, dim3(N1, lt.n), dim3(kNT), s, data, src, lt,
+              : launch(c, PROF_NTT_TILE_INV, bytes, k_ntt_tile<true>, dim3(N1, lt.n), dim3(kNT8), s, data, src, lt,
                        1, c->d_itw, c->d_info, c->log_n);
 }
 
@@ -1528,7 +1372,7 @@ hipError_t launch_rescale_fused(const nj_ctx *c, int level, const uint64_t *in, 
     if (e == hipSuccess && N1 > 1) e = launch_lift_col(c, last, level, n_polys, n_out, lifted, s);
     if (N1 == 1) lifted = last;
     if (e != hipSuccess) return e;
-    return launch(c, PROF_OTHER, 8.0 * N * n_polys * n_out * 4.0, k_ntt_tile_rs, dim3(N1, n_polys * n_out), dim3(kNT),
+    return launch(c, PROF_OTHER, 8.0 * N * n_polys * n_out * 4.0, k_ntt_tile_rs, dim3(N1, n_polys * n_out), dim3(kNT8),
                   s, lifted, in, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q, c->d_tw, c->d_info, c->log_n);
 }
 
@@ -1570,7 +1414,7 @@ hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uin
 #undef NJ_LS
     if (e != hipSuccess) return e;
     return launch(c, PROF_OTHER, 8.0 * N * P * n_out * (2.0 + rt.n + (rt.add ? 1 : 0)), k_ntt_tile_rsum,
-                  dim3(N1, P * n_out), dim3(kNT), s, out, rt, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q,
+                  dim3(N1, P * n_out), dim3(kNT8), s, out, rt, out, level, n_out, c->d_qlinv, c->d_qlinvq, c->n_q,
                   c->d_tw, c->d_info, c->log_n);
 }
 
@@ -1580,7 +1424,7 @@ hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, 
     const int N = c->N, N1 = N / kT;
     if (N1 < 1) return hipErrorInvalidValue;
     if (lt.n == 0) return hipSuccess;
-    return launch(c, PROF_NTT_TILE, 16.0 * N * lt.n, k_ntt_tile<false>, dim3(N1, lt.n), dim3(kNT), s, data, nullptr,
+    return launch(c, PROF_NTT_TILE, 16.0 * N * lt.n, k_ntt_tile<false>, dim3(N1, lt.n), dim3(kNT8), s, data, nullptr,
                   lt, 1, c->d_tw, c->d_info, c->log_n);
 }
 
@@ -1654,10 +1498,10 @@ hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv,
     }
     const double bytes = 8.0 * N * (n * 3.0 + K * (L1 - skip) + (acc ? n : 0));
     if (conj)
-        return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<true>, dim3(N1, n), dim3(kNT), s, conv, u_base, mj, acc,
+        return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<true>, dim3(N1, n), dim3(kNT8), s, conv, u_base, mj, acc,
                       level, L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip,
                       N1 > 1);
-    return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<false>, dim3(N1, n), dim3(kNT), s, conv, u_base, mj, acc, level,
+    return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<false>, dim3(N1, n), dim3(kNT8), s, conv, u_base, mj, acc, level,
                   L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip,
                       N1 > 1);
 }
@@ -1677,7 +1521,7 @@ hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64
             return launch(c, PROF_KEYIP, bytes, k_md_tile<ND>, dim3(n), dim3(kNT8), s, conv, c->moddown[level].hat, \
                           nullptr, kj, mj, 0, nullptr, level, c->L, c->alpha, c->d_pinv, c->d_pinvq, c->d_tw,      \
                           c->d_info, nullptr, c->d_itw, MdConj{nullptr, nullptr, nullptr});                        \
-        return launch(c, PROF_KEYIP, bytes, k_key_ip_md<ND>, dim3(N1, n), dim3(kNT), s, conv, kj, mj, level, c->L, \
+        return launch(c, PROF_KEYIP, bytes, k_key_ip_md<ND>, dim3(N1, n), dim3(kNT8), s, conv, kj, mj, level, c->L, \
                       c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n);
     switch (nd) {
         NJ_IPMD(1) NJ_IPMD(2) NJ_IPMD(3) NJ_IPMD(4)
@@ -1738,7 +1582,7 @@ hipError_t launch_key_ip_ptile(const nj_ctx *c, int level, const KeyJobs &kj, in
     const dim3 grid(2 * n_jobs, N1, c->alpha);
 #define NJ_PT(ND)                                                                                             \
     case ND:                                                                                                  \
-        return launch(c, PROF_KEYIP, bytes, k_key_ip_ptile<ND>, grid, dim3(kNT), s, kj, level, c->L, c->alpha, \
+        return launch(c, PROF_KEYIP, bytes, k_key_ip_ptile<ND>, grid, dim3(kNT8), s, kj, level, c->L, c->alpha, \
                       c->n_q, c->d_info, c->log_n, pout, c->d_itw, c->d_downscale);
     switch (nd) {
         NJ_PT(1) NJ_PT(2) NJ_PT(3) NJ_PT(4)
