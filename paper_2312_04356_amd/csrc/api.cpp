@@ -39,6 +39,11 @@ nj_status ks_fused(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
     return ks_down(c, l, K, mj, sum, acc, M, s, true, nullptr, conj);
 }
 
+// Lazy giant steps' c0 parts are summed where ModDown's combine adds them, up to NJ_MAX_GIANT of
+// them on the fused combine; else in a pass of their own.  N = 2^16: a batch of 11 32.8 -> 31.6 ms
+// (one pass per giant step there), conv + CoeffToSlot 3.17 -> 3.13 ms.
+static bool sum_in_md(const nj_ctx *c, size_t giants) { return c->N >= 4096 && giants <= NJ_MAX_GIANT; }
+
 // One key switch of tau_g(d) (d in evaluation form, level l) with `key`: ModUp,
 // inner product, ModDown, and out = (ModDown_0 + add read through X -> X^g_add,
 // ModDown_1) (add may be null).  The single-job case of the batched path, so it runs
@@ -207,7 +212,7 @@ nj_status ks_multi(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
 // evaluation-form digits instead of read from M.u; plain combine only).
 nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint64_t *acc, MultiBufs &M,
                   hipStream_t s, bool p_tiled, uint64_t *last_out, const MdConj *conj, bool drop, const KeyJobs *ipq,
-                  size_t acc_stride)
+                  size_t acc_stride, const MdSum *ms)
 {
     const int N = c->N, ne = l + 1 + c->alpha, al = c->alpha;
     const bool fused = N >= 4096 && al <= 8;  // as in modup_multi
@@ -219,6 +224,7 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
     if (ipq && (sum || acc || last_out || conj || drop || !fused || !fuse_ip(c, l)))
         return fail(NJ_EUNSUPPORTED, "ModDown: inner products in the combine need the plain fused combine");
     if (conj && !one) return fail(NJ_EUNSUPPORTED, "ModDown: the fused split needs one job, N >= 4096");
+    if (ms && (sum || ipq || N < 4096)) return fail(NJ_EUNSUPPORTED, "ModDown: summed c0 parts need the fused combine");
     // one job with a previous value held elsewhere: the fused combine reads it there
     const uint64_t *acc0 = one && acc && acc != mj.out[0] ? acc : nullptr;
     if (acc && !sum && K == 1 && acc != mj.out[0] && !one)
@@ -257,7 +263,7 @@ nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint
     }
     if (!sum && N >= 4096) {  // the combine runs inside the transform's tile pass
         NJ_HIP(launch_ntt_moddown(c, l, K, conv_in ? M.pc : M.conv, M.u, mj, acc != nullptr, fused, s, acc0, last_out, conj,
-                                  drop ? l - 1 : 0));
+                                  drop ? l - 1 : 0, ms));
         return NJ_OK;
     }
     auto ntt = [&](const LimbTab &t) { return fused ? launch_ntt_tiles(c, M.conv, t, s) : launch_ntt(c, M.conv, t, false, s); };
@@ -407,6 +413,9 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
         // are computed for those limbs (and the special primes) alone
         const bool dr = drop && fuse_ip(c, l) && N > 4096 && l >= 2 && !last_out;
         const int skip = dr ? l - 1 : 0;
+        MdSum ms;
+        ms.n = 0;
+        const bool in_md = sum_in_md(c, gl.size());
         for (size_t c0 = 0; c0 < gl.size(); c0 += kGiantChunk) {
             const int K = (int)std::min((size_t)kGiantChunk, gl.size() - c0);
             const bool f = fuse_ip(c, l);  // fused: tau_ge rides on ModUp and the own-limb reads
@@ -433,15 +442,19 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
             const bool last = c0 + K == gl.size();  // its special-prime rows go on to ModDown's inverse transform
             NJ_HIP(f ? launch_ntt_ip(c, l, kj, K, usum, 1, c0 ? 1 : 0, s, last ? M.pc : nullptr, skip, M.part)
                      : launch_key_ip_sum(c, l, kj, K, usum, c0 ? 1 : 0, s));
-            NJ_HIP(launch_automorph_acc(c, ac, K, l + 1, c0sum, 0, c0 ? 3 : 2, s, skip));
+            if (in_md)
+                for (int z = 0; z < K; z++) ms.off[ms.n] = gl[c0 + z] * clen, ms.g[ms.n++] = ac.g[z];
+            else
+                NJ_HIP(launch_automorph_acc(c, ac, K, l + 1, c0sum, 0, c0 ? 3 : 2, s, skip));
         }
         MultiBufs M1 = M;
         M1.u = usum;
         MdJobs mj;
-        mj.add[0] = c0sum, mj.g_add[0] = 1, mj.out[0] = out;
+        mj.add[0] = in_md ? inner : c0sum, mj.g_add[0] = 1, mj.out[0] = out;
         const bool hand = last_out && N >= 4096 && c->alpha <= 8;  // the rescale's first pass rides along
         if (hand && last_done) *last_done = true;
-        return ks_down(c, l, 1, mj, 0, acc, M1, s, fuse_ip(c, l), hand ? last_out : nullptr, nullptr, dr);
+        return ks_down(c, l, 1, mj, 0, acc, M1, s, fuse_ip(c, l), hand ? last_out : nullptr, nullptr, dr, nullptr, 0,
+                       in_md ? &ms : nullptr);
     }
     for (size_t c0 = 0; c0 < gl.size(); c0 += kGiantChunk) {
         const int K = (int)std::min((size_t)kGiantChunk, gl.size() - c0);
@@ -566,6 +579,9 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
     for (int g = 0; g < ng; g++)
         if (lt.giants[g] != 0) g_last = g;
     bool first = true;
+    MdSum ms;
+    ms.n = 0;
+    const bool in_md = sum_in_md(c, ng);
     for (int g = 0; g < ng; g++) {
         if (lt.giants[g] == 0) continue;
         const uint32_t ge = galois_of_rot(c, (long long)lt.giants[g] * lt.n1 * lt.u);
@@ -594,7 +610,10 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
                 NJ_HIP(launch_ntt_ip(c, l, kj, K, usum, 0, first ? 0 : 1, s, g == g_last ? M.pc : nullptr, 0, M.part));
             else
                 NJ_HIP(launch_key_ip_shared(c, l, kj, K, key_of(c, ge), usum, s, first ? 0 : 1));
-            NJ_HIP(launch_automorph_acc(c, ac, K, l + 1, c0sum, plen, first ? 0 : 1, s));
+            if (in_md)
+                ms.off[ms.n] = g * clen, ms.g[ms.n++] = ge;
+            else
+                NJ_HIP(launch_automorph_acc(c, ac, K, l + 1, c0sum, plen, first ? 0 : 1, s));
             first = false;
             continue;
         }
@@ -610,8 +629,13 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
         MultiBufs M1 = M;
         M1.u = usum;
         MdJobs mj;
-        for (int z = 0; z < K; z++) mj.add[z] = c0sum + z * plen, mj.g_add[z] = 1, mj.out[z] = out + z * clen;
-        if ((st = ks_down(c, l, K, mj, 0, have ? out : nullptr, M1, s, f))) return st;
+        for (int z = 0; z < K; z++) {
+            mj.add[z] = in_md ? inner_all + (size_t)z * ng * clen : c0sum + z * plen;
+            mj.g_add[z] = 1, mj.out[z] = out + z * clen;
+        }
+        if ((st = ks_down(c, l, K, mj, 0, have ? out : nullptr, M1, s, f, nullptr, nullptr, false, nullptr, 0,
+                          in_md ? &ms : nullptr)))
+            return st;
     }
     return NJ_OK;
 }

@@ -82,12 +82,14 @@ nj_status ks_multi(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
 // (sum = 0: for K = 1 it may be any ciphertext, else it must be the outputs).
 // last_out, one job, N >= 4096: the output's last limb also leaves through the first
 // 12 stages of its inverse transform into last_out [2][N], for rescale(last_pre))
+// ms, sum = 0, N >= 4096: what is added is a sum of polynomials (MdSum)
 // sum > 0: mj.out[g], g < sum, = acc + g acc_stride + the sum of the jobs g, g + sum, ..
 // drop: only output limbs 0 and l (the fused one-job combine, no last_out or conj, l >= 2;
 // the inner products' Q rows 0 and l and special-prime rows are all it reads)
 nj_status ks_down(nj_ctx *c, int l, int K, const MdJobs &mj, int sum, const uint64_t *acc, MultiBufs &M,
                   hipStream_t s, bool p_tiled = false, uint64_t *last_out = nullptr, const MdConj *conj = nullptr,
-                  bool drop = false, const KeyJobs *ipq = nullptr, size_t acc_stride = 0);
+                  bool drop = false, const KeyJobs *ipq = nullptr, size_t acc_stride = 0,
+                  const MdSum *ms = nullptr);
 
 // inner_g += diag_dg (.) baby_b for each entry, any number of baby and giant steps
 struct MacEntry {

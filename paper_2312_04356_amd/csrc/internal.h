@@ -214,6 +214,14 @@ struct RsTerms {
     const uint64_t *add;
 };
 
+// c0 parts of lazy giant steps summed inside the ModDown combine: job z adds the n polynomials
+// at add[z] + off[i], each read through X -> X^g[i], instead of add[z] alone
+struct MdSum {
+    int n;
+    size_t off[NJ_MAX_GIANT];
+    uint32_t g[NJ_MAX_GIANT];
+};
+
 struct MacPlan {
     int nb, ng;
     int dl;  // limbs per stored diagonal (the plan's encoding level + 1)
@@ -405,7 +413,8 @@ hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64
                                  const MdJobs &mj, hipStream_t s);
 hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv, const uint64_t *u_base,
                               const MdJobs &mj, int acc, int cols_done, hipStream_t s, const uint64_t *acc0 = nullptr,
-                              uint64_t *last_out = nullptr, const MdConj *conj = nullptr, int skip = 0);
+                              uint64_t *last_out = nullptr, const MdConj *conj = nullptr, int skip = 0,
+                              const MdSum *ms = nullptr);
 hipError_t launch_ntt_fast(const nj_ctx *c, uint64_t *data, const uint64_t *src, const LimbTab &lt, bool inverse,
                            hipStream_t s);
 // out = a op b per limb (op 0 add, 1 sub, 2 mul), evaluation form

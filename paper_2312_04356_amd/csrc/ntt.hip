@@ -859,6 +859,32 @@ __global__ __launch_bounds__(kBcCols * kBcWaves, 4) void k_bconv_col(BconvShared
     }
 }
 
+// The words a ModDown combine adds, summed over the terms of MdSum: canonical, words w0 + 64 k of
+// the limb at add (two terms requested at once).
+__device__ __forceinline__ void md_sum(double av[8], const uint64_t *add, const MdSum &ms, int w0, int logN, Mod m)
+{
+#pragma unroll
+    for (int k = 0; k < 8; k++) av[k] = 0.0;
+#pragma unroll 1
+    for (int q = 0; q < ms.n; q += 2) {
+        const bool two = q + 1 < ms.n;
+        const int q1 = two ? q + 1 : q;
+        const uint32_t g0 = ms.g[q], g1 = ms.g[q1], b0 = gal_base(w0, g0, logN), b1 = gal_base(w0, g1, logN);
+        uint64_t x[8], y[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            x[k] = add[ms.off[q] + gal_at(b0, 64 * k, g0, logN)];
+            y[k] = add[ms.off[q1] + gal_at(b1, 64 * k, g1, logN)];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[k] = add_mod(av[k], u2d(x[k]), m);
+        if (two) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) av[k] = add_mod(av[k], u2d(y[k]), m);
+        }
+    }
+}
+
 // ModDown of K key switches, finished inside the forward transform's tile pass.  The
 // converted limbs conv [K][2][l+1][N] (coefficient form, column pass already applied)
 // are transformed tile by tile and, instead of being stored, combined at once:
@@ -872,7 +898,7 @@ template <bool CONJ>
 __global__ __launch_bounds__(kNT8, 4) void k_ntt_tile_md(const uint64_t *conv, const uint64_t *u_base, MdJobs mj, int acc,
                                                      int level, int ne, const double *pinv, const double *pinvq,
                                                      const double *tw, const PrimeInfo *info, int logN, const uint64_t *acc0,
-                                                     uint64_t *last_out, const double *itw, MdConj cj, int skip, int part)
+                                                     uint64_t *last_out, const double *itw, MdConj cj, int skip, int part, MdSum ms)
 {
     __shared__ double s[kT + kT / 8];
     __shared__ double tws[kTw8R2];
@@ -898,18 +924,24 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_tile_md(const uint64_t *conv, c
         for (int k = 0; k < 8; k++) v[k] = b2d(in[tid + 512 * k]);
     }
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
-    uint64_t av[8];
-    if (add) {
-        const uint32_t g = mj.g_add[z], gb = gal_base((int)t0 + wl, g, logN);
-        add += (size_t)i * N;
-#pragma unroll
-        for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; k++) av[k] = 0;
-    }
     double tw3[7];
     load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
+    uint64_t av[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) av[k] = 0;
+    if (add) {
+        add += (size_t)i * N;
+        if (ms.n) {
+            double sum[8];
+            md_sum(sum, add, ms, (int)t0 + wl, logN, m);
+#pragma unroll
+            for (int k = 0; k < 8; k++) av[k] = d2u(sum[k]);
+        } else {
+            const uint32_t g = mj.g_add[z], gb = gal_base((int)t0 + wl, g, logN);
+#pragma unroll
+            for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
+        }
+    }
     tile_forward8(v, s, tws, tw3, tid, tile, logN1, W, N, m, [] {});
     uint64_t *out = mj.out[z] + ((size_t)p * L1 + i) * N + t0;
     const uint64_t *prev = acc0 && z == 0 ? acc0 + ((size_t)p * L1 + i) * N + t0 : out;
@@ -1015,16 +1047,16 @@ __global__ __launch_bounds__(kNT8, 4) void k_key_ip_md(const uint64_t *conv, Key
 
 // The ModDown combine on the ring of one tile, with its conversion: pc [2 K][alpha][N], the
 // special-prime rows after their inverse transform, canonical and scaled.  ND = 0: as
-// k_ntt_tile_md (u read, all its options); else the key inner products of ND extended
+// k_ntt_tile_md (u read, all its options; ND = -1: with MdSum); else the key inner products of ND extended
 // evaluation-form digits, as k_key_ip_md.  8 words per thread, everything requested before the
 // transform: a block alone on its compute unit waits for each round trip in full.  grid
 // 2 K (l+1) blocks.
 template <int ND>
-__global__ __launch_bounds__(kNT8, ND ? 2 : 4) void k_md_tile(const uint64_t *pc, const double *hat, const uint64_t *u_base,
+__global__ __launch_bounds__(kNT8, ND > 0 ? 2 : 4) void k_md_tile(const uint64_t *pc, const double *hat, const uint64_t *u_base,
                                                      KeyJobs kj, MdJobs mj, int acc, const uint64_t *acc0, int level,
                                                      int L, int alpha, const double *pinv, const double *pinvq,
                                                      const double *tw, const PrimeInfo *info, uint64_t *last_out,
-                                                     const double *itw, MdConj cj)
+                                                     const double *itw, MdConj cj, MdSum ms)
 {
     __shared__ double s[kT + kT / 8];
     __shared__ double tws[kTw8R2];
@@ -1036,7 +1068,7 @@ __global__ __launch_bounds__(kNT8, ND ? 2 : 4) void k_md_tile(const uint64_t *pc
     const double *W = tw + (size_t)i * kT;
     double a[8], v[8], tw3[7];
     load_twiddles8(tws, tw3, W, 0, 0, kT, tid);
-    if (ND == 0) {
+    if (ND <= 0) {
         const uint64_t *u = u_base + ((size_t)h * r.ne + i) * kT + wl;
 #pragma unroll
         for (int k = 0; k < 8; k++) a[k] = u2d(u[64 * k]);
@@ -1056,14 +1088,20 @@ __global__ __launch_bounds__(kNT8, ND ? 2 : 4) void k_md_tile(const uint64_t *pc
     }
     const uint64_t *add = p == 0 ? mj.add[z] : nullptr;
     uint64_t av[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) av[k] = 0;
     if (add) {
-        const uint32_t g = mj.g_add[z], gb = gal_base(wl, g, logN);
         add += (size_t)i * kT;
+        if (ND < 0) {
+            double sum[8];
+            md_sum(sum, add, ms, wl, logN, m);
 #pragma unroll
-        for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
-    } else {
+            for (int k = 0; k < 8; k++) av[k] = d2u(sum[k]);
+        } else {
+            const uint32_t g = mj.g_add[z], gb = gal_base(wl, g, logN);
 #pragma unroll
-        for (int k = 0; k < 8; k++) av[k] = 0;
+            for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
+        }
     }
     tile_convert<8>(v, pc + (size_t)h * alpha * kT, alpha, hat + i, L1, m, tid);
     tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
@@ -1472,7 +1510,7 @@ hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvP
 // as the transform followed by the combine.
 hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv, const uint64_t *u_base,
                               const MdJobs &mj, int acc, int cols_done, hipStream_t s, const uint64_t *acc0,
-                              uint64_t *last_out, const MdConj *conj, int skip)
+                              uint64_t *last_out, const MdConj *conj, int skip, const MdSum *ms)
 {
     const int N = c->N, N1 = N / kT, L1 = level + 1, n = 2 * K * (L1 - skip);
     if (N < kT || K < 1 || K > NJ_MAX_JOBS || ((last_out || conj) && K != 1) || (last_out && conj) || skip < 0 ||
@@ -1480,11 +1518,19 @@ hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv,
         return hipErrorInvalidValue;
     MdConj cj{nullptr, nullptr, nullptr};
     if (conj) cj = *conj;
+    MdSum msum;
+    msum.n = 0;
+    if (ms) msum = *ms;
+    if (msum.n < 0 || msum.n > NJ_MAX_GIANT) return hipErrorInvalidValue;
     if (N1 == 1 && cols_done) {
         if (skip || c->alpha > 8) return hipErrorInvalidValue;
-        return launch(c, PROF_NTT_MD, 8.0 * N * (n * 3.0 + K * L1 + (acc ? n : 0)), k_md_tile<0>, dim3(n), dim3(kNT8), s,
-                      conv, c->moddown[level].hat, u_base, KeyJobs{}, mj, acc, acc0, level, c->L, c->alpha, c->d_pinv,
-                      c->d_pinvq, c->d_tw, c->d_info, last_out, c->d_itw, cj);
+        const double b = 8.0 * N * (n * 3.0 + K * L1 * std::max(1, msum.n) + (acc ? n : 0));
+#define NJ_MDT(ND)                                                                                                   \
+    launch(c, PROF_NTT_MD, b, k_md_tile<ND>, dim3(n), dim3(kNT8), s, conv, c->moddown[level].hat, u_base, KeyJobs{}, \
+           mj, acc, acc0, level, c->L, c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, last_out, c->d_itw, cj,  \
+           msum)
+        return msum.n ? NJ_MDT(-1) : NJ_MDT(0);
+#undef NJ_MDT
     }
     if (N1 > 1 && !cols_done) {
         LimbTab lt;
@@ -1496,14 +1542,14 @@ hipError_t launch_ntt_moddown(const nj_ctx *c, int level, int K, uint64_t *conv,
             if (e != hipSuccess) return e;
         }
     }
-    const double bytes = 8.0 * N * (n * 3.0 + K * (L1 - skip) + (acc ? n : 0));
+    const double bytes = 8.0 * N * (n * 3.0 + K * (L1 - skip) * std::max(1, msum.n) + (acc ? n : 0));
     if (conj)
         return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<true>, dim3(N1, n), dim3(kNT8), s, conv, u_base, mj, acc,
                       level, L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip,
-                      N1 > 1);
+                      N1 > 1, msum);
     return launch(c, PROF_NTT_MD, bytes, k_ntt_tile_md<false>, dim3(N1, n), dim3(kNT8), s, conv, u_base, mj, acc, level,
                   L1 + c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n, acc0, last_out, c->d_itw, cj, skip,
-                      N1 > 1);
+                      N1 > 1, msum);
 }
 
 // The plain ModDown combine of K key switches (converted limbs column-passed) with their
@@ -1520,7 +1566,7 @@ hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64
         if (N1 == 1)                                                                                               \
             return launch(c, PROF_KEYIP, bytes, k_md_tile<ND>, dim3(n), dim3(kNT8), s, conv, c->moddown[level].hat, \
                           nullptr, kj, mj, 0, nullptr, level, c->L, c->alpha, c->d_pinv, c->d_pinvq, c->d_tw,      \
-                          c->d_info, nullptr, c->d_itw, MdConj{nullptr, nullptr, nullptr});                        \
+                          c->d_info, nullptr, c->d_itw, MdConj{nullptr, nullptr, nullptr}, MdSum{});               \
         return launch(c, PROF_KEYIP, bytes, k_key_ip_md<ND>, dim3(N1, n), dim3(kNT8), s, conv, kj, mj, level, c->L, \
                       c->alpha, c->d_pinv, c->d_pinvq, c->d_tw, c->d_info, c->log_n);
     switch (nd) {
