@@ -23,23 +23,24 @@ def family(name):
     n = re.sub(r"k_ntt_col<\d+, (false|true)(, (false|true))?>", r"k_ntt_col<\1>", n)
     n = re.sub(r"k_ntt_tile_md<(false|true)>", "k_ntt_tile_md", n)
     n = n.strip()
-    if n == "k_ntt_tile_gal":  # ModUp's inverse tile pass through X -> X^g
+    n = re.sub(r"k_md_tile<(0|-1)>", "k_ntt_tile_md", n)
+    if n in ("k_ntt_tile_gal", "k_intt_tile", "k_ntt_tile_dec"):  # inverse tile passes with work on the way in
         return "k_ntt_tile<true>"
     # the same families the library's HIP-event counters use
-    if n.startswith("k_bconv"):
+    if n.startswith("k_bconv") or n == "k_conv_tile":
         return "k_bconv"
-    if n.startswith("k_key_ip") or n.startswith("k_ntt_ip"):
+    if n.startswith(("k_key_ip", "k_ntt_ip", "k_md_tile")) or n in ("k_conv_ip", "k_ip_reduce"):
         return "k_key_ip"
     if n.startswith("k_bsgs_mac"):
         return "k_pmac"
-    if n in OTHER or n.startswith("k_lift_col"):
+    if n in OTHER or n.startswith(("k_lift_col", "k_lift_sum")):
         return "other"
     return n
 
 
 # kernels the library times together under "other"
 OTHER = ("k_moddown_multi", "k_automorph_multi", "k_automorph_acc", "k_tensor", "k_mul_int",
-         "k_add_int", "k_zero", "k_ntt_tile_rs")
+         "k_add_int", "k_zero", "k_ntt_tile_rs", "k_ntt_tile_rsum")
 
 
 def main(trace, bench_json, plain_json, command):
