@@ -382,14 +382,14 @@ hipError_t launch_ntt_tiles(const nj_ctx *c, uint64_t *data, const LimbTab &lt, 
 hipError_t launch_bconv_col(const nj_ctx *c, const BconvShared &sh, const BconvPtrs &jp, int n_jobs,
                             const double *scale, hipStream_t s);
 // key inner products fused with the extended digits' forward tile pass (N >= 4096,
-// 1..4 digits, every g = 1): per job u_base + z 2 ne N, or (sum) one output summed over
-// the jobs; accumulate adds to the output's previous value
-hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u, int sum,
+// 1..4 digits): output o at u + o 2 ne N sums the jobs o per .. o per + per - 1; accumulate adds
+// to the output's previous value
+hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u, int per,
                          int accumulate, hipStream_t s, uint64_t *pout = nullptr, int skip = 0,
                          uint64_t *part = nullptr);
 // (part: N = 4096, room for the unsummed products, [n_jobs][digits][2][ne][N]; pout given: the
 // special-prime rows skip u and leave through the first 12 stages of ModDown's inverse
-// transform, job z's halves at rows (2 z + p) alpha + a of pout (N = 4096: canonical and
+// transform, output o's halves at rows (2 o + p) alpha + a of pout (N = 4096: canonical and
 // scaled); skip > 0, N >= 8192: Q limbs 1..skip are not computed, skip = l - 1 keeping Q
 // limbs 0 and l)
 // special-prime rows of n_jobs key inner products whose digits are extended and in

@@ -328,12 +328,12 @@ __device__ __forceinline__ void ip_request_x(const KeyJobs &kj, const IpRow &r, 
 // the converted limb ext_z[j][t] of tau_g(d_z), which arrives with only its column
 // pass applied: the block finishes that tile's transform in LDS and
 // multiplies it by the key words at once, so extended digits are never stored in
-// evaluation form.  Grid (jobs, N/4096, l+1+alpha-skip): grid row 0 is limb 0, row r > 0
+// evaluation form.  Grid (outputs, N/4096, l+1+alpha-skip): grid row 0 is limb 0, row r > 0
 // limb r + skip (skip = l - 1: only Q limbs 0 and l and the special primes, what a
-// rescale followed by a drop to level 0 reads).  SUM: u = (accumulate ? u : 0) +
-// the sum over all jobs (one block per tile); else job z = blockIdx.x has its own u_z
-// = u_base + z 2 ne N (plus its previous value when accumulate): jobs vary fastest, so
-// jobs sharing one key read each key tile close together in time.  After each job the
+// rescale followed by a drop to level 0 reads).  Output o =
+// blockIdx.x, u_base + o 2 ne N, is (accumulate ? itself : 0) + the sum of the jobs o per ..
+// (SUM; else job o alone): outputs vary fastest, so those sharing keys read each key tile
+// close together in time.  After each job the
 // running sums take at most ND <= 4 lazy terms on a reduced value.
 // A block works through its (job, digit) steps one after another, and both the memory
 // stream (32 KB of digit and 64 KB of key words a step) and the transform take most of a
@@ -345,7 +345,7 @@ __device__ __forceinline__ void ip_request_x(const KeyJobs &kj, const IpRow &r, 
 // ahead, 236 this way, when the memory stream alone takes 228; one key switch at level 20
 // 48 and 39 us.  Non-temporal key words and digits: 216 and 33 us.
 template <int ND, bool SUM, bool NT>
-__global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint64_t *u_base, int accumulate, int level,
+__global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int per, uint64_t *u_base, int accumulate, int level,
                                                  int L, int alpha, int nq, const double *tw, const PrimeInfo *info,
                                                  int logN, uint64_t *pout, const double *itw, int skip)
 {
@@ -362,8 +362,8 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint
     const int wl = wv8(tid);
     double *sw = s + pad8(wl);
     const size_t w0 = t0 + wl;
-    const int z0 = SUM ? 0 : (int)blockIdx.x, z1 = SUM ? n_jobs : z0 + 1;
-    uint64_t *u = u_base + (SUM ? 0 : (size_t)z0 * 2 * r.ne * N);
+    const int z0 = SUM ? (int)blockIdx.x * per : (int)blockIdx.x, z1 = z0 + (SUM ? per : 1);
+    uint64_t *u = u_base + (size_t)blockIdx.x * 2 * r.ne * N;
     const size_t o0 = r.t * N + w0, o1 = (r.ne + r.t) * N + w0;
     const int q0 = z0 * ND, q1 = z1 * ND;
     double tw3[7], a0[8], a1[8];
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int n_jobs, uint
         if (j == ND - 1) reduce8(a0, m), reduce8(a1, m);
     }
     if (pout && t > level) {  // special-prime rows: on to ModDown's inverse transform
-        uint64_t *out = pout + ((size_t)2 * z0 * alpha + (t - level - 1)) * N + t0 + tid;
+        uint64_t *out = pout + ((size_t)2 * blockIdx.x * alpha + (t - level - 1)) * N + t0 + tid;
         const double *iW = itw + (size_t)pidx * N;
         tile_inverse8(a0, s, tid, tile, logN1, iW, N, m);
 #pragma unroll
@@ -1577,15 +1577,17 @@ hipError_t launch_key_ip_moddown(const nj_ctx *c, int level, int K, const uint64
 }
 
 // Key inner products of n_jobs jobs (digits of tau_g(d) column-passed only, own limbs
-// read from d through X -> X^g) fused with the digits' tile pass; sum = 1: one output,
-// summed over the jobs; accumulate: added to the output's previous value.
-hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u, int sum,
+// read from d through X -> X^g) fused with the digits' tile pass; output o sums the jobs
+// o per .. o per + per - 1; accumulate: added to the output's previous value.
+hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jobs, uint64_t *u, int per,
                          int accumulate, hipStream_t s, uint64_t *pout, int skip, uint64_t *part)
 {
     const int N = c->N, N1 = N / kT, nd = n_digits(c, level), ne = level + 1 + c->alpha;
-    if (N1 < 1 || nd < 1 || nd > 4 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || skip < 0 || skip > std::max(0, level - 1))
+    if (N1 < 1 || nd < 1 || nd > 4 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || per < 1 || n_jobs % per ||
+        skip < 0 || skip > std::max(0, level - 1))
         return hipErrorInvalidValue;
-    const double bytes = 8.0 * N * (ne - skip) * (3.0 * nd * n_jobs + 2.0 * (sum ? 1 : n_jobs) * (1 + accumulate));
+    const int n_out = n_jobs / per;
+    const double bytes = 8.0 * N * (ne - skip) * (3.0 * nd * n_jobs + 2.0 * n_out * (1 + accumulate));
     if (N1 == 1) {
         if (!part || skip || c->alpha > 8) return hipErrorInvalidValue;
         IpTiles it;
@@ -1593,20 +1595,21 @@ hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jo
         hipError_t e = launch(c, PROF_KEYIP, bytes, k_conv_ip, dim3(n_jobs, ne, nd), dim3(kNT8), s, kj, it, part, level,
                               c->L, c->alpha, c->n_q, c->d_tw, c->d_info);
         if (e != hipSuccess) return e;
-        return launch(c, PROF_KEYIP, 16.0 * N * ne * (nd * n_jobs + (sum ? 1 : n_jobs)), k_ip_reduce,
-                      dim3(sum ? 1 : n_jobs, 2 * ne), dim3(kNT8), s, part, sum ? nd * n_jobs : nd, u, accumulate, level,
+        return launch(c, PROF_KEYIP, 16.0 * N * ne * (nd * n_jobs + n_out), k_ip_reduce,
+                      dim3(n_out, 2 * ne), dim3(kNT8), s, part, nd * per, u, accumulate, level,
                       c->alpha, c->n_q, c->d_info, pout, c->d_itw, c->d_downscale);
     }
-    const dim3 grid(sum ? 1 : n_jobs, N1, ne - skip);
+    const dim3 grid(n_out, N1, ne - skip);
     // key words stay in the caches only for the jobs that share them (a batch: 33.3 ms cached,
     // 35.8 non-temporal; giant steps with a key each at N = 2^14: 0.78 and 0.75 ms a step)
-    const bool shared = !sum && n_jobs > 1 && kj.key[0] == kj.key[1];
+    const bool shared = n_out > 1 && kj.key[0] == kj.key[per];
 #define NJ_IP_K(ND, SUM, NT)                                                                                         \
-    launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, SUM, NT>, grid, dim3(kNT8), s, kj, n_jobs, u, accumulate, level, c->L, \
+    launch(c, PROF_KEYIP, bytes, k_ntt_ip<ND, SUM, NT>, grid, dim3(kNT8), s, kj, per, u, accumulate, level, c->L, \
            c->alpha, c->n_q, c->d_tw, c->d_info, c->log_n, pout, c->d_itw, skip)
 #define NJ_IP(ND)                                                                                                   \
     case ND:                                                                                                        \
-        return sum ? NJ_IP_K(ND, true, true) : shared ? NJ_IP_K(ND, false, false) : NJ_IP_K(ND, false, true);
+        return per > 1 ? (shared ? NJ_IP_K(ND, true, false) : NJ_IP_K(ND, true, true))                              \
+                       : (shared ? NJ_IP_K(ND, false, false) : NJ_IP_K(ND, false, true));
     switch (nd) {
         NJ_IP(1) NJ_IP(2) NJ_IP(3) NJ_IP(4)
     }
