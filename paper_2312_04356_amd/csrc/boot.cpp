@@ -412,9 +412,10 @@ size_t eval_mod_words(const nj_ctx *c, int l0, int K = 1)
     return (Ev::slots_needed() + 4 * kBranchSlots + kTreeSlots) * slot + (1 + kBranchWorkers) * eval_ks_words(c, l0, K);
 }
 
-// ModEval of K ciphertexts in[z] (level l0, scale s0) evaluated together (packed; K > 1
-// needs N >= 4096): out[z] at level l0 - 11
-nj_status eval_mod(nj_ctx *c, int K, const uint64_t *const *in, int l0, double s0, double Kr, const double *cf,
+// ModEval of K ciphertexts in[z] (level l0, scale s0[z]) evaluated together (packed; K > 1
+// needs N >= 4096): out[z] at level l0 - 11, scale out_scale[z].  The evaluation itself reads
+// every input at scale Kr q_0, so only the result's recorded scale depends on s0.
+nj_status eval_mod(nj_ctx *c, int K, const uint64_t *const *in, int l0, const double *s0, double Kr, const double *cf,
                    uint64_t *const *out, double *out_scale, Arena A, hipStream_t s)
 {
     const size_t N = c->N, slot = K * 2 * N * (l0 + 1), pool = Ev::slots_needed() * slot;
@@ -453,9 +454,10 @@ nj_status eval_mod(nj_ctx *c, int K, const uint64_t *const *in, int l0, double s
         g = h;
     }
     if (!ev.ok()) return ev.err;
-    for (int z = 0; z < K; z++)
+    for (int z = 0; z < K; z++) {
         NJ_HIP(hipMemcpyAsync(out[z], g.d + z * ev.cstride(g.l), 2 * N * (g.l + 1) * 8, hipMemcpyDeviceToDevice, s));
-    *out_scale = g.s * (2.0 * M_PI) * s0 / q0;
+        out_scale[z] = g.s * (2.0 * M_PI) * s0[z] / q0;
+    }
     return NJ_OK;
 }
 
@@ -562,7 +564,7 @@ nj_status nj_eval_mod(nj_ctx *c, const nj_ct *in, int K, int r, const double *co
     double sc = 0.0;
     const uint64_t *ins[1] = {in->data};
     uint64_t *outs[1] = {out->data};
-    if ((st = eval_mod(c, 1, ins, in->level, in->scale, (double)K, cf.data(), outs, &sc, A, S(stream)))) return st;
+    if ((st = eval_mod(c, 1, ins, in->level, &in->scale, (double)K, cf.data(), outs, &sc, A, S(stream)))) return st;
     out->level = in->level - kEvalModLevels, out->is_ntt = 1, out->scale = sc;
     return NJ_OK;
 }
@@ -581,7 +583,9 @@ nj_status nj::ex::eval_mod_pair(nj_ctx *c, const nj_ct *re, const nj_ct *im, int
     }
     st = check_ct(c, re, "nj_eval_mod");
     if (st || (st = check_ct(c, im, "nj_eval_mod"))) return st;
-    if (re->level != im->level || re->scale != im->scale) return fail(NJ_ELEVEL, "eval_mod_pair: Re and Im differ");
+    // (the smallest packed ring takes scales that differ, as nj_combine does later on)
+    if (re->level != im->level || (c->N > 4096 && re->scale != im->scale))
+        return fail(NJ_ELEVEL, "eval_mod_pair: Re and Im differ");
     if (K < 1 || r != 3 || (coeffs && n_coeffs != kChebDegree + 1))
         return fail(NJ_EUNSUPPORTED, "nj_eval_mod: supports r = 3 double angles and 64 Chebyshev coefficients");
     if (re->level < kEvalModLevels + 1) return fail(NJ_ELEVEL, "nj_eval_mod: needs input level >= 12");
@@ -594,11 +598,12 @@ nj_status nj::ex::eval_mod_pair(nj_ctx *c, const nj_ct *re, const nj_ct *im, int
     if (!ok) return fail(NJ_ENOMEM, "scratch");
     const uint64_t *ins[2] = {re->data, im->data};
     uint64_t *outs[2] = {out_re->data, out_im->data};
-    double sc = 0.0;
-    if ((st = eval_mod(c, 2, ins, re->level, re->scale, (double)K, cf.data(), outs, &sc, A, S(stream)))) return st;
+    const double s0[2] = {re->scale, im->scale};
+    double sc[2];
+    if ((st = eval_mod(c, 2, ins, re->level, s0, (double)K, cf.data(), outs, sc, A, S(stream)))) return st;
     out_re->level = out_im->level = re->level - kEvalModLevels;
     out_re->is_ntt = out_im->is_ntt = 1;
-    out_re->scale = out_im->scale = sc;
+    out_re->scale = sc[0], out_im->scale = sc[1];
     return NJ_OK;
 }
 
