@@ -305,21 +305,32 @@ __device__ __forceinline__ void tile_convert(double v[W], const uint64_t *in, in
 // Requests the words of step q = z ND + j of a key inner product (job z, digit j) of one
 // tile into LDS (xb, in memory order): the extended digit's tile ([ND][ne][N], as it came out
 // of its column pass), or for the job's own limb the tile that X -> X^g reads (it moves whole
-// tiles).  16 bytes per lane straight to LDS: no registers held while they are under way.
-template <int ND>
+// tiles).  Straight to LDS, so no registers are held while they are under way: 16 bytes per
+// lane, or 4 where ANY8 allows a polynomial of the caller's, only known to be 8-byte aligned,
+// to start at an odd word (the digits and summed jobs' polynomials lie in the library's
+// scratch, whole limbs from its start).
+template <int ND, bool ANY8>
 __device__ __forceinline__ void ip_request_x(const KeyJobs &kj, const IpRow &r, int q, int tile, int tid, int logN,
                                              double *xb)
 {
+    using lds = __attribute__((address_space(3))) void *;
     const size_t N = (size_t)1 << logN;
     const int z = q / ND, j = q - z * ND;
     const uint64_t *p = j == r.own ? kj.d[z] + r.t * N + (galois_src2(tile * kT, kj.g[z], logN) & ~(kT - 1))
                                    : kj.ext[z] + (j * r.ne + r.t) * N + tile * kT;
     const auto rs = buf_rsrc(p, 8u * kT);
-    const uint32_t c0 = 4096u * __builtin_amdgcn_readfirstlane(tid >> 6), vo = 16u * (tid & 63);
+    const uint32_t c0 = 4096u * __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    if (!ANY8 || ((uintptr_t)p & 15) == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; i++)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(xb + (c0 + 1024u * i) / 8u),
-                                                 16, vo, c0 + 1024u * i, 0, 0);
+        for (int i = 0; i < 4; i++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds)(xb + (c0 + 1024u * i) / 8u), 16, 16u * lane,
+                                                     c0 + 1024u * i, 0, 0);
+    } else {
+#pragma unroll 1
+        for (int i = 0; i < 16; i++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds)(xb + (c0 + 256u * i) / 8u), 4, 4u * lane, c0 + 256u * i,
+                                                     0, 0);
+    }
 }
 
 // Key inner products fused with the forward tile pass of the extended digits (N >=
@@ -350,7 +361,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int per, uint64_
                                                  int logN, uint64_t *pout, const double *itw, int skip)
 {
     __shared__ double s[kT + kT / 8];
-    __shared__ double xb[kT];
+    __shared__ __align__(16) double xb[kT];
     __shared__ double tws[kTw8R2];
     const int N = 1 << logN, logN1 = logN - 12;
     const int t = blockIdx.z == 0 ? 0 : (int)blockIdx.z + skip, tile = blockIdx.y, tid = threadIdx.x;
@@ -368,7 +379,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int per, uint64_
     const int q0 = z0 * ND, q1 = z1 * ND;
     double tw3[7], a0[8], a1[8];
     load_twiddles8(tws, tw3, W, tile, logN1, N, tid);
-    ip_request_x<ND>(kj, r, q0, tile, tid, logN, xb);
+    ip_request_x<ND, !SUM>(kj, r, q0, tile, tid, logN, xb);
     if (accumulate) {
 #pragma unroll
         for (int k = 0; k < 8; k++) a0[k] = u2d(u[o0 + 64 * k]), a1[k] = u2d(u[o1 + 64 * k]);
@@ -400,7 +411,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_ntt_ip(KeyJobs kj, int per, uint64_
 #pragma unroll
         for (int k = 0; k < 8; k++) kb[k] = buf_ld<NT>(key, vb, 512u * k);
         auto next = [&]() {
-            if (q + 1 < q1) ip_request_x<ND>(kj, r, q + 1, tile, tid, logN, xb);
+            if (q + 1 < q1) ip_request_x<ND, !SUM>(kj, r, q + 1, tile, tid, logN, xb);
         };
         if (own) {
 #pragma unroll
@@ -1586,6 +1597,8 @@ hipError_t launch_ntt_ip(const nj_ctx *c, int level, const KeyJobs &kj, int n_jo
     if (N1 < 1 || nd < 1 || nd > 4 || n_jobs < 1 || n_jobs > NJ_MAX_JOBS || per < 1 || n_jobs % per ||
         skip < 0 || skip > std::max(0, level - 1))
         return hipErrorInvalidValue;
+    for (int z = 0; per > 1 && z < n_jobs; z++)
+        if ((uintptr_t)kj.d[z] & 15) return hipErrorInvalidValue;  // (ip_request_x: scratch, always aligned)
     const int n_out = n_jobs / per;
     const double bytes = 8.0 * N * (ne - skip) * (3.0 * nd * n_jobs + 2.0 * n_out * (1 + accumulate));
     if (N1 == 1) {
