@@ -9,9 +9,10 @@
 // FP64 operations, about 1.8x the throughput of a 64-bit Shoup product built from
 // 32-bit integer multiplies (measured: 3.2 vs 1.8 T products/s).
 //
-// Bounds used below (u = 2^-53, every modulus t in [2^40, 2^50)):
+// Bounds used below (u = 2^-53, every modulus t < 2^50; contexts take primes from 2^30 on):
 //   mul_canon:  a, b in [0, t)              -> |ab/t - c| < 7/8, result in [0, t)
-//   mul_lazy:   |a| <= 2^50, b in [0, t)    -> exact representative in (-t, t)
+//   mul_lazy:   |a| <= B 2^50, b in [0, t)  -> exact representative within (1/2 + 3B/8) t, B <= 8
+//               (7/8 t at B = 1; corr may follow directly only for B < 4/3, else reduce)
 //   corr:       integer s in (-t, 2t)       -> [0, t)
 //   reduce:     integer |x| < 2^53          -> [0, t)
 //   reduce_c:   integer |x| < 2^53          -> centred, |r| <= t/2 + 2 (half of reduce's cost)
@@ -76,9 +77,10 @@ NJ_HD double mul_shoup(double b, double w, double wq, Mod m)
     return corr(fma(-c, m.t, h) + l, m);
 }
 
-// Lazy product for signed operands |a| < 2^50, |b| < t: returns an exact
-// representative of a*b mod t in (-2t, 2t).  |ab/t| < 2^50, quotient error
-// < 3u 2^50 < 1/2, so |ab - ct| < t; h - ct and the sum stay below 2^52.
+// Lazy product for signed operands |a| <= B 2^50, |b| < t, B <= 8: returns an exact
+// representative of a*b mod t.  |ab/t| <= B 2^50 is estimated to within 3u B 2^50 = 3B/8 and
+// rounded, so |ab - ct| <= (1/2 + 3B/8) t; c is at most 2^53, |l| at most 2^49, and h - ct and
+// the sum stay integers below 2^53.
 NJ_HD double mul_lazy(double a, double b, Mod m)
 {
     double h = a * b;
@@ -87,7 +89,7 @@ NJ_HD double mul_lazy(double a, double b, Mod m)
     return fma(-c, m.t, h) + l;
 }
 
-// any exact integer |x| < 2^52  ->  x mod t in [0, t)
+// any exact integer |x| < 2^53  ->  x mod t in [0, t)
 NJ_HD double reduce(double x, Mod m)
 {
     double c = rint(x * m.ti);
