@@ -271,35 +271,34 @@ __global__ __launch_bounds__(kNT8) void k_ntt_tile(uint64_t *data, const uint64_
 
 // Rings of one tile (N = 4096) have no column pass, and their launches are a few blocks each:
 // what bounds them is the chain of launches, so the basis conversion runs inside the kernels
-// that transform its result.  v = words tid + 256 k of sum_a x_a hat[a n_out] mod t, centred: x_a
+// that transform its result.  v = words tid + 512 k of sum_a x_a hat[a n_out] mod t, centred: x_a
 // the canonical words of limb a of `in` ([m][N], scaled by launch_intt_tiles), m <= 8.
-template <int W>  // words per thread: tid + (4096 / W) k
-__device__ __forceinline__ void tile_convert(double v[W], const uint64_t *in, int m, const double *hat, int n_out,
+__device__ __forceinline__ void tile_convert(double v[8], const uint64_t *in, int m, const double *hat, int n_out,
                                              Mod mo, int tid)
 {
-    constexpr int kA = W == 8 ? 4 : 2;  // limbs requested at once
+    constexpr int kA = 4;  // limbs requested at once
 #pragma unroll
-    for (int k = 0; k < W; k++) v[k] = 0.0;
+    for (int k = 0; k < 8; k++) v[k] = 0.0;
 #pragma unroll 1
     for (int a = 0; a < m; a += kA) {
-        uint64_t x[kA][W];
+        uint64_t x[kA][8];
         double h[kA];
 #pragma unroll
         for (int i = 0; i < kA; i++) {
             const int ai = min(a + i, m - 1);
             h[i] = a + i < m ? const_tab(hat)[ai * n_out] : 0.0;
 #pragma unroll
-            for (int k = 0; k < W; k++) x[i][k] = in[(size_t)ai * kT + tid + kT / W * k];
+            for (int k = 0; k < 8; k++) x[i][k] = in[(size_t)ai * kT + tid + 512 * k];
         }
 #pragma unroll
         for (int i = 0; i < kA; i++) {
             if (a + i >= m) break;
 #pragma unroll
-            for (int k = 0; k < W; k++) v[k] += mul_lazy(u2d(x[i][k]), h[i], mo);
+            for (int k = 0; k < 8; k++) v[k] += mul_lazy(u2d(x[i][k]), h[i], mo);  // 8 products within 7/8 t
         }
     }
 #pragma unroll
-    for (int k = 0; k < W; k++) v[k] = reduce_c(v[k], mo);
+    for (int k = 0; k < 8; k++) v[k] = reduce_c(v[k], mo);
 }
 
 // Requests the words of step q = z ND + j of a key inner product (job z, digit j) of one
@@ -490,7 +489,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_conv_ip(KeyJobs kj, IpTiles it, uin
     } else {
         const int a0 = j * alpha, mj = min(alpha, level + 1 - a0);
         load_twiddles8(tws, tw3, W, 0, 0, kT, tid);
-        tile_convert<8>(v, kj.ext[z] + (size_t)a0 * kT, mj, it.hat[j] + (t < a0 ? t : t - mj), level + 1 + alpha - mj,
+        tile_convert(v, kj.ext[z] + (size_t)a0 * kT, mj, it.hat[j] + (t < a0 ? t : t - mj), level + 1 + alpha - mj,
                         m, tid);
         tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
 #pragma unroll
@@ -584,7 +583,7 @@ __global__ __launch_bounds__(kNT8, 4) void k_conv_tile(BconvShared sh, BconvPtrs
     const Mod m = info[pidx].m;
     double v[8], tw3[7];
     load_twiddles8(tws, tw3, W, 0, 0, kT, tid);
-    tile_convert<8>(v, jp.in[z] + (size_t)sh.in_off0[j] * kT, sh.m[j], sh.hat[j] + o, sh.n_out[j], m, tid);
+    tile_convert(v, jp.in[z] + (size_t)sh.in_off0[j] * kT, sh.m[j], sh.hat[j] + o, sh.n_out[j], m, tid);
     tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
     uint64_t *out = jp.out[z] + (size_t)sh.out_off[j][o] * kT + wv8(tid);
 #pragma unroll
@@ -1114,7 +1113,7 @@ __global__ __launch_bounds__(kNT8, ND > 0 ? 2 : 4) void k_md_tile(const uint64_t
             for (int k = 0; k < 8; k++) av[k] = add[gal_at(gb, 64 * k, g, logN)];
         }
     }
-    tile_convert<8>(v, pc + (size_t)h * alpha * kT, alpha, hat + i, L1, m, tid);
+    tile_convert(v, pc + (size_t)h * alpha * kT, alpha, hat + i, L1, m, tid);
     tile_forward8(v, s, tws, tw3, tid, 0, 0, W, kT, m, [] {});
     const size_t o = ((size_t)p * L1 + i) * kT + wl;
     const uint64_t *prev = acc0 && z == 0 ? acc0 : mj.out[z];
