@@ -145,9 +145,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *base, uin
 // dirty in the 256 MiB last-level cache and is written back while the next kernel reads:
 // 341 MB of words written and then read beside 682 MB of keys took 226 us to read, 182 with
 // non-temporal stores, 165 with non-temporal key loads as well; the writes themselves took
-// 53 us either way.  No size was found where the extended digits or keys do better cached:
-// with both non-temporal from 0, 64, 128 or 256 MB per launch on, a rotation at N = 2^16
-// takes 118.6, 121.7, 121.5, 123.5 us, the benchmark's step 3.25, 3.26, 3.28, 3.39 ms.
+// 53 us either way.  For keys that no two jobs of a launch share, and their extended digits,
+// no size was found where they do better cached: with both non-temporal from 0, 64, 128 or 256
+// MB per launch on, a rotation at N = 2^16 takes 118.6, 121.7, 121.5, 123.5 us, the benchmark's
+// step 3.25, 3.26, 3.28, 3.39 ms.  Keys that jobs share are another matter (launch_ntt_ip).
 template <bool NT = false>
 __device__ __forceinline__ uint64_t buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {

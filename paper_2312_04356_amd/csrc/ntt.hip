@@ -347,10 +347,11 @@ __device__ __forceinline__ void ip_request_x(const KeyJobs &kj, const IpRow &r, 
 // running sums take at most ND <= 4 lazy terms on a reduced value.
 // A block works through its (job, digit) steps one after another, and both the memory
 // stream (32 KB of digit and 64 KB of key words a step) and the transform take most of a
-// step, so they have to overlap: a step's key words are requested before its transform, the
-// next step's digit words, straight to LDS, as soon as this step's have left it.  8 words
-// per thread leave room for that in 128 registers (4 waves per SIMD, two blocks per CU by
-// LDS); with 16 per thread at 2 waves per SIMD it spills.  7 giant steps at level 23 of N =
+// step, so they have to overlap: the b half of a step's key words is requested before its
+// transform, the next step's digit words, straight to LDS, as soon as this step's have left
+// it.  8 words per thread leave room for that in 128 registers (4 waves per SIMD, two blocks
+// per CU by LDS), but not for the a half, which is requested after the transform (before it:
+// 18 registers spilled, 259 us); with 16 words per thread at 2 waves per SIMD it spills.  7 giant steps at level 23 of N =
 // 2^16 (704 MB of keys, 352 MB of digits): 258 us with 256 threads and neither request
 // ahead, 236 this way, when the memory stream alone takes 228; one key switch at level 20
 // 48 and 39 us.  Non-temporal key words and digits: 216 and 33 us.
@@ -624,7 +625,12 @@ __global__ __launch_bounds__(kNT8) void k_ntt_tile_dec(uint64_t *data, const uin
 // 12 stages of ModDown's inverse transform into row (2 z + p) alpha + a of pout, as
 // launch_ntt_ip does with its special-prime rows.  The products never go to memory in
 // evaluation form.  Grid (2 jobs, N/4096, alpha): blockIdx.x = 2 z + p, so the two
-// halves of one tile, which read the same digit words, are dispatched together.
+// halves of one tile, which read the same digit words, are dispatched together.  Key words
+// are non-temporal here and in k_key_ip_md, for rotations of one ciphertext, each with a key
+// of its own.  Block convs give one key to every input's job and would do a little better
+// with cached loads (16 diagonals per block; non-temporal / cached): 8 x 1 blocks at levels 1
+// and 23 of N = 2^16 412 / 403 us and 2.40 / 2.32 ms, 4 x 4 395 / 393 us and 2.82 / 2.80 ms; 2
+// x 3 blocks of 20 babies at level 11 of N = 2^13 236 / 216 us.
 template <int ND>
 __global__ __launch_bounds__(kNT8, 4) void k_key_ip_ptile(KeyJobs kj, int level, int L, int alpha, int nq,
                                                          const PrimeInfo *info, int logN, uint64_t *pout,
@@ -1446,7 +1452,9 @@ hipError_t launch_rescale_sum(const nj_ctx *c, int level, const RsTerms &rt, uin
     hipError_t e = launch_intt_tiles(c, last, base, lt, s);
     if (e != hipSuccess) return e;
     // the inverse column passes are repeated per target chunk: two chunks for many terms,
-    // two targets at a time, as launch_lift_col, for one or two
+    // two targets at a time, as launch_lift_col, for one or two.  (For many terms it hardly
+    // matters: a layer with 2 targets, 4 targets, a quarter of them, half of them or all of
+    // them per block 8.637, 8.624, 8.592, 8.605 and 8.615 ms.)
     const int per = rt.n > 2 ? (n_out + 1) / 2 : 2;
     const dim3 g(kT / kNT, (n_out + per - 1) / per, P);
     const double b = 8.0 * N * P * (rt.n + n_out);
