@@ -44,6 +44,12 @@ nj_status ks_fused(nj_ctx *c, int l, int K, const KeyJobs &kj, const MdJobs &mj,
 // (one pass per giant step there), conv + CoeffToSlot 3.17 -> 3.13 ms.
 static bool sum_in_md(const nj_ctx *c, size_t giants) { return c->N >= 4096 && giants <= NJ_MAX_GIANT; }
 
+// giant steps of a transform that rotate
+static size_t rotating(const nj_lt_t &lt)
+{
+    return lt.giants.size() - std::count(lt.giants.begin(), lt.giants.end(), 0);
+}
+
 // One key switch of tau_g(d) (d in evaluation form, level l) with `key`: ModUp,
 // inner product, ModDown, and out = (ModDown_0 + add read through X -> X^g_add,
 // ModDown_1) (add may be null).  The single-job case of the batched path, so it runs
@@ -322,7 +328,7 @@ size_t bsgs_words(const nj_ctx *c, const nj_lt_t &lt)
 {
     const size_t N = c->N, l = lt.level, ne = l + 1 + c->alpha;
     return N * 2 * (l + 1) * (lt.babies.size() + lt.giants.size()) + multi_words(c, l, bsgs_jobs(lt)) +
-           (lt.lazy ? N * (2 * ne + l + 1) : 0);
+           (lt.lazy ? N * (2 * ne + (sum_in_md(c, rotating(lt)) ? 0 : l + 1)) : 0);
 }
 
 // sum_d diag_d (.) (in <<< j_d u), baby-step giant-step; out must not alias in.
@@ -406,8 +412,9 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
         return NJ_OK;
     }
     if (lt.lazy) {  // key inner products summed over Q_l u P, one ModDown
-        uint64_t *usum = A.take(2 * ne * N), *c0sum = A.take(plen);
-        if (!c0sum) return fail(NJ_ENOMEM, "scratch too small");
+        const bool in_md = sum_in_md(c, gl.size());
+        uint64_t *usum = A.take(2 * ne * N), *c0sum = in_md ? nullptr : A.take(plen);
+        if (!usum || (!in_md && !c0sum)) return fail(NJ_ENOMEM, "scratch too small");
         // drop: the output goes on to a rescale and a drop to level 0, which read only its
         // Q limbs 0 and l; the giant steps' digits, inner products, c0 sums and ModDown
         // are computed for those limbs (and the special primes) alone
@@ -415,7 +422,6 @@ nj_status bsgs_apply(nj_ctx *c, const nj_lt_t &lt, const uint64_t *in, uint64_t 
         const int skip = dr ? l - 1 : 0;
         MdSum ms;
         ms.n = 0;
-        const bool in_md = sum_in_md(c, gl.size());
         for (size_t c0 = 0; c0 < gl.size(); c0 += kGiantChunk) {
             const int K = (int)std::min((size_t)kGiantChunk, gl.size() - c0);
             const bool f = fuse_ip(c, l);  // fused: tau_ge rides on ModUp and the own-limb reads
@@ -511,7 +517,7 @@ size_t bsgs_batch_words(const nj_ctx *c, const nj_lt_t &lt, int K)
     const size_t N = c->N, l = lt.level, clen = 2 * N * (l + 1);
     if (!batch_mac_fits(lt)) return bsgs_words(c, lt);
     return clen * K * (lt.babies.size() + lt.giants.size()) + multi_words(c, l, K * batch_pairs(c, lt, (int)l, K)) +
-           (lt.lazy ? N * K * (2 * (l + 1 + c->alpha) + l + 1) : 0);
+           (lt.lazy ? N * K * (2 * (l + 1 + c->alpha) + (sum_in_md(c, rotating(lt)) ? 0 : l + 1)) : 0);
 }
 
 nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *in, uint64_t *out, Arena A,
@@ -573,10 +579,12 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
                                     hipMemcpyDeviceToDevice, s));
             have = true;
         }
+    const bool in_md = sum_in_md(c, rotating(lt));
     uint64_t *usum = nullptr, *c0sum = nullptr;
     if (lt.lazy) {
-        usum = A.take(N * K * 2 * ne), c0sum = A.take(N * K * (l + 1));
-        if (!c0sum) return fail(NJ_ENOMEM, "scratch too small");
+        usum = A.take(N * K * 2 * ne);
+        if (!in_md) c0sum = A.take(N * K * (l + 1));
+        if (!usum || (!in_md && !c0sum)) return fail(NJ_ENOMEM, "scratch too small");
     }
     // fused (N >= 4096): tau_ge rides on ModUp's inverse transform and on the own-limb
     // reads, and the key inner product (one key, one job per ciphertext) runs the digits'
@@ -586,7 +594,6 @@ nj_status bsgs_apply_batch(nj_ctx *c, const nj_lt_t &lt, int K, const uint64_t *
     bool first = true;
     MdSum ms;
     ms.n = 0;
-    const bool in_md = sum_in_md(c, ng);
     const int per = batch_pairs(c, lt, l, K);
     std::vector<int> gl;
     for (int g = 0; g < ng; g++)
