@@ -176,7 +176,9 @@ nj_status nj_apply_galois(nj_ctx *ctx, const nj_ct *in, uint32_t galois_elt, nj_
  * threads, any context) race and must be serialised by the caller.  Nothing in it needs
  * clearing between calls.  NJ_EUNSUPPORTED when the key switch needs more scratch than
  * the array holds (ModUp digits, inner products and ModDown limbs at level l: about
- * (2(l+1) + dnum_l (l+1+alpha) + 2(l+1+alpha) + 2 alpha + 3(l+1)) N words) or while live
+ * (2(l+1) + dnum_l (l+1+alpha) + 2(l+1+alpha) + 2 alpha + 3(l+1)) N words, and at N = 4096
+ * with alpha <= 8 another 2 min(dnum_l, 4) (l+1+alpha) N for unsummed products, which never
+ * reaches the array's size there) or while live
  * profiling is on; otherwise the errors of nj_apply_galois. */
 nj_status nj_apply_galois_noalloc(nj_ctx *ctx, const nj_ct *in, uint32_t galois_elt, nj_ct *out, void *stream);
 /* Key switching of one polynomial d (evaluation form, level l): (out0, out1) with

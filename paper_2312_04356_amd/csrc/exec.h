@@ -26,7 +26,8 @@ struct Arena {
 // Buffers for K jobs at level l: polynomials to switch d [K][l+1], their
 // coefficient form [K][l+1], extended digits [K][dnum][l+1+alpha], inner
 // products [K][2][l+1+alpha], special-prime limbs [K][2][alpha], converted limbs
-// [K][2][l+1] (all x N words).
+// [K][2][l+1], and on the ring of one tile (N = 4096, alpha <= 8) the unsummed products
+// [K][min(dnum, 4)][2][l+1+alpha] (all x N words).
 struct MultiBufs {
     uint64_t *d, *coef, *ext, *u, *pc, *conv, *part;
 };
