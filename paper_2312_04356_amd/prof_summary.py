@@ -44,7 +44,7 @@ OTHER = ("k_moddown_multi", "k_automorph_multi", "k_automorph_acc", "k_tensor", 
 
 
 def main(trace, bench_json, plain_json, command):
-    rows = list(csv.DictReader(open(trace)))
+    rows = sorted(csv.DictReader(open(trace)), key=lambda r: int(r["Start_Timestamp"]))  # the trace is not in order
     bench = json.loads(open(bench_json).read().strip().splitlines()[-1])
     plain = json.loads(open(plain_json).read().strip().splitlines()[-1])
     steps = bench["steps"]
